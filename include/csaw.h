@@ -232,12 +232,12 @@ csaw_status csaw_sample_noalloc(csaw_graph g, const csaw_sample_args* args, csaw
  * HOST out: max_edges. */
 csaw_status csaw_sample_bound(csaw_graph g, const csaw_sample_args* args, int64_t* max_edges);
 
-/* Work assignment of the sampling kernel by degree bucket (the frontier
- * queue of Section III-A, with sub-wave groups for small lists). A frontier
- * entry whose work -- the candidates of a take-all list or of a weighted
- * draw, the slots of an unbiased draw -- is at most bound16 is served by 16
- * lanes, four entries to a wavefront; at most bound32, by 32 lanes; the
- * others by a whole wavefront (or the long-list path). 0 turns a bucket off.
+/* Work assignment of the sampling kernels by degree bucket (the frontier
+ * queue of Section III-A). Draws take a lane per slot, several entries to a
+ * wavefront: every unbiased list, every weighted list whose weight array has
+ * its walk guide, and the weighted lists without one of at most
+ * max(bound16, bound32) candidates, which each lane scans. The other weighted
+ * lists take a whole wavefront each. 0 for both leaves the scan out.
  * Results never depend on these bounds (the draws are keyed by their
  * counters and taken in slot order either way); only the speed does.
  * The setting belongs to the graph and applies to later calls. */
@@ -320,10 +320,11 @@ csaw_status csaw_walk(csaw_graph g, const csaw_walk_args* args, int32_t* paths,
  * prefixes: the same pick as a search of the whole prefix. About 48 bytes
  * per edge per weight array (51 GB for 2^30 edges); with the guide off (or
  * not yet built in a caller memory call) walks take the chunk tables with
- * one wavefront per walker, with the same paths. Sampling calls draw from
- * the long lists (more than 512 edges) of a weight array through its guide
- * when it is built and on (a walk or a server builds it), else through the
- * chunk tables: the same edges either way.
+ * one wavefront per walker, with the same paths. Sampling calls draw
+ * through a weight array's guide when it is built and on (a walk or a server
+ * builds it, or csaw_sample once its calls have sampled m / 4 edges by that
+ * array and the tables fit half of the free device memory), else from the
+ * weights and the chunk tables: the same edges either way.
  * enable: 1 (default) or 0. A walk already running keeps its route. INVALID_ARG
  * otherwise. Turning the guide off does not free built tables. */
 csaw_status csaw_set_walk_guides(csaw_graph g, int32_t enable);

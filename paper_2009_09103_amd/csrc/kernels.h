@@ -174,9 +174,10 @@ struct SampleLayer {
     int64_t nwp;                     // bitmap words per instance (multiple of 4)
     uint32_t* summ;                  // [ni * nsw] summary bitmap of next (sparse builds) or null
     int64_t nsw;
-    int32_t group16, group32;        // sub-wave bucket bounds (<= 16, <= 32; 0 = off)
+    int32_t group16, group32;        // longest list without a guide that a lane scans: the larger of the two (0: none)
     int32_t rounds;                  // repeated-sampling rounds (0: every slot by direct draw)
     uint32_t burn;                   // forest fire threshold (0: fixed fanout)
+    int32_t weighted;                // some instance draws by weight
     int32_t vlo, vhi;                // entries of vertices in [vlo, vhi) only (out-of-memory schedule)
 };
 
@@ -202,16 +203,22 @@ void launch_mark_seeds(const int32_t* seeds, int64_t num_seeds, const int64_t* s
 int64_t frontier_build_blocks(int64_t words);
 int64_t dirty_compact_blocks(int64_t summary_words);
 int64_t sparse_build_blocks(int64_t capacity);
-// Bitmap words (all instances) above which frontier builds are sparse.
-constexpr int64_t kSparseWords = int64_t(1) << 23;
+// Bitmap words (all instances) above which frontier builds are sparse: one
+// instance of a 2^25-vertex graph or eight of a 2^22-vertex one. A dense build
+// reads every word; 37 instances on R-MAT 22 (4.8M words) take 48 and 69 us a
+// layer densely, 17 and 25 us through the summary and the dirty words.
+constexpr int64_t kSparseWords = int64_t(1) << 20;
 void launch_frontier_build(const FrontierBuild& fb, hipStream_t s, LaunchEvents ev = {});
+// Every entry that a lane per slot serves (all but the weighted draws below).
 void launch_select(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev = {});
-void launch_select_small(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev = {});
 // Chunk prefix table of every list longer than kWaveMaxD (GraphDev::gtab_*),
 // rows ((m >> kTabShift) + 1) * kChunkGroups uint64.
 int64_t chunk_table_rows(int64_t m);
 void launch_chunk_table(RowPtr rowptr, const uint32_t* w, int64_t n, uint64_t* tab, uint64_t* ctab,
                         hipStream_t s);
+// Weighted draws from lists without a walk guide that are too long for a lane
+// to scan: the list in a wavefront's registers, or searched through the
+// chunk prefix table. The layer needs it only where needs_list_kernels says so.
 void launch_select_big(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev = {});
 // Clears the visited bits of every frontier entry of the call's layers.
 struct ClearVisited {
@@ -243,6 +250,9 @@ void launch_partition_work(const int32_t* fv, const int32_t* cnt, const SampleCt
                            hipStream_t s);
 
 // --- graph preparation (sample_kernels.hip)
+// Weak: a host build whose launchers are stand-ins may leave a weak function
+// out (null); the runtime then does without what it serves.
+__attribute__((weak)) size_t free_device_bytes();
 void launch_degree_weights(RowPtr rowptr, const int32_t* col, int64_t m, uint32_t* degw,
                            hipStream_t s);
 void launch_positive_counts(RowPtr rowptr, const uint32_t* w, int64_t n, int32_t* ppos, uint64_t* wtot,

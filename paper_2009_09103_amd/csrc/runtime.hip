@@ -235,12 +235,14 @@ struct csaw_graph_s {
     WalkVertex* wvtx_deg = nullptr;
     WalkBucket* wgd_ew = nullptr;
     WalkBucket* wgd_deg = nullptr;
-    std::mutex mu;                       // lazy preparation + workspace pool
+    mutable std::mutex mu;               // lazy preparation + workspace pool
     std::vector<Workspace*> pool;
     std::atomic<int32_t> bound16{kDefaultBound16}, bound32{kDefaultBound32};  // sub-wave buckets
     std::atomic<int32_t> walk_guides{1};  // weighted walks build and use the walk guides
+    std::atomic<int64_t> drawn_ew{0}, drawn_deg{0};  // edges that csaw_sample calls sampled, per weight array
 
     GraphDev dev() const {
+        std::lock_guard<std::mutex> lk(mu);  // a table may be appearing under another call
         GraphDev g;
         g.n = n;
         g.m = m;
@@ -417,6 +419,7 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     if (hipMalloc((void**)&rec, (size_t)g->m * sizeof(WalkEdge)) != hipSuccess ||
         (small && hipMalloc((void**)&vtx, (size_t)std::max<int64_t>(g->n, 1) * sizeof(WalkVertex)) != hipSuccess) ||
         hipMalloc((void**)&gd, (size_t)(kGuideBucketsPerEdge * g->m + g->n) * sizeof(WalkBucket)) != hipSuccess) {
+        (void)hipGetLastError();  // the caller may go on without the tables
         if (rec) (void)hipFree(rec);
         if (vtx) (void)hipFree(vtx);
         return fail(CSAW_ERR_OUT_OF_MEMORY, "walk guide tables: allocation failed");
@@ -433,6 +436,23 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     (dg ? g->wvtx_deg : g->wvtx_ew) = vtx;
     (dg ? g->wgd_deg : g->wgd_ew) = gd;
     return CSAW_OK;
+}
+
+// Sampling calls draw through the walk guide too, but do without it until
+// their weighted draws have paid for it: building it costs about what m / 4
+// sampled edges gain (R-MAT 22, 65M edges: 4 ms and 4 GB of allocations against
+// 0.2 ms per million edges), and it is left out where it would take more than
+// half of the device memory that is free. A failure leaves the chunk tables.
+void guides_for_sampling(csaw_graph g, int32_t kind, hipStream_t s) {
+    const std::atomic<int64_t>& drawn = kind == kNeighborDegree ? g->drawn_deg : g->drawn_ew;
+    if (!g->walk_guides.load() || drawn.load() < g->m / 4 || !free_device_bytes) return;
+    {
+        std::lock_guard<std::mutex> lk(g->mu);
+        if (kind == kNeighborDegree ? g->wgd_deg : g->wgd_ew) return;
+    }
+    const size_t bytes = (size_t)g->m * sizeof(WalkEdge) + (size_t)g->n * sizeof(WalkVertex) +
+                         (size_t)(kGuideBucketsPerEdge * g->m + g->n) * sizeof(WalkBucket);
+    if (bytes <= free_device_bytes() / 2 && prepare_walk_guides(g, kind, s) != CSAW_OK) t_err.clear();
 }
 
 int64_t sat_mul(int64_t a, int64_t b) {
@@ -747,7 +767,16 @@ csaw_status csaw_sample_bound(csaw_graph g, const csaw_sample_args* a, int64_t* 
 // stream, launched directly, no allocation of any kind on the device.
 struct Streamer;
 static csaw_status stream_layer(Streamer& st, const SampleLayer& p, int32_t l, int64_t cap, bool big_path,
-                                bool uses_ew, bool uses_deg, int32_t b16, int32_t b32, hipStream_t s);
+                                bool uses_ew, bool uses_deg, hipStream_t s);
+
+// Blocks of a selection launch over at most cap entries: a wavefront per entry
+// while they fit the chip's 8,192 resident ones (small launches are bound by one
+// wavefront's chain of loads), then up to twice that many for the dispatcher to
+// balance, each taking a run of consecutive entries.
+constexpr int kSelectBlocks = 4096;
+static int select_grid(int64_t cap, int most) {
+    return (int)std::min<int64_t>(std::max<int64_t>((cap + 3) / 4, 1), most);
+}
 
 static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sample_out* out, csaw_stream stream,
                                char* scratch, size_t scratch_bytes, Streamer* streamer = nullptr) {
@@ -773,6 +802,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     } else {
         if (P.uses_deg && (st = prepare_bias(g, kNeighborDegree, s)) != CSAW_OK) return st;
         if (P.uses_ew && (st = prepare_bias(g, kEdgeWeight, s)) != CSAW_OK) return st;
+        if (P.uses_deg && !streamer) guides_for_sampling(g, kNeighborDegree, s);
+        if (P.uses_ew && !streamer) guides_for_sampling(g, kEdgeWeight, s);
     }
 
     const int32_t ni = P.ni, L = P.L;
@@ -783,6 +814,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         HIP_OR_FAIL(hipStreamSynchronize(s));
         return CSAW_OK;
     }
+    const GraphDev gd = g->dev();
     const int64_t nwp = bitmap_words_per_instance(g->n);
     const int64_t words = nwp * ni;
     SampleLayout lay;
@@ -795,9 +827,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                  o_bigs = lay.o_bigs;
     const std::vector<size_t>& o_fv = lay.o_fv;
     const std::vector<size_t>& o_fi = lay.o_fi;
-    // weighted calls can have long-list entries (lists longer than kWaveMaxD,
-    // or with a total weight of 2^32 or more)
-    const bool big_path = P.uses_deg || P.uses_ew;
+    // weighted draws from lists without a walk guide
+    const bool big_path = (P.uses_deg && !gd.wgd_deg) || (P.uses_ew && !gd.wgd_ew);
     const size_t o_hctl = align_up(tab_bytes, 64);
     Workspace* ws = nullptr;
     char* A = nullptr;
@@ -863,7 +894,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                               (uint32_t*)(A + o_tab), (int64_t)(tab_bytes / 4), s);
 
         FrontierBuild fb;
-        fb.g = g->dev();
+        fb.g = gd;
         fb.next = next;
         fb.visited = visited;
         fb.nwords = words;
@@ -902,7 +933,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
             build(0, LaunchEvents{});
         }
         SampleLayer p;
-        p.g = g->dev();
+        p.g = gd;
         p.num_instances = ni;
         p.inst_id = (const uint32_t*)(A + o_tab + t_iid);
         p.inst_key = (const uint64_t*)(A + o_tab + t_key);
@@ -926,6 +957,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         p.group32 = b32;
         p.rounds = P.rounds;
         p.burn = a->burn_threshold;
+        p.weighted = P.uses_deg || P.uses_ew;
         p.vlo = 0;  // every vertex (an out-of-memory schedule narrows it per partition)
         p.vhi = INT32_MAX;
         int computed_layers = 1;  // frontiers F_0 .. F_{computed_layers-1} exist
@@ -937,7 +969,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
             p.fi = (const int32_t*)(A + o_fi[l]);
             const int64_t cap = P.fcap[l];
             if (streamer) {  // out of memory: partition by partition, each once resident
-                if ((st = stream_layer(*streamer, p, l, cap, big_path, P.uses_ew, P.uses_deg, b16, b32, s)) != CSAW_OK)
+                if ((st = stream_layer(*streamer, p, l, cap, big_path, P.uses_ew, P.uses_deg, s)) != CSAW_OK)
                     return st;
                 if (l + 1 < L && P.fcap[l + 1] > 0) {
                     build(l + 1, LaunchEvents{});
@@ -945,32 +977,23 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                 }
                 continue;
             }
-            // the long-list path and the wavefront kernel touch disjoint outputs:
+            // the long-list path and the slot kernel touch disjoint outputs:
             // run them side by side (scratch calls: one after the other)
-            hipStream_t aux = scratch ? s : ws->aux;
-            if (!scratch) {
+            const bool beside = big_path && !scratch;
+            hipStream_t aux = beside ? ws->aux : s;
+            if (beside) {
                 HIP_OR_FAIL(hipEventRecord(ws->fork, s));
                 HIP_OR_FAIL(hipStreamWaitEvent(aux, ws->fork, 0));
             }
             if (big_path) {
                 ProfScope ps("select_big", aux, true);
-                launch_select_big(p, (int)std::min<int64_t>(std::max<int64_t>((cap + 3) / 4, 1), 2048), aux,
-                                  ps.ev());
-            }
-            if (b16 > 0 || b32 > 0) {
-                ProfScope ps("select_small", s, true);
-                // one wavefront per run of 64 entries, up to the resident slots
-                const int grid = (int)std::min<int64_t>(std::max<int64_t>((cap + 255) / 256, 1), 2048);
-                launch_select_small(p, grid, s, ps.ev());
+                launch_select_big(p, select_grid(cap, 2048), aux, ps.ev());
             }
             {
-                ProfScope ps("select_wave", s, true);
-                // more wavefronts than resident slots (the dispatcher balances them),
-                // each taking a short run of consecutive entries
-                const int grid = (int)std::min<int64_t>(std::max<int64_t>((cap + 3) / 4, 1), 4096);
-                launch_select(p, grid, s, ps.ev());
+                ProfScope ps("select_slots", s, true);
+                launch_select(p, select_grid(cap, kSelectBlocks), s, ps.ev());
             }
-            if (!scratch) {
+            if (beside) {
                 HIP_OR_FAIL(hipEventRecord(ws->join, aux));
                 HIP_OR_FAIL(hipStreamWaitEvent(s, ws->join, 0));
             }
@@ -1022,7 +1045,6 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
             // the graph's arrays are baked into the kernel arguments too; the
             // bias tables of a weight array appear on its first use, so a
             // sequence captured before then must not serve a later call
-            const GraphDev gd = g->dev();
             for (const void* q : {gd.rowptr.data(), (const void*)gd.col, (const void*)gd.ew, (const void*)gd.degw,
                                   (const void*)gd.ppos_ew, (const void*)gd.ppos_deg, (const void*)gd.gtab_ew,
                                   (const void*)gd.gtab_deg, (const void*)gd.wtot_ew, (const void*)gd.wtot_deg,
@@ -1061,6 +1083,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     rel.clean = true;
     out->num_edges = L > 0 ? h_ctl->out_base[L] : 0;
     if (out->num_edges < 0) return fail(CSAW_ERR_DEVICE, "the device reported a negative edge count");
+    if (P.uses_deg) g->drawn_deg += out->num_edges;
+    if (P.uses_ew) g->drawn_ew += out->num_edges;
     if (h_ctl->bad_seed) return fail(CSAW_ERR_INVALID_ARG, "a seed is outside [0, n)");
     if (h_ctl->unsupported)
         return fail(CSAW_ERR_UNSUPPORTED, "a drawn fanout exceeds %d", CSAW_MAX_FANOUT);
@@ -1197,7 +1221,7 @@ csaw_status load_partition(csaw_pgraph pg, csaw_pgraph_s::Slot& x, int32_t q, bo
 }  // namespace
 
 static csaw_status stream_layer(Streamer& st, const SampleLayer& p, int32_t l, int64_t cap, bool big_path,
-                                bool uses_ew, bool uses_deg, int32_t b16, int32_t b32, hipStream_t s) {
+                                bool uses_ew, bool uses_deg, hipStream_t s) {
     csaw_pgraph pg = st.pg;
     const int32_t np = pg->np;
     // the layer's work per partition
@@ -1251,10 +1275,8 @@ static csaw_status stream_layer(Streamer& st, const SampleLayer& p, int32_t l, i
         pp.g.wgd_ew = pp.g.wgd_deg = nullptr;
         pp.vlo = (int32_t)pg->vb[q];
         pp.vhi = (int32_t)std::min<int64_t>(pg->vb[q + 1], INT32_MAX);
-        if (big_path) launch_select_big(pp, (int)std::min<int64_t>(std::max<int64_t>((cap + 3) / 4, 1), 2048), s);
-        if (b16 > 0 || b32 > 0)
-            launch_select_small(pp, (int)std::min<int64_t>(std::max<int64_t>((cap + 255) / 256, 1), 2048), s);
-        launch_select(pp, (int)std::min<int64_t>(std::max<int64_t>((cap + 3) / 4, 1), 4096), s);
+        if (big_path) launch_select_big(pp, select_grid(cap, 2048), s);
+        launch_select(pp, select_grid(cap, kSelectBlocks), s);
         HIP_OR_FAIL(hipGetLastError());
         HIP_OR_FAIL(hipEventRecord(x.idle, s));  // the slot may be reloaded after this
     }

@@ -5,15 +5,14 @@
 //                    edge count min(k, P), edge offset, list fields and
 //                    route (one pass with a decoupled look-back);
 //                    visited |= next
-//   select         : one wavefront per frontier vertex: EdgeBias, exact
-//                    prefix, Philox draws, inverse transform search,
-//                    collision rounds, direct draw from the updated prefix;
-//                    writes the edges and marks new neighbors in the
-//                    instance's next bitmap. Small entries are served by
-//                    sub-wave groups (select_small); weighted lists longer
-//                    than kWaveMaxD, or with a total weight of 2^32 or more,
-//                    one wavefront each (select_big), searched through the
-//                    graph's chunk prefix tables.
+//   select         : EdgeBias, exact prefix, Philox draws, inverse transform
+//                    search, collision rounds, direct draw from the updated
+//                    prefix; writes the edges and marks new neighbors in the
+//                    instance's next bitmap. A lane per slot, several
+//                    entries to a wavefront (k_select_slots); weighted lists
+//                    without a walk guide that are too long for a lane to scan
+//                    take a wavefront each, in registers (k_select_wave) or
+//                    through the graph's chunk prefix tables (k_select_big).
 // Frontier entries are (vertex, instance) pairs sorted by (instance, vertex),
 // so edges come out in (layer, instance, source, slot) order without a sort.
 #include "device_common.h"
@@ -599,9 +598,8 @@ __global__ void __launch_bounds__(kBlock) k_dirty_compact(FrontierBuild fb) {
 }
 
 // ----------------------------------------------------------------- select
-// Lists of the wavefront kernel (weighted d <= kWaveMaxD, and every unbiased
-// list) are searched in registers (draw_resident) or directly (r is the
-// position for unbiased lists). Long lists use a coarse table: groups of
+// Lists of k_select_wave (weighted, d <= kWaveMaxD) are searched in registers
+// (draw_resident). Long lists without a walk guide use a coarse table: groups of
 // g = 16 consecutive candidates, C[t] = S[t*g] (exclusive prefix at the group
 // starts) and C[nc] = W in LDS; a search finds the group by binary search in
 // C and the candidate by scanning the group's weights from global memory / L2.
@@ -843,16 +841,17 @@ __device__ __forceinline__ int32_t draw_resident(const uint32_t* __restrict__ w,
     return draw_resident_t<E, uint32_t>(x, incl - (uint32_t)ls, W, key, c0, c1, c2, k, rounds);
 }
 
-// A picked neighbor joins the instance's next bitmap unless it is visited or
-// already there: picks concentrate on hubs, and skipping those atomics keeps
-// them from queueing on a few hot words. (The frontier build also masks
-// visited vertices.)
-__device__ __forceinline__ void claim(bool do_claim, const uint32_t* visb, uint32_t* nextb, uint32_t* summb,
-                                      int32_t x) {
+// A picked neighbor joins the instance's next bitmap unless it is already
+// there: picks concentrate on hubs, and skipping those atomics keeps them from
+// queueing on a few hot words. Visited vertices join too and are masked by the
+// frontier build: testing the visited bit here reads a second random line per
+// pick (batched R-MAT 22: 2 x 50M lines of a 4 GB pair of bitmaps) to save few
+// atomics.
+__device__ __forceinline__ void claim(bool do_claim, uint32_t* nextb, uint32_t* summb, int32_t x) {
     if (!do_claim) return;
     const uint32_t bit = 1u << (x & 31);
     const int64_t wd = x >> 5;
-    if (!((visb[wd] | nextb[wd]) & bit)) {
+    if (!(nextb[wd] & bit)) {
         // the claim that makes a word non-zero records it in the summary (sparse builds)
         const uint32_t old = atomicOr(&nextb[wd], bit);
         if (summb && old == 0u) atomicOr(&summb[wd >> 5], 1u << (wd & 31));
@@ -903,7 +902,8 @@ struct EntryRun {
     uint64_t key;
 };
 
-template <bool kBurn>
+// An entry's edge count c is k when it draws and P when it takes every positive
+// candidate, so c < P tells the two apart.
 __device__ __forceinline__ void load_run(const SampleLayer& p, int64_t e, bool valid, int64_t out_base,
                                          EntryRun& R) {
     R.c = valid ? p.cnt[e] : 0;
@@ -918,57 +918,12 @@ __device__ __forceinline__ void load_run(const SampleLayer& p, int64_t e, bool v
     R.c0 = 0;
     R.key = 0;
     if (R.c) {
-        R.k = p.fanout[R.inst];
+        R.k = R.c < (R.pinfo & ~kWideList) ? R.c : -1;
         R.kind = p.bias[R.inst];
         R.do_claim = p.fanout_next[R.inst] != 0;
         R.key = p.inst_key[R.inst];
         R.c0 = p.inst_id[R.inst];
-        R.k = neighbor_size<kBurn>(R.k, p.burn, R.key, (uint32_t)R.c0, p.layer, R.v);
     }
-}
-
-// A run kept in LDS (one array per field), so that its fields need no
-// registers while the wavefront works through the run.
-struct RunLds {
-    int32_t c[kWave], v[kWave], inst[kWave], pinfo[kWave], k[kWave], kind[kWave], do_claim[kWave], c0[kWave],
-        d[kWave];
-    int64_t o[kWave], beg[kWave];
-    uint64_t key[kWave];
-};
-
-__device__ __forceinline__ void store_run(RunLds& L, const EntryRun& R, int lane) {
-    L.c[lane] = R.c;
-    L.v[lane] = R.v;
-    L.inst[lane] = R.inst;
-    L.pinfo[lane] = R.pinfo;
-    L.k[lane] = R.k;
-    L.kind[lane] = R.kind;
-    L.do_claim[lane] = R.do_claim;
-    L.c0[lane] = R.c0;
-    L.d[lane] = R.d;
-    L.o[lane] = R.o;
-    L.beg[lane] = R.beg;
-    L.key[lane] = R.key;
-}
-
-// The fields of run entry j, wave-uniform.
-__device__ __forceinline__ EntryInfo lds_entry(const RunLds& L, int j) {
-    EntryInfo E;
-    E.c = uniform_i32(L.c[j]);
-    E.v = uniform_i32(L.v[j]);
-    E.inst = uniform_i32(L.inst[j]);
-    E.o = uniform_i64(L.o[j]);
-    E.beg = uniform_i64(L.beg[j]);
-    E.d = uniform_i32(L.d[j]);
-    const int32_t pinfo = uniform_i32(L.pinfo[j]);
-    E.P = pinfo & ~kWideList;
-    E.wide = (pinfo & kWideList) != 0;
-    E.k = uniform_i32(L.k[j]);
-    E.kind = uniform_i32(L.kind[j]);
-    E.do_claim = uniform_i32(L.do_claim[j]) != 0;
-    E.key = (uint64_t)uniform_i64((int64_t)L.key[j]);
-    E.c0 = (uint32_t)uniform_i32(L.c0[j]);
-    return E;
 }
 
 // The fields of run entry j, wave-uniform.
@@ -997,285 +952,537 @@ __device__ __forceinline__ void emit_slots(const SampleLayer& p, const EntryInfo
         const int32_t x = p.g.col[E.beg + pos];
         p.src[E.o + lane] = E.v;
         p.dst[E.o + lane] = x;
-        claim(E.do_claim, p.visited + (int64_t)E.inst * p.nwp, p.next + (int64_t)E.inst * p.nwp, summary_of(p, E.inst),
-              x);
+        claim(E.do_claim, p.next + (int64_t)E.inst * p.nwp, summary_of(p, E.inst), x);
     }
 }
 
-__device__ void select_entry(const SampleLayer& p, const EntryInfo& E) {
+// ---------------------------------------------------------- slot per lane
+// Main selection kernel: a lane is one slot of one entry. A wavefront loads a
+// run of entries and packs whole entries into its 64 lanes (a draw takes its
+// k slots, a take-all list of up to 64 candidates its d candidates), so one
+// Philox block, one search and one column load serve the slots of several
+// entries at once, and small fanouts leave few lanes idle. A slot finds its
+// candidate by itself: an unbiased draw is its position; a weighted draw goes
+// through the list's walk guide (a bucket pair, about 80% of the time nothing
+// else, whatever the list's length); without a guide a list of at most
+// `bound` weights is scanned by each lane (the lanes of an entry read the
+// same few words). Longer lists without a guide are left to k_select_wave and
+// k_select_big.
+// Collisions: in the first round a slot is accepted iff no lower slot of its
+// entry drew the same candidate (a lower slot that was itself rejected was
+// rejected for a still lower one), found by shifting the picks one lane at a
+// time, for all entries side by side; the few open slots of the later rounds
+// are taken one at a time in slot order, and those left after the last round
+// by direct draws, one per entry at a time. The same picks, in the same
+// order, as a wavefront per entry makes.
+constexpr int kDppWaveShr1 = 0x138;
+constexpr int32_t kScanMax = 32;  // longest list a lane scans
+
+template <bool kWeighted>
+struct SlotRun {
+    int32_t v[kWave], inst[kWave], d[kWave], c0[kWave], info[kWave], own[kWave], stage[kWave];
+    int64_t o[kWave], beg[kWave];
+    uint64_t key[kWave];
+    uint64_t W[kWeighted ? kWave : 1];
+};
+constexpr int kInfoKind = 3, kInfoTake = 4, kInfoClaim = 8, kInfoZeros = 16;
+
+// Short lists (unbiased, or weighted with a walk guide; d at most kStagePer times
+// the slots, a total below 2^32) are drawn from in LDS: their inclusive prefixes,
+// copied from the edge records by the entry's own lanes (a list of 8 k edges
+// takes as many lines as a bucket per slot), and a claim word per candidate.
+// What these lists wait for is the chain of their rounds, and the
+// direct draws, one after the other, of lists hardly longer than k or with a
+// few heavy weights: a search per round and a slot at a time for its
+// acceptance, through the buckets or through LDS, took 52 us for the 8,192 lists of a
+// degree-biased layer.
+// Here a round is one search and one atomic minimum for all open
+// slots: the claim word keeps the smallest round * 64 + slot, so a held
+// candidate stays held and the lowest slot of a round wins. A direct draw
+// counts the updated prefixes at or below it with all lanes of the entry.
+// (6 and 8 wavefronts per SIMD fit the LDS of a CU)
+template <bool kWeighted>
+constexpr int kStageWords = kWeighted ? 368 : 220;
+constexpr int kStagePer = 8;
+constexpr int64_t kSlotResident = 5120;  // wavefronts of the weighted kernel on the chip at once
+constexpr int64_t kSlotBatch = 6;        // entries of about ten slots that fill a wavefront
+
+// Long take-all entry: every positive-bias neighbor in list order, one
+// wavefront, 64 candidates (weighted with zero weights: 512) at a time.
+__device__ __forceinline__ void take_all_entry(const SampleLayer& p, int32_t v, int32_t inst, int32_t info, int64_t o,
+                                               int64_t beg, int32_t d) {
     const int lane = lane_id();
-    if (E.c == 0) return;
-    if (E.o + E.c > p.capacity) {
-        if (lane == 0) p.ctl->overflow = 1;
+    const bool do_claim = (info & kInfoClaim) != 0;
+    uint32_t* nextb = p.next + (int64_t)inst * p.nwp;
+    uint32_t* summb = summary_of(p, inst);
+    const int32_t* col = p.g.col + beg;
+    int32_t* src = p.src + o;
+    int32_t* dst = p.dst + o;
+    if (!(info & kInfoZeros)) {
+        for (int64_t j = lane; j < d; j += kWave) {
+            const int32_t x = col[j];
+            src[j] = v;
+            dst[j] = x;
+            claim(do_claim, nextb, summb, x);
+        }
         return;
     }
-    if (route_of(E.kind, E.k, E.P, E.d, E.wide) != kRouteWave) return;  // long-list path
-    const uint32_t* visb = p.visited + (int64_t)E.inst * p.nwp;
-    uint32_t* nextb = p.next + (int64_t)E.inst * p.nwp;
-    uint32_t* summb = summary_of(p, E.inst);
-    const bool weighted = E.kind != kUniform;
-    const uint32_t* w = weighted ? (E.kind == kEdgeWeight ? p.g.ew : p.g.degw) + E.beg : nullptr;
-    const int32_t* col = p.g.col + E.beg;
-    int32_t* src = p.src + E.o;
-    int32_t* dst = p.dst + E.o;
-    const int64_t d = E.d;
+    const uint32_t* w = ((info & kInfoKind) == kEdgeWeight ? p.g.ew : p.g.degw) + beg;
+    int64_t run = 0;
+    for (int64_t base = 0; base < d; base += 8 * kWave) {
+        uint32_t x[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int64_t idx = base + c * kWave + lane;
+            x[c] = idx < d ? w[idx] : 0u;
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int64_t idx = base + c * kWave + lane;
+            const bool pos = x[c] > 0;
+            const uint64_t mask = ballot(pos);
+            if (pos) {
+                const int64_t slot = run + __popcll(mask & lanemask_lt());
+                const int32_t nb = col[idx];
+                src[slot] = v;
+                dst[slot] = nb;
+                claim(do_claim, nextb, summb, nb);
+            }
+            run += __popcll(mask);
+        }
+    }
+}
 
-    // ---- NeighborSize >= pool: every positive-bias neighbor, list order
-    if (E.k < 0 || E.k >= E.P) {
-        if (!weighted || E.P == d) {
-            for (int64_t j = lane; j < d; j += kWave) {
-                const int32_t x = col[j];
-                src[j] = E.v;
-                dst[j] = x;
-                claim(E.do_claim, visb, nextb, summb, x);
+__device__ __forceinline__ bool has_guide(const GraphDev& g, int32_t kind) {
+    return kind == kEdgeWeight ? g.wgd_ew != nullptr : g.wgd_deg != nullptr;
+}
+
+// Does the slot kernel serve run entry R? (The others: k_select_wave, k_select_big.)
+__device__ __forceinline__ bool slot_served(const SampleLayer& p, const EntryRun& R) {
+    if (R.k < 0 || R.kind == kUniform || has_guide(p.g, R.kind)) return true;
+    const int32_t bound = p.group32 > p.group16 ? p.group32 : p.group16;
+    return !(R.pinfo & kWideList) && R.d <= (bound < kScanMax ? bound : kScanMax);
+}
+
+// m = max{i : S_i <= r}, r in [0, W), of the weighted list of vertex v (first
+// edge beg, length d): nb receives the neighbor where the guide's records
+// hold it, else -1.
+__device__ __forceinline__ int32_t slot_search(const GraphDev& g, int32_t kind, int32_t v, int64_t beg, int32_t d,
+                                               uint64_t W, uint64_t r, int32_t& nb) {
+    const bool ew = kind == kEdgeWeight;
+    nb = -1;
+    if (!has_guide(g, kind)) {  // at most kScanMax weights, 8 loads in flight
+        const uint32_t* w = (ew ? g.ew : g.degw) + beg;
+        uint64_t run = 0;
+        int32_t m = 0;
+        for (int32_t i = 0; i < d; i += 8) {
+            uint32_t x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = w[i + q < d ? i + q : d - 1];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                run += x[q];
+                m += i + q < d && run <= r ? 1 : 0;
+            }
+        }
+        return m;
+    }
+    const WalkBucket* G = (ew ? g.wgd_ew : g.wgd_deg) + guide_base(beg, v);
+    const int sh = guide_shift(W, d);
+    const uint64_t k = r >> sh;
+    const bool last = k + 1 > (W - 1) >> sh;
+    const WalkBucket b0 = G[k], b1 = G[last ? k : k + 1];
+    int32_t lo = (int32_t)b0.pos;
+    const int32_t hi = last ? d - 1 : (int32_t)b1.pos;
+    if (hi == lo || (!last && hi == lo + 1)) {  // the buckets hold the bracket's prefixes and ids
+        const bool first = hi == lo || b0.S > r;
+        nb = first ? b0.col : b1.col;
+        return first ? lo : hi;
+    }
+    const WalkEdge* er = (ew ? g.wrec_ew : g.wrec_deg) + beg;
+    constexpr int kProbe = 4;
+    for (;;) {  // edge records from lo on (positions past hi read hi, whose prefix exceeds r)
+        uint64_t S[kProbe];
+        int32_t y[kProbe];
+#pragma unroll
+        for (int j = 0; j < kProbe; ++j) {
+            const WalkEdge* e = er + (lo + j < hi ? lo + j : hi);
+            S[j] = e->S;
+            y[j] = e->col;
+        }
+        int c = 0;
+#pragma unroll
+        for (int j = 0; j < kProbe; ++j) c += S[j] <= r ? 1 : 0;
+        if (c < kProbe) {
+            nb = y[0];
+#pragma unroll
+            for (int j = 1; j < kProbe; ++j) nb = c == j ? y[j] : nb;
+            return lo + c;
+        }
+        lo += kProbe;
+    }
+}
+
+// S_m and b_m of a position of such a list.
+__device__ __forceinline__ void slot_bias(const GraphDev& g, int32_t kind, int64_t beg, int32_t m, uint64_t& Sm,
+                                          uint32_t& bm) {
+    const bool ew = kind == kEdgeWeight;
+    if (has_guide(g, kind)) {
+        const WalkEdge e = (ew ? g.wrec_ew : g.wrec_deg)[beg + m];
+        Sm = e.S - e.w;
+        bm = e.w;
+        return;
+    }
+    const uint32_t* w = (ew ? g.ew : g.degw) + beg;
+    Sm = 0;
+    for (int32_t i = 0; i < m; ++i) Sm += w[i];
+    bm = w[m];
+}
+
+__device__ __forceinline__ uint64_t bperm_u64(uint64_t x, int from) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from * 4, (int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from * 4, (int)(uint32_t)(x >> 32));
+    return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
+// Sum of x over the lanes [sl, se) of the calling lane's entry (every lane active).
+__device__ __forceinline__ uint64_t segment_sum(uint64_t x, int sl, int se) {
+    const uint64_t run = wave_incl_scan_u64(x);
+    const uint64_t upto = bperm_u64(run, se > 0 ? se - 1 : 0), from = bperm_u64(run, sl > 0 ? sl - 1 : 0);
+    return upto - (sl > 0 ? from : 0ull);
+}
+
+// The draws of the staged entries of a wavefront's batch (every lane calls it;
+// lanes [sl, se) are an entry, lane sl + j its slot j): returns this lane's
+// position, or m for a lane of no staged entry. The staged words of the batch
+// are pre[0, words) and claim[0, words); an entry's begin at `at`: pre[at] = 0,
+// pre[at + 1 + i] the inclusive prefix of candidate i, claim[at + i].
+template <bool kWeighted>
+__device__ __forceinline__ int32_t draw_staged(const SampleLayer& p, const SlotRun<kWeighted>& L, uint32_t* pre, uint32_t* claim,
+                                               int q, bool staged, int at, int sl, int se, uint64_t segmask, int words,
+                                               int32_t m) {
+    const int lane = lane_id();
+    const int slot = lane - sl, k = se - sl;
+    const int32_t d = L.d[q];
+    const int32_t kind = kWeighted ? L.info[q] & kInfoKind : kUniform;
+    const uint32_t c0 = (uint32_t)L.c0[q], v = (uint32_t)L.v[q];
+    const Key key{(uint32_t)L.key[q], (uint32_t)(L.key[q] >> 32)};
+    if (staged) {
+        if (slot == 0) {
+            pre[at] = 0u;
+            claim[at + d] = ~0u;  // the last prefix's word has no candidate
+        }
+        if (kWeighted && kind != kUniform) {
+            const WalkEdge* er = (kind == kEdgeWeight ? p.g.wrec_ew : p.g.wrec_deg) + L.beg[q];
+            for (int32_t i = slot; i < d; i += 4 * k) {
+                uint32_t x[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) x[t] = (uint32_t)er[i + t * k < d ? i + t * k : d - 1].S;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if (i + t * k < d) {
+                        pre[at + 1 + i + t * k] = x[t];
+                        claim[at + i + t * k] = ~0u;
+                    }
+                }
             }
         } else {
-            int64_t run = 0;
-            for (int64_t base = 0; base < d; base += 8 * kWave) {
-                uint32_t x[8];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const int64_t idx = base + c * kWave + lane;
-                    x[c] = idx < d ? w[idx] : 0u;
-                }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const int64_t idx = base + c * kWave + lane;
-                    const bool pos = x[c] > 0;
-                    const uint64_t mask = ballot(pos);
-                    if (pos) {
-                        const int64_t slot = run + __popcll(mask & lanemask_lt());
-                        const int32_t nb = col[idx];
-                        src[slot] = E.v;
-                        dst[slot] = nb;
-                        claim(E.do_claim, visb, nextb, summb, nb);
-                    }
-                    run += __popcll(mask);
-                }
+            for (int32_t i = slot; i < d; i += k) {
+                pre[at + 1 + i] = (uint32_t)i + 1;
+                claim[at + i] = ~0u;
             }
         }
-        return;
     }
-
-    // ---- k < P <= d: draw k distinct candidates (k <= kMaxDrawFanout)
-    const Key key{(uint32_t)E.key, (uint32_t)(E.key >> 32)};
-    const uint32_t c0 = E.c0;
-    const uint32_t c1 = (uint32_t)p.layer;
-    const uint32_t c2 = (uint32_t)E.v;
-    int64_t pos;
-    if (!weighted) {
-        const auto pick = [](uint64_t r, int64_t& m, uint64_t& Sm, uint32_t& bm) {
-            m = (int64_t)r;
-            Sm = r;
-            bm = 1;
-        };
-        pos = draw_slots(key, c0, c1, c2, E.k, p.rounds, (uint64_t)d, pick, pick);
-    } else if (d <= 64) {
-        pos = draw_resident<1>(w, d, key, c0, c1, c2, E.k, p.rounds);
-    } else if (d <= 128) {
-        pos = draw_resident<2>(w, d, key, c0, c1, c2, E.k, p.rounds);
-    } else if (d <= 256) {
-        pos = draw_resident<4>(w, d, key, c0, c1, c2, E.k, p.rounds);
-    } else {
-        pos = draw_resident<8>(w, d, key, c0, c1, c2, E.k, p.rounds);
-    }
-    emit_slots(p, E, pos);
-}
-
-// ------------------------------------------------------- sub-wave groups
-// Entries whose work fits G lanes -- a take-all list of at most G
-// candidates, an unbiased draw of at most G slots, a weighted draw from at
-// most G candidates -- are served 64/G side by side, G lanes each: slot j of
-// an entry is lane j of its group, a weighted candidate i is lane i. The
-// rounds take each group's slots in slot order exactly as the full-wave path
-// does (one slot index t at a time for all groups), so results do not depend
-// on the grouping. An entry with slots still open after the rounds is returned
-// to the full-wave path, which repeats its rounds and ends with direct draws.
-// The bucket bounds (largest size served by 16- and 32-lane groups) are call
-// parameters, so a tuner can pick them per workload.
-
-// The value of x at lane (group base + t), on every lane of the group.
-template <int G>
-__device__ __forceinline__ uint32_t group_bcast_u32(uint32_t x, int t) {
-    const int lane = lane_id();
-    uint32_t r = readlane_u32(x, t);
-#pragma unroll
-    for (int q = 1; q < kWave / G; ++q) {
-        const uint32_t y = readlane_u32(x, q * G + t);
-        r = lane >= q * G ? y : r;
-    }
-    return r;
-}
-
-// Inclusive scan inside each group of G lanes (every lane active).
-template <int G>
-__device__ __forceinline__ uint32_t group_incl_scan_u32(uint32_t x) {
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppRowShr1, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppRowShr2, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppRowShr4, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppRowShr8, 0xf, 0xf, false);
-    if (G >= 32) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppRowBcast15, 0xa, 0xf, false);
-    return x;
-}
-
-// Does run entry R (this lane's) fit groups of G lanes with bucket bound b?
-__device__ __forceinline__ bool group_fits(const EntryRun& R, int64_t capacity, int32_t b) {
-    if (R.c == 0 || R.o + R.c > capacity) return false;
-    const int32_t P = R.pinfo & ~kWideList;
-    if (route_of(R.kind, R.k, P, R.d, (R.pinfo & kWideList) != 0) != kRouteWave) return false;
-    const bool take = R.k < 0 || R.k >= P;
-    return (take || R.kind != kUniform) ? R.d <= b : R.k <= b;
-}
-
-template <int G>
-__device__ uint64_t select_groups(const SampleLayer& p, const RunLds& R, uint64_t elig) {
-    constexpr uint64_t kLow = (1ull << G) - 1;
-    const int lane = lane_id();
-    const int gl = lane & (G - 1);
-    const int gbase = lane & ~(G - 1);
-    const uint64_t gmask = kLow << gbase;
-    uint64_t back = 0;
-    for (uint64_t rem = elig; rem;) {
-        // the next 64/G eligible entries, one per group
-        int srcl = -1;
-#pragma unroll
-        for (int q = 0; q < kWave / G; ++q) {
-            const int s = rem ? __ffsll((unsigned long long)rem) - 1 : -1;
-            rem = rem ? rem & (rem - 1) : 0ull;
-            srcl = gbase == q * G ? s : srcl;
-        }
-        const bool valid = srcl >= 0;
-        const int sl = valid ? srcl : 0;
-        const int32_t v = R.v[sl];
-        const int32_t inst = R.inst[sl];
-        const int64_t o = R.o[sl];
-        const int64_t beg = R.beg[sl];
-        const int32_t d = R.d[sl];
-        const int32_t P = R.pinfo[sl] & ~kWideList;
-        const int32_t k = R.k[sl];
-        const int32_t kind = R.kind[sl];
-        const bool do_claim = R.do_claim[sl] != 0;
-        const uint64_t ekey = R.key[sl];
-        const uint32_t c0 = (uint32_t)R.c0[sl];
-        const bool take = k < 0 || k >= P;
-        const bool weighted = kind != kUniform;
-        const uint32_t* w = (kind == kEdgeWeight ? p.g.ew : p.g.degw) + beg;  // read only if weighted
-
-        // weights of a weighted group, one candidate per lane
-        const bool wlist = valid && weighted && !(take && P == d);
-        uint32_t x = 0;
-        if (wlist && gl < d) x = w[gl];
-
-        // take-all groups: every positive candidate, list order
-        int32_t pos = -1, slot = gl;
-        const uint64_t posm = ballot(valid && take && wlist && x > 0);
-        if (valid && take && gl < d) {
-            if (!wlist) pos = gl;
-            else if (x > 0) {
-                pos = gl;
-                slot = __popcll(posm & gmask & lanemask_lt());
-            }
-        }
-
-        // draw groups: rounds in slot order per group
-        const bool drw = valid && !take;
-        const uint32_t S = group_incl_scan_u32<G>(drw ? x : 0u);
-        const uint32_t Wg = group_bcast_u32<G>(S, G - 1);
-        const uint64_t W = weighted ? (uint64_t)Wg : (uint64_t)(uint32_t)d;
-        const Key key{(uint32_t)ekey, (uint32_t)(ekey >> 32)};
-        uint64_t open = ballot(drw && gl < k);
-        int32_t hid = -1;  // candidate this lane marks held (uniform: its slot's pick; weighted: itself)
-        for (int a = 0; a < p.rounds && open; ++a) {
-            uint32_t r = 0;
-            if ((open >> lane) & 1ull) r = (uint32_t)draw(key, c0, (uint32_t)p.layer, (uint32_t)v, (uint32_t)gl | ((uint32_t)a << 16), W);
-            uint64_t tm = 0;
-#pragma unroll
-            for (int q = 0; q < kWave / G; ++q) tm |= (open >> (q * G)) & kLow;
-            for (; tm; tm &= tm - 1) {
-                const int t = __ffsll((unsigned long long)tm) - 1;
-                const uint32_t rt = group_bcast_u32<G>(r, t);
-                const int32_t mt = weighted ? __popcll(ballot(S <= rt) & gmask) : (int32_t)rt;
-                const bool free = (ballot(hid >= 0 && hid == mt) & gmask) == 0;
-                const bool acc = free && ((open >> (gbase + t)) & 1ull);
-                if (acc) {
-                    if (gl == t) pos = mt;
-                    if (weighted ? gl == mt : gl == t) hid = mt;
+    wave_lds_sync();
+    uint32_t W = staged ? pre[at + d] : 0u;
+    uint64_t open = ballot(staged);
+    for (int a = 0; a < p.rounds && open; ++a) {
+        const bool mine = ((open >> lane) & 1ull) != 0;
+        uint32_t tag = 0;
+        if (mine) {
+            const uint64_t u = philox_u64(key.k0, key.k1, c0, (uint32_t)p.layer, v, (uint32_t)slot | ((uint32_t)a << 16));
+            const uint32_t r = (uint32_t)range_reduce(u, W);
+            int32_t i = (int32_t)r;
+            if (kWeighted && kind != kUniform) {
+                int32_t hi = d - 1;  // the first candidate whose prefix exceeds r
+                for (i = 0; i < hi;) {
+                    const int32_t mid = (i + hi) >> 1;
+                    if (pre[at + 1 + mid] > r) hi = mid;
+                    else i = mid + 1;
                 }
-                open &= ~ballot(acc && gl == t);
             }
+            m = i;
+            tag = (uint32_t)(a * kWave + slot);
+            atomicMin(&claim[at + m], tag);
         }
-        // groups with open slots go back to the full-wave path, unwritten
-        const bool unfinished = (open & gmask) != 0;
-        for (uint64_t ub = ballot(unfinished && gl == 0); ub; ub &= ub - 1)
-            back |= 1ull << readlane_i32(sl, __ffsll((unsigned long long)ub) - 1);
-        if (pos >= 0 && !unfinished) {
-            const int32_t nb = p.g.col[beg + pos];
-            p.src[o + slot] = v;
-            p.dst[o + slot] = nb;
-            claim(do_claim, p.visited + (int64_t)inst * p.nwp, p.next + (int64_t)inst * p.nwp, summary_of(p, inst), nb);
-        }
+        wave_lds_sync();
+        open &= ~ballot(mine && claim[at + m] == tag);
+        wave_lds_sync();
     }
-    return back;
+    if (!open) return m;
+    // the prefixes without the held candidates: one running sum of the held
+    // biases over all staged words (an entry's leading zero takes the sum before
+    // it, so that differences from it are the entry's own; 32 bits wrap alike)
+    uint64_t u = 0;
+    if ((open >> lane) & 1ull)
+        u = philox_u64(key.k0, key.k1, c0, (uint32_t)p.layer, v, (uint32_t)slot | (kFallbackRound << 16));
+    uint32_t carry = 0;
+    for (int w0 = 0; w0 < words; w0 += kWave) {
+        const int w = w0 + lane;
+        const uint32_t lo = w < words ? pre[w] : 0u;
+        const uint32_t hi = w + 1 < words ? pre[w + 1] : 0u;
+        const bool held = w + 1 < words && claim[w] != ~0u;
+        const uint32_t b = held ? hi - lo : 0u;
+        const uint32_t incl = wave_incl_scan_u32(b);
+        wave_lds_sync();
+        if (w < words) pre[w] = lo - (carry + incl - b);
+        carry += readlane_u32(incl, kWave - 1);
+        wave_lds_sync();
+    }
+    for (; open;) {
+        const uint64_t o = open & segmask;
+        const int j = o ? __ffsll((unsigned long long)o) - 1 : lane;  // the entry's lowest open slot
+        const uint32_t zero = staged ? pre[at] : 0u;
+        const uint32_t Wp = staged ? pre[at + d] - zero : 0u;
+        const uint32_t r = (uint32_t)__builtin_amdgcn_ds_bpermute(j * 4, (int)(uint32_t)range_reduce(u, Wp));
+        int32_t c = 0;  // candidates whose updated prefix is at or below r
+        for (int32_t i = slot; ballot(o && i < d); i += k) {
+            const bool le = o && i < d && pre[at + 1 + (i < d ? i : 0)] - zero <= r;
+            c += __popcll(ballot(le) & segmask);
+        }
+        const uint32_t b = o ? pre[at + 1 + c] - pre[at + c] : 0u;
+        wave_lds_sync();
+        if (o) {
+            for (int32_t i = slot; i < d; i += k)
+                if (i >= c) pre[at + 1 + i] -= b;
+        }
+        wave_lds_sync();
+        if (o && j == lane) m = c;
+        open &= ~ballot(o && j == lane);
+    }
+    return m;
 }
 
-// A sub-wave entry whose slots were still open after the rounds, redone by
-// the whole wavefront: an unbiased draw of at most 32 slots or a weighted
-// draw from at most 32 candidates (the draw branch of select_entry).
-__device__ void select_entry_small_draw(const SampleLayer& p, const EntryInfo& E) {
-    const Key key{(uint32_t)E.key, (uint32_t)(E.key >> 32)};
-    const uint32_t c1 = (uint32_t)p.layer;
-    const uint32_t c2 = (uint32_t)E.v;
-    int64_t pos;
-    if (E.kind == kUniform) {
-        const auto pick = [](uint64_t r, int64_t& m, uint64_t& Sm, uint32_t& bm) {
-            m = (int64_t)r;
-            Sm = r;
-            bm = 1;
-        };
-        pos = draw_slots(key, E.c0, c1, c2, E.k, p.rounds, (uint64_t)E.d, pick, pick);
-    } else {
-        pos = draw_resident<1>((E.kind == kEdgeWeight ? p.g.ew : p.g.degw) + E.beg, E.d, key, E.c0, c1, c2, E.k,
-                                 p.rounds);
-    }
-    emit_slots(p, E, pos);
-}
-
-// Sub-wave entries of the layer: each wavefront takes runs of 64 frontier
-// entries (grid-stride), keeps the run in LDS and serves its small entries
-// in groups of 16 and 32 lanes; the other entries are left to k_select.
-template <bool kBurn>
-__global__ void __launch_bounds__(kBlock, 6) k_select_small(SampleLayer p) {
-    __shared__ RunLds runs[kWavesPerBlock];
+// kWeighted: some instance of the call draws by weight.
+template <bool kWeighted>
+__global__ void __launch_bounds__(kBlock, kWeighted ? 5 : 7) k_select_slots(SampleLayer p) {
+    __shared__ SlotRun<kWeighted> runs[kWavesPerBlock];
+    __shared__ uint32_t stage_prefix[kWavesPerBlock][kStageWords<kWeighted>], stage_claim[kWavesPerBlock][kStageWords<kWeighted>];
     const int wid = uniform_i32(threadIdx.x / kWave);
-    RunLds& L = runs[wid];
+    SlotRun<kWeighted>& L = runs[wid];
     const int lane = lane_id();
     const int64_t fcount = p.ctl->fcount[p.layer];
     const int64_t out_base = p.ctl->out_base[p.layer];
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
-    for (int64_t e0 = (blockIdx.x * (int64_t)kWavesPerBlock + wid) * kWave; e0 < fcount; e0 += waves * kWave) {
-        const int n = (int)(fcount - e0 < kWave ? fcount - e0 : kWave);
-        uint64_t e16, e32;
+    const int64_t wave = blockIdx.x * (int64_t)kWavesPerBlock + wid;
+    // one entry a wavefront while the resident wavefronts last (the chain of one
+    // entry is then all there is to wait for), then up to a batch's worth, so
+    // that a second round of wavefronts starts only with full lanes: 206 -> 172 us
+    // for a degree-biased call of 1M edges against an even share of the grid
+    const int64_t share = (fcount + kSlotResident - 1) / kSlotResident, even = (fcount + waves - 1) / waves;
+    const int64_t least = share < kSlotBatch ? share : kSlotBatch;
+    const int64_t per = even > least ? even : least;
+    const int64_t lo = wave * per < fcount ? wave * per : fcount;
+    const int64_t hi = lo + per < fcount ? lo + per : fcount;
+    for (int64_t e0 = lo; e0 < hi; e0 += kWave) {
+        const int n = (int)(hi - e0 < kWave ? hi - e0 : kWave);
+        uint32_t ln;           // lanes the entry takes
+        uint32_t sincl, sd = 0;  // words staged in LDS, summed over the run, and the entry's own
+        uint64_t long_take;
         {
             EntryRun R;
-            load_run<kBurn>(p, e0 + lane, lane < n, out_base, R);
-            e16 = p.group16 > 0 ? ballot(lane < n && group_fits(R, p.capacity, p.group16)) : 0ull;
-            e32 = p.group32 > 0 ? ballot(lane < n && group_fits(R, p.capacity, p.group32)) & ~e16 : 0ull;
-            store_run(L, R, lane);
+            load_run(p, e0 + lane, lane < n, out_base, R);
+            bool ok = R.c != 0;
+            if (ok && R.o + R.c > p.capacity) {
+                p.ctl->overflow = 1;
+                ok = false;
+            }
+            ok = ok && (!kWeighted || slot_served(p, R));
+            const bool take = R.k < 0;
+            ln = !ok ? 0u : (uint32_t)(take ? R.d : R.k);
+            long_take = ballot(ln > (uint32_t)kWave);
+            if (ln > (uint32_t)kWave) ln = 0;
+            uint64_t W = (uint64_t)(uint32_t)R.d;
+            if (kWeighted && ln && !take && R.kind != kUniform)
+                W = (R.kind == kEdgeWeight ? p.g.wtot_ew : p.g.wtot_deg)[R.v];
+            if (ln && !take && R.d <= kStagePer * R.k && R.d < kStageWords<kWeighted> &&
+                (R.kind == kUniform || (has_guide(p.g, R.kind) && !(W >> 32))))
+                sd = (uint32_t)R.d + 1;  // a zero, then the prefixes
+            sincl = wave_incl_scan_u32(sd);
+            wave_lds_sync();
+            L.v[lane] = R.v;
+            L.inst[lane] = R.inst;
+            L.d[lane] = R.d;
+            L.c0[lane] = R.c0;
+            L.info[lane] = R.kind | (take ? kInfoTake : 0) | (R.do_claim ? kInfoClaim : 0) |
+                           (take && R.kind != kUniform && (R.pinfo & ~kWideList) != R.d ? kInfoZeros : 0);
+            L.o[lane] = R.o;
+            L.beg[lane] = R.beg;
+            L.key[lane] = R.key;
+            if (kWeighted) L.W[lane] = W;
         }
-        wave_lds_sync();
-        uint64_t back = 0;
-        if (e16) back |= select_groups<16>(p, L, e16);
-        if (e32) back |= select_groups<32>(p, L, e32);
-        for (; back; back &= back - 1) select_entry_small_draw(p, lds_entry(L, __ffsll((unsigned long long)back) - 1));
-        wave_lds_sync();  // the next run overwrites L
+        const uint32_t incl = wave_incl_scan_u32(ln);
+        const uint32_t excl = incl - ln;
+        for (int s0 = 0; s0 < n;) {
+            // entries [s0, s1): as many as fit the 64 lanes and the staging words
+            const uint32_t base = s0 ? readlane_u32(incl, s0 - 1) : 0u;
+            const uint32_t sbase = s0 ? readlane_u32(sincl, s0 - 1) : 0u;
+            const uint64_t fit = ballot(incl - base <= (uint32_t)kWave && sincl - sbase <= (uint32_t)kStageWords<kWeighted>) >> s0;
+            const int s1 = s0 + (~fit ? __ffsll((unsigned long long)~fit) - 1 : kWave);
+            const int total = (int)(readlane_u32(incl, s1 - 1) - base);
+            const int total_words = (int)(readlane_u32(sincl, s1 - 1) - sbase);
+            const bool mine = lane >= s0 && lane < s1 && ln > 0;
+            s0 = s1;
+            if (total == 0) continue;
+            wave_lds_sync();
+            L.own[lane] = -1;
+            wave_lds_sync();
+            if (mine) {
+                L.own[excl - base] = lane;
+                L.stage[lane] = sd ? (int32_t)(sincl - sd - sbase) : -1;
+            }
+            wave_lds_sync();
+            // lanes [sl, se) are the entry of run position q
+            const uint64_t starts = ballot(L.own[lane] >= 0);
+            const bool valid = lane < total;
+            const uint64_t upto = starts & (~0ull >> (63 - lane)), after = starts & ~(~0ull >> (63 - lane));
+            const int sl = 63 - __clzll((long long)(upto | 1ull));
+            const int se = after ? __ffsll((unsigned long long)after) - 1 : total;
+            const uint64_t segmask = valid ? (~0ull >> (64 - (se - sl))) << sl : 0ull;
+            const int q = valid ? L.own[sl] : 0;
+            const int slot = lane - sl;
+            const int32_t info = L.info[q];
+            bool draws = valid && !(info & kInfoTake);
+            int32_t m = slot, nb = -1;  // this slot's position, and its neighbor once known
+            int at = slot;              // edge slot of this lane
+            bool emit = valid;
+            if (kWeighted && ballot(valid && (info & kInfoZeros))) {  // take-all lists with zero weights: positives only
+                const bool z = valid && (info & kInfoZeros);
+                const bool pos = z && ((info & kInfoKind) == kEdgeWeight ? p.g.ew : p.g.degw)[L.beg[q] + slot] > 0;
+                const uint64_t pm = ballot(pos);
+                if (z) {
+                    emit = pos;
+                    at = __popcll(pm & segmask & lanemask_lt());
+                }
+            }
+            const int stage_at = draws ? L.stage[q] : -1;
+            const bool staged = stage_at >= 0;
+            if (ballot(staged))
+                m = draw_staged<kWeighted>(p, L, stage_prefix[wid], stage_claim[wid], q, staged, stage_at, sl, se,
+                                           segmask, total_words, m);
+            draws = draws && !staged;
+            uint64_t open = ballot(draws);
+            // direct draws: start in the updated prefix and bias of this held
+            // slot, and the held bias of its entry
+            uint64_t start = 0, removed = 0;
+            uint32_t bias = 0;
+            for (int a = 0; open; ++a) {
+                // the entry's fields again from LDS: held in registers across
+                // the rounds they cost occupancy
+                wave_lds_sync();
+                const int32_t kind = kWeighted ? L.info[q] & kInfoKind : kUniform;
+                const int32_t v = L.v[q], d = L.d[q];
+                const int64_t beg = L.beg[q];
+                const uint64_t W = kWeighted ? L.W[q] : (uint64_t)(uint32_t)d;
+                const uint64_t key = L.key[q];
+                const bool direct = a >= p.rounds;
+                const uint64_t eopen = open & segmask;  // the entry's open slots
+                const bool myopen = ((open >> lane) & 1ull) != 0;
+                const bool held = draws && eopen && !myopen;  // (direct draws)
+                const int j = eopen ? __ffsll((unsigned long long)eopen) - 1 : lane;
+                const bool turn = direct ? draws && eopen && j == lane : myopen;
+                uint64_t r = 0;
+                if (turn)
+                    r = philox_u64((uint32_t)key, (uint32_t)(key >> 32), (uint32_t)L.c0[q], (uint32_t)p.layer, (uint32_t)v,
+                                   (uint32_t)slot | ((direct ? kFallbackRound : (uint32_t)a) << 16));
+                if (direct) {
+                    if (a == p.rounds) {
+                        if (held) {
+                            start = (uint64_t)(uint32_t)m;
+                            bias = 1;
+                            if (kWeighted && kind != kUniform) slot_bias(p.g, kind, beg, m, start, bias);
+                        }
+                        const uint64_t S0 = start;
+                        for (uint64_t hm = ballot(held); hm; hm &= hm - 1) {
+                            const int h = __ffsll((unsigned long long)hm) - 1;
+                            const uint64_t Sh = readlane_u64(S0, h);
+                            const uint32_t bh = readlane_u32(bias, h);
+                            if (eopen && h >= sl && h < se) {
+                                removed += bh;
+                                if (held && Sh < S0) start -= bh;
+                            }
+                        }
+                    }
+                    // r0 in [0, W - held bias), plus every held candidate whose
+                    // start in the updated prefix is at or below it
+                    r = range_reduce(r, W - removed);
+                    const uint64_t rj = bperm_u64(r, j);
+                    r += segment_sum(held && start <= rj ? bias : 0u, sl, se);
+                } else if (turn) {
+                    r = range_reduce(r, W);
+                }
+                if (turn) {
+                    m = (int32_t)r;
+                    if (kWeighted && kind != kUniform) m = slot_search(p.g, kind, v, beg, d, W, r, nb);
+                }
+                if (direct) {
+                    uint64_t Sj = (uint64_t)(uint32_t)m;
+                    uint32_t bj = 1;
+                    if (kWeighted && turn && kind != kUniform) slot_bias(p.g, kind, beg, m, Sj, bj);
+                    const int32_t mt = __builtin_amdgcn_ds_bpermute(j * 4, m);
+                    const uint32_t bt = (uint32_t)__builtin_amdgcn_ds_bpermute(j * 4, (int)bj);
+                    const uint64_t below = segment_sum(held && m < mt ? bias : 0u, sl, se);
+                    if (eopen) {
+                        removed += bt;
+                        if (held && m > mt) start -= bt;
+                    }
+                    if (turn) {
+                        start = Sj - below;
+                        bias = bj;
+                    }
+                    open &= ~ballot(turn);
+                } else if (a == 0) {
+                    // a slot yields to a lower one of its entry with the same pick
+                    bool dup = false;
+                    int32_t y = m;
+                    for (int t = 1; ballot(draws && slot >= t); ++t) {
+                        y = __builtin_amdgcn_update_dpp(0, y, kDppWaveShr1, 0xf, 0xf, false);
+                        dup |= slot >= t && y == m;
+                    }
+                    open = ballot(draws && dup);
+                } else {
+                    for (uint64_t todo = open; todo; todo &= todo - 1) {  // slot order
+                        const int i = __ffsll((unsigned long long)todo) - 1;
+                        const int32_t mi = readlane_i32(m, i);
+                        const uint64_t si = readlane_u64(segmask, i);
+                        if ((ballot(m == mi) & si & ~open) == 0) open &= ~(1ull << i);
+                    }
+                }
+            }
+            if (emit) {
+                if (nb < 0) nb = p.g.col[L.beg[q] + m];
+                const int64_t o = L.o[q] + at;
+                const int32_t inst = L.inst[q];
+                p.src[o] = L.v[q];
+                p.dst[o] = nb;
+                claim((info & kInfoClaim) != 0, p.next + (int64_t)inst * p.nwp, summary_of(p, inst), nb);
+            }
+        }
+        for (; long_take; long_take &= long_take - 1) {
+            const int q = __ffsll((unsigned long long)long_take) - 1;
+            take_all_entry(p, uniform_i32(L.v[q]), uniform_i32(L.inst[q]), uniform_i32(L.info[q]),
+                           uniform_i64(L.o[q]), uniform_i64(L.beg[q]), uniform_i32(L.d[q]));
+        }
     }
 }
 
-// Each wavefront takes a contiguous share of the frontier (a short run when
-// the grid has more wavefronts than resident slots), loaded 64 entries at a
-// time; entries of the sub-wave buckets are skipped (k_select_small).
-template <bool kBurn>
-__global__ void __launch_bounds__(kBlock) k_select(SampleLayer p) {
+// Weighted draws from lists without a walk guide, longer than a lane scans
+// and of at most kWaveMaxD candidates: one wavefront per entry, the list and
+// its prefix in registers. Each wavefront takes a contiguous share of the
+// frontier, loaded 64 entries at a time; a share holds few such entries when
+// the call is mixed, and the launch is left out when every weighted kind of
+// the call has its guide.
+__global__ void __launch_bounds__(kBlock) k_select_wave(SampleLayer p) {
     const int wid = uniform_i32(threadIdx.x / kWave);
     const int lane = lane_id();
     const int64_t fcount = p.ctl->fcount[p.layer];
@@ -1285,13 +1492,24 @@ __global__ void __launch_bounds__(kBlock) k_select(SampleLayer p) {
     const int64_t per = (fcount + waves - 1) / waves;
     const int64_t lo = wave * per < fcount ? wave * per : fcount;
     const int64_t hi = lo + per < fcount ? lo + per : fcount;
-    const int32_t bound = p.group32 > p.group16 ? p.group32 : p.group16;
     for (int64_t e0 = lo; e0 < hi; e0 += kWave) {
         const int n = (int)(hi - e0 < kWave ? hi - e0 : kWave);
         EntryRun R;
-        load_run<kBurn>(p, e0 + lane, lane < n, out_base, R);
-        uint64_t todo = ballot(lane < n && R.c != 0 && !(bound > 0 && group_fits(R, p.capacity, bound)));
-        for (; todo; todo &= todo - 1) select_entry(p, run_entry(R, __ffsll((unsigned long long)todo) - 1));
+        load_run(p, e0 + lane, lane < n, out_base, R);
+        uint64_t todo = ballot(R.c != 0 && R.o + R.c <= p.capacity && !slot_served(p, R) && R.d <= kWaveMaxD &&
+                               !(R.pinfo & kWideList));
+        for (; todo; todo &= todo - 1) {
+            const EntryInfo E = run_entry(R, __ffsll((unsigned long long)todo) - 1);
+            const Key key{(uint32_t)E.key, (uint32_t)(E.key >> 32)};
+            const uint32_t* w = (E.kind == kEdgeWeight ? p.g.ew : p.g.degw) + E.beg;
+            const uint32_t c1 = (uint32_t)p.layer, c2 = (uint32_t)E.v;
+            int64_t pos;
+            if (E.d <= 64) pos = draw_resident<1>(w, E.d, key, E.c0, c1, c2, E.k, p.rounds);
+            else if (E.d <= 128) pos = draw_resident<2>(w, E.d, key, E.c0, c1, c2, E.k, p.rounds);
+            else if (E.d <= 256) pos = draw_resident<4>(w, E.d, key, E.c0, c1, c2, E.k, p.rounds);
+            else pos = draw_resident<8>(w, E.d, key, E.c0, c1, c2, E.k, p.rounds);
+            emit_slots(p, E, pos);
+        }
     }
 }
 
@@ -1363,59 +1581,6 @@ __device__ __forceinline__ int32_t row_group(const uint64_t* __restrict__ row, u
 // LDS, the chunk by a walk over the unit's chunk totals, the group by binary
 // search in the chunk's G row and the candidate by scanning the group's
 // weights (global memory / L2).
-// A list's walk guide (when the graph has one for its weight array): its
-// buckets and edge records, total W and bucket shift.
-struct GuidePool {
-    const WalkBucket* G;
-    const WalkEdge* er;
-    uint64_t W, K;
-    int64_t d;
-    int sh;
-};
-
-// m = max{i : S_i <= r} with S_m and b_m through the walk guide, per lane:
-// the bracket [G[k].pos, G[k+1].pos] of bucket k = r >> s (every position
-// before it ends at or below k * 2^s <= r; its last ends past (k+1) * 2^s,
-// or is the list's last), then the bracket's edge records 8 at a time
-// (positions past its end read the end, whose prefix exceeds r):
-// m = lo + #{j : S_(lo+j+1) <= r}, S_m = S_(m+1) - b_m. Two dependent loads
-// for a bracket of up to 8 positions, whatever the list's length.
-__device__ __forceinline__ void guide_search(const GuidePool& gp, uint64_t r, int64_t& m, uint64_t& Sm,
-                                             uint32_t& bm) {
-    const uint64_t k = r >> gp.sh;
-    const bool last = k + 1 >= gp.K;
-    int64_t lo = gp.G[k].pos;
-    const uint32_t p1 = gp.G[last ? k : k + 1].pos;
-    const int64_t hi = last ? gp.d - 1 : (int64_t)p1;
-    for (;;) {
-        uint64_t S[8];
-        uint32_t b[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t q = lo + j < hi ? lo + j : hi;
-            S[j] = gp.er[q].S;
-            b[j] = gp.er[q].w;
-        }
-        int c = 0;
-#pragma unroll
-        for (int j = 0; j < 7; ++j) c += S[j] <= r ? 1 : 0;
-        if (c < 7 || lo + 7 >= hi) {
-            uint64_t s = S[0];
-            uint32_t x = b[0];
-#pragma unroll
-            for (int j = 1; j < 8; ++j) {
-                s = c == j ? S[j] : s;
-                x = c == j ? b[j] : x;
-            }
-            m = lo + c;
-            Sm = s - x;
-            bm = x;
-            return;
-        }
-        lo += 7;
-    }
-}
-
 struct UnitPool {
     const uint64_t* tab;    // LDS, nu + 1 entries
     int64_t nu;
@@ -1468,19 +1633,6 @@ __device__ void select_big_entry(const SampleLayer& p, const EntryInfo& E, uint6
     const int64_t d = E.d;
     const Key key{(uint32_t)E.key, (uint32_t)(E.key >> 32)};
     const uint32_t c0 = E.c0, c1 = (uint32_t)p.layer, c2 = (uint32_t)E.v;
-    const bool ew = E.kind == kEdgeWeight;
-    const WalkBucket* gb = ew ? p.g.wgd_ew : p.g.wgd_deg;
-    const WalkEdge* ge = ew ? p.g.wrec_ew : p.g.wrec_deg;
-    if (gb && ge) {  // the list's walk guide: no table to build, two loads a draw
-        const uint64_t W = ld_uniform((ew ? p.g.wtot_ew : p.g.wtot_deg) + E.v);
-        const int sh = guide_shift(W, d);
-        const GuidePool gp{gb + guide_base(E.beg, E.v), ge + E.beg, W, ((W - 1) >> sh) + 1, d, sh};
-        const auto search = [&gp](uint64_t r, int64_t& m, uint64_t& Sm, uint32_t& bm) {
-            guide_search(gp, r, m, Sm, bm);
-        };
-        emit_slots(p, E, draw_slots(key, c0, c1, c2, E.k, p.rounds, W, search, search));
-        return;
-    }
     const int64_t nch = chunks_of(d);
     const uint32_t* w = (E.kind == kEdgeWeight ? p.g.ew : p.g.degw) + E.beg;
     const uint64_t* G = (E.kind == kEdgeWeight ? p.g.gtab_ew : p.g.gtab_deg) + (E.beg >> kTabShift) * kChunkGroups;
@@ -1549,7 +1701,6 @@ __device__ void select_big_entry(const SampleLayer& p, const EntryInfo& E, uint6
     wave_lds_sync();  // the table is rewritten by the wave's next list
 }
 
-template <bool kBurn>
 __global__ void __launch_bounds__(kBlock) k_select_big(SampleLayer p) {
     __shared__ uint64_t tabs[kWavesPerBlock][kBigTab + 1];
     const int wid = uniform_i32(threadIdx.x / kWave);
@@ -1566,8 +1717,10 @@ __global__ void __launch_bounds__(kBlock) k_select_big(SampleLayer p) {
         const bool valid = lane < n;
         const int64_t pos = valid ? p.bigs[h0 + lane] : 0;
         EntryRun R;
-        load_run<kBurn>(p, pos, valid, out_base, R);
-        for (int j = 0; j < n; ++j) select_big_entry(p, run_entry(R, j), tabs[wid]);
+        load_run(p, pos, valid, out_base, R);
+        // (a kind with its walk guide is the slot kernel's)
+        for (uint64_t todo = ballot(R.c != 0 && !has_guide(p.g, R.kind)); todo; todo &= todo - 1)
+            select_big_entry(p, run_entry(R, __ffsll((unsigned long long)todo) - 1), tabs[wid]);
     }
 }
 
@@ -1830,6 +1983,11 @@ __global__ void __launch_bounds__(kBlock) k_partition_work(const int32_t* __rest
 // ---------------------------------------------------------------- launchers}  // namespace
 
 // ---------------------------------------------------------------- launchers
+size_t free_device_bytes() {
+    size_t free_b = 0, total = 0;
+    return hipMemGetInfo(&free_b, &total) == hipSuccess ? free_b : 0;
+}
+
 void launch_partition_work(const int32_t* fv, const int32_t* cnt, const SampleCtl* ctl, int32_t layer,
                            int64_t capacity, const int64_t* bounds, int32_t np, unsigned long long* work,
                            hipStream_t s) {
@@ -1909,11 +2067,7 @@ int64_t dirty_compact_blocks(int64_t summary_words) {
 }
 
 void launch_select(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev) {
-    launch_kernel(p.burn ? k_select<true> : k_select<false>, dim3(grid), dim3(kBlock), s, ev, p);
-}
-
-void launch_select_small(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev) {
-    launch_kernel(p.burn ? k_select_small<true> : k_select_small<false>, dim3(grid), dim3(kBlock), s, ev, p);
+    launch_kernel(p.weighted ? k_select_slots<true> : k_select_slots<false>, dim3(grid), dim3(kBlock), s, ev, p);
 }
 
 void launch_layer_sample(const LayerParams& p, hipStream_t s, LaunchEvents ev) {
@@ -1936,7 +2090,8 @@ void launch_chunk_table(RowPtr rowptr, const uint32_t* w, int64_t n, uint64_t* t
 }
 
 void launch_select_big(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev) {
-    launch_kernel(p.burn ? k_select_big<true> : k_select_big<false>, dim3(grid), dim3(kBlock), s, ev, p);
+    hipLaunchKernelGGL(k_select_wave, dim3(grid), dim3(kBlock), 0, s, p);
+    launch_kernel(k_select_big, dim3(grid), dim3(kBlock), s, ev, p);
 }
 
 void launch_clear_visited(const ClearVisited& c, hipStream_t s, LaunchEvents ev) {
