@@ -60,6 +60,17 @@ struct alignas(16) WalkBucket {
     int32_t col;
 };
 
+// One edge of the hop table (graphs with m < 2^32): the neighbor and its list
+// [beg, beg + d), so that an unbiased step reads one 16-byte record where the
+// neighbor id and its row offsets were two scattered lines, the second waiting
+// for the first.
+struct alignas(16) WalkHop {
+    int32_t col;
+    uint32_t beg;
+    uint32_t d;
+    uint32_t pad;
+};
+
 struct GraphDev {
     int64_t n, m;
     RowPtr rowptr;             // n+1
@@ -92,6 +103,7 @@ struct GraphDev {
     const WalkVertex* wvtx_deg;
     const WalkBucket* wgd_ew;
     const WalkBucket* wgd_deg;
+    const WalkHop* hops = nullptr;  // m, or null
 };
 
 constexpr int kWaveMaxD = 512;   // longest weighted list of the wavefront kernels
@@ -294,6 +306,8 @@ void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev =
 // vtx[n] (may be null), gd[2 m + n].
 void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, const uint64_t* wtot, int64_t n,
                         WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, hipStream_t s);
+// The hop table of a graph (weak: see free_device_bytes).
+__attribute__((weak)) void launch_walk_hops(RowPtr rowptr, const int32_t* col, int64_t m, WalkHop* hops, hipStream_t s);
 constexpr int kGuideBucketsPerEdge = 2;  // a list of d edges gets at most 2 d buckets
 
 // Buckets of a list's walk guide: width 2^s, K = ((W - 1) >> s) + 1 of them,
@@ -345,6 +359,8 @@ void launch_layer_sample(const LayerParams& p, hipStream_t s, LaunchEvents ev = 
 struct MdrwParams {
     GraphDev g;
     int32_t num_instances;
+    int32_t max_pool = kMaxPool;     // largest pool of the call (sizes the LDS)
+    uint64_t max_degree = ~0u;       // longest list of the graph
     const int64_t* pool_off;         // [ni+1], host-mapped memory
     const int32_t* pool;
     uint64_t instance_base;

@@ -1000,7 +1000,7 @@ constexpr int kInfoKind = 3, kInfoTake = 4, kInfoClaim = 8, kInfoZeros = 16;
 // slots: the claim word keeps the smallest round * 64 + slot, so a held
 // candidate stays held and the lowest slot of a round wins. A direct draw
 // counts the updated prefixes at or below it with all lanes of the entry.
-// (6 and 8 wavefronts per SIMD fit the LDS of a CU)
+// (5 wavefronts per SIMD: more spilled registers to scratch memory)
 template <bool kWeighted>
 constexpr int kStageWords = kWeighted ? 368 : 220;
 constexpr int kStagePer = 8;
@@ -1265,7 +1265,7 @@ __device__ __forceinline__ int32_t draw_staged(const SampleLayer& p, const SlotR
 
 // kWeighted: some instance of the call draws by weight.
 template <bool kWeighted>
-__global__ void __launch_bounds__(kBlock, kWeighted ? 5 : 7) k_select_slots(SampleLayer p) {
+__global__ void __launch_bounds__(kBlock, 5) k_select_slots(SampleLayer p) {
     __shared__ SlotRun<kWeighted> runs[kWavesPerBlock];
     __shared__ uint32_t stage_prefix[kWavesPerBlock][kStageWords<kWeighted>], stage_claim[kWavesPerBlock][kStageWords<kWeighted>];
     const int wid = uniform_i32(threadIdx.x / kWave);

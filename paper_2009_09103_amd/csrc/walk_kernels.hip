@@ -78,10 +78,54 @@ __device__ __forceinline__ WalkerCtx walker_ctx(const WalkParams& p, int64_t w) 
     return c;
 }
 
+// A lane's path entries, written kPathRun at a time in 16-byte stores: a 4-byte
+// store into a row of its own per step leaves each line part written in the L2
+// when it is evicted, over and over; a run of a line's length reaches its line
+// (or two) at once. 2^20 unbiased walkers x 80: 2.63 ms with runs of 8, 2.53
+// with 16, 2.37 with 32 and 2.25 with 64, although the registers cost
+// occupancy; 262,144 weighted walkers: 1.05 ms with 8 to 32, 1.12 with 64.
+typedef int32_t PathQuad __attribute__((ext_vector_type(4), aligned(4)));
+template <int kPathRun>
+struct PathRun {
+    int32_t e[kPathRun] = {};
+    int n = 0;
+    int64_t at = 1;  // path index of e[0]
+    __device__ __forceinline__ void flush(int32_t* path) {
+#pragma unroll
+        for (int j = 0; j < kPathRun; ++j)
+            if (j < n) path[at + j] = e[j];
+        at += n;
+        n = 0;
+    }
+    __device__ __forceinline__ void push(int32_t* path, int32_t x) {
+#pragma unroll
+        for (int j = 0; j < kPathRun; ++j) e[j] = n == j ? x : e[j];
+        if (++n == kPathRun) {
+#pragma unroll
+            for (int j = 0; j < kPathRun; j += 4)
+                *(PathQuad*)(path + at + j) = PathQuad{e[j], e[j + 1], e[j + 2], e[j + 3]};
+            at += kPathRun;
+            n = 0;
+        }
+    }
+};
+
+// v's list.
+__device__ __forceinline__ void list_of(const GraphDev& g, int32_t v, int64_t& beg, int64_t& d) {
+    beg = g.rowptr[v];
+    d = g.rowptr[v + 1] - beg;
+}
+
+// Unbiased walks, one lane per walker. kHops: the graph has its hop table, and a
+// step is one scattered 16-byte read, the picked edge's record (neighbor and
+// its list), plus its share of a path run; without the table, the neighbor id
+// and then its row offsets. Scattered lines bound it (41e9 a second on this
+// chip): 2^20 walkers x 80 on 500M edges took 4.96 ms with two reads a step and
+// a 4-byte path store each, 2.25 ms with one read and runs.
 // kMH: Metropolis-Hastings (Section II-A): the uniform pick u is a proposal,
 // accepted iff x * deg(u) < deg(v) * 2^32 for x in [0, 2^32) drawn with
 // counter (walker id, step, v, 4); a rejected proposal is a step that stays.
-template <bool kMH>
+template <bool kMH, bool kHops>
 __global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t w0 = blockIdx.x * (int64_t)blockDim.x; w0 < p.num_walkers; w0 += stride) {
@@ -103,27 +147,43 @@ __global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
                 path[0] = v;
                 const int32_t start = v;
                 const uint32_t c0 = wc.c0;
+                PathRun<64> run;
+                int64_t beg, d;
+                list_of(p.g, v, beg, d);
                 for (; s < wc.length; ++s) {
                     int32_t to;
                     if (walk_move(p, key, c0, s, v, start, to)) {
                         v = to;
-                        path[s + 1] = v;
+                        list_of(p.g, v, beg, d);
+                        run.push(path, v);
                         continue;
                     }
-                    const int64_t beg = p.g.rowptr[v];
-                    const int64_t d = p.g.rowptr[v + 1] - beg;
                     if (d == 0) break;
                     const uint64_t r = draw(key, c0, (uint32_t)s, (uint32_t)v, 0u, (uint64_t)d);
-                    const int32_t u = p.g.col[beg + (int64_t)r];
-                    if (kMH) {
-                        const uint64_t du = (uint64_t)(p.g.rowptr[u + 1] - p.g.rowptr[u]);
-                        const uint64_t x = draw(key, c0, (uint32_t)s, (uint32_t)v, 4u, uint64_t(1) << 32);
-                        if (x * du < ((uint64_t)d << 32)) v = u;
+                    int32_t u;
+                    int64_t ub, ud;
+                    if (kHops) {
+                        const uint4 h = *(const uint4*)(p.g.hops + beg + (int64_t)r);
+                        u = (int32_t)h.x;
+                        ub = h.y;
+                        ud = h.z;
                     } else {
-                        v = u;
+                        u = p.g.col[beg + (int64_t)r];
+                        list_of(p.g, u, ub, ud);
                     }
-                    path[s + 1] = v;
+                    bool move = true;
+                    if (kMH) {
+                        const uint64_t x = draw(key, c0, (uint32_t)s, (uint32_t)v, 4u, uint64_t(1) << 32);
+                        move = x * (uint64_t)ud < ((uint64_t)d << 32);
+                    }
+                    if (move) {
+                        v = u;
+                        beg = ub;
+                        d = ud;
+                    }
+                    run.push(path, v);
                 }
+                run.flush(path);
                 for (int64_t q = s + 1; q < L1; ++q) path[q] = -1;
             }
             my_steps = s;
@@ -134,6 +194,14 @@ __global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
             const int64_t ws = wave_sum_i64(my_steps);
             if (lane_id() == 0 && ws) atomicAdd(p.steps, (unsigned long long)ws);
         }
+    }
+}
+
+__global__ void k_walk_hops(RowPtr rowptr, const int32_t* __restrict__ col, int64_t m, WalkHop* __restrict__ hops) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t x = col[e];
+        const int64_t b = rowptr[x];
+        *(uint4*)(hops + e) = make_uint4((uint32_t)x, (uint32_t)b, (uint32_t)(rowptr[x + 1] - b), 0u);
     }
 }
 
@@ -891,29 +959,6 @@ constexpr int kLaneProbe = 8;
 // 8,192 walkers, ahead at 16,384).
 constexpr int64_t kLaneWalkMin = 12288;
 
-// A lane's path entries, written kPathRun at a time: a 4-byte store into a row
-// of its own per step leaves each line part written in the L2 when it is
-// evicted, over and over; a run of consecutive entries reaches its line at
-// once.
-constexpr int kPathRun = 8;
-struct PathRun {
-    int32_t e[kPathRun] = {};
-    int n = 0;
-    int64_t at = 1;  // path index of e[0]
-    __device__ __forceinline__ void flush(int32_t* path) {
-#pragma unroll
-        for (int j = 0; j < kPathRun; ++j)
-            if (j < n) path[at + j] = e[j];
-        at += n;
-        n = 0;
-    }
-    __device__ __forceinline__ void push(int32_t* path, int32_t x) {
-#pragma unroll
-        for (int j = 0; j < kPathRun; ++j) e[j] = n == j ? x : e[j];
-        if (++n == kPathRun) flush(path);
-    }
-};
-
 template <bool kMoves>
 __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
     const bool dg = p.bias == kNeighborDegree;
@@ -940,7 +985,7 @@ __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
                 path[0] = v;
                 const int32_t start = v;
                 const uint32_t c0 = wc.c0;
-                PathRun run;
+                PathRun<32> run;
                 for (; s < wc.length; ++s) {
                     int32_t to;
                     if (kMoves && walk_move(p, key, c0, s, v, start, to)) {
@@ -1085,6 +1130,13 @@ __global__ void __launch_bounds__(kBlock) k_walk_guides(RowPtr rowptr, const int
 
 }  // namespace
 
+void launch_walk_hops(RowPtr rowptr, const int32_t* col, int64_t m, WalkHop* hops, hipStream_t s) {
+    if (m <= 0) return;
+    int64_t g = (m + kBlock - 1) / kBlock;
+    if (g > 65536) g = 65536;
+    hipLaunchKernelGGL(k_walk_hops, dim3((unsigned)g), dim3(kBlock), 0, s, rowptr, col, m, hops);
+}
+
 void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, const uint64_t* wtot, int64_t n,
                         WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, hipStream_t s) {
     if (n <= 0) return;
@@ -1107,8 +1159,10 @@ void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev) 
     if (p.bias == kUniform || flat_n2v || p.bias == kMetropolis) {
         int64_t g = (p.num_walkers + kBlock - 1) / kBlock;
         if (g > grid) g = grid;
-        if (p.bias == kMetropolis) launch_kernel(k_walk_uniform<true>, dim3((unsigned)g), dim3(kBlock), s, ev, p);
-        else launch_kernel(k_walk_uniform<false>, dim3((unsigned)g), dim3(kBlock), s, ev, p);
+        const bool mh = p.bias == kMetropolis;
+        launch_kernel(p.g.hops ? (mh ? k_walk_uniform<true, true> : k_walk_uniform<false, true>)
+                               : (mh ? k_walk_uniform<true, false> : k_walk_uniform<false, false>),
+                      dim3((unsigned)g), dim3(kBlock), s, ev, p);
     } else {
         int64_t g = (p.num_walkers + kWavesPerBlock - 1) / kWavesPerBlock;
         if (g > grid) g = grid;
