@@ -310,16 +310,17 @@ csaw_status csaw_walk(csaw_graph g, const csaw_walk_args* args, int32_t* paths,
  * the inverse transform selection of Section II-B, Eq. equ:tp, served in
  * a constant expected number of loads). On a weight
  * array's first walk the graph builds, once: the exact inclusive prefix of
- * every edge in its list (8 bytes per edge), and per list of total W and
- * degree d a table of K <= 2 d equal buckets of width 2^s over [0, W), each
- * holding the first position whose interval reaches its start, with that
- * position's prefix and neighbor (16 bytes per bucket, 2 m + n entries),
- * and per vertex its list and W (16 bytes, when m < 2^32). A step's draw r
- * then lies between the positions of buckets r >> s and (r >> s) + 1, and
- * m = #{i : S_(i+1) <= r} follows from the two buckets or a few exact
- * prefixes: the same pick as a search of the whole prefix. About 48 bytes
- * per edge per weight array (51 GB for 2^30 edges); with the guide off (or
- * not yet built in a caller memory call) walks take the chunk tables with
+ * every edge in its list beside its neighbor and weight (16 bytes per edge),
+ * per vertex its list and W (16 bytes, when m < 2^32), and per list of total
+ * W and degree d a table of K <= 4 d equal buckets of width 2^s over [0, W), each
+ * naming the position whose interval holds its start, and where at most two
+ * positions meet it the two neighbors and the bound between them (16 bytes
+ * per bucket, 4 m + n entries; 2 m + n where that would be more than a third of
+ * the free device memory). A step's draw r reads bucket r >> s, which names
+ * the pick nine times in ten, else the edge records from its position on: the
+ * same pick as a search of the whole prefix. About 80 bytes per edge per
+ * weight array (85 GB for 2^30 edges), or 48; with the guide off (or not yet
+ * built in a caller memory call) walks take the chunk tables with
  * one wavefront per walker, with the same paths. Sampling calls draw
  * through a weight array's guide when it is built and on (a walk or a server
  * builds it, or csaw_sample once its calls have sampled m / 4 edges by that

@@ -50,15 +50,22 @@ struct alignas(16) WalkVertex {
     uint32_t d;
 };
 
-// One bucket of a list's walk guide: the position i whose interval
-// [S_i, S_(i+1)) holds the bucket's start, with that position's exact
-// prefix S_(i+1) and neighbor, so that a bracket of one or two positions
-// needs no edge record.
+// One bucket of a list's walk guide: what a draw r in [k 2^s, (k+1) 2^s) needs
+// nine times in ten, in one 16-byte read. pos is the position whose interval
+// [S_i, S_(i+1)) holds the bucket's start and col its neighbor. Where the
+// intervals of at most two positions meet the bucket, S holds the first one's
+// end relative to the bucket's start (low half, ~0 where it reaches the bucket's
+// end) and the second one's neighbor (high half); otherwise the high half is
+// ~0 and r is searched in the edge records from pos on. (Weights of 32 bits keep
+// s below 32.)
 struct alignas(16) WalkBucket {
     uint64_t S;
     uint32_t pos;
     int32_t col;
 };
+
+constexpr int kGuideBucketsPerEdge = 4;  // a list of d edges gets at most 4 d buckets ...
+constexpr int kGuideBucketsScarce = 2;   // ... or 2 d where memory is short
 
 // One edge of the hop table (graphs with m < 2^32): the neighbor and its list
 // [beg, beg + d), so that an unbiased step reads one 16-byte record where the
@@ -94,15 +101,15 @@ struct GraphDev {
     // array): wrec[e] = edge e's inclusive prefix in its list and its
     // neighbor (lists with a positive total); wvtx[v] = v's list and total
     // (every vertex; null when m >= 2^32); the list v starting at edge b
-    // owns the buckets wgd[2 b + v + k], k < K (at most 2 d of its 2 d + 1
-    // slots; K and s from guide_shift): the first position i with
-    // S_(i+1) > k * 2^s, its S_(i+1) and its neighbor
+    // owns the buckets wgd[guide_base(b, v) + k], k < K (K and s from
+    // guide_shift)
     const WalkEdge* wrec_ew;
     const WalkEdge* wrec_deg;
     const WalkVertex* wvtx_ew;
     const WalkVertex* wvtx_deg;
     const WalkBucket* wgd_ew;
     const WalkBucket* wgd_deg;
+    int32_t gper_ew = kGuideBucketsPerEdge, gper_deg = kGuideBucketsPerEdge;  // buckets per edge, per weight array
     const WalkHop* hops = nullptr;  // m, or null
 };
 
@@ -303,21 +310,24 @@ struct WalkParams {
 };
 void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev = {});
 // The walk guide tables of weight array w (list totals wtot): rec[m],
-// vtx[n] (may be null), gd[2 m + n].
+// vtx[n] (may be null), gd[kGuideBucketsPerEdge * m + n].
 void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, const uint64_t* wtot, int64_t n,
                         WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, hipStream_t s);
 // The hop table of a graph (weak: see free_device_bytes).
 __attribute__((weak)) void launch_walk_hops(RowPtr rowptr, const int32_t* col, int64_t m, WalkHop* hops, hipStream_t s);
-constexpr int kGuideBucketsPerEdge = 2;  // a list of d edges gets at most 2 d buckets
+// The same with at most per d buckets (weak: see free_device_bytes).
+__attribute__((weak)) void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w,
+                                              const uint64_t* wtot, int64_t n, WalkEdge* rec, WalkVertex* vtx,
+                                              WalkBucket* gd, int per, hipStream_t s);
 
 // Buckets of a list's walk guide: width 2^s, K = ((W - 1) >> s) + 1 of them,
-// s the smallest shift that keeps K within kGuideBucketsPerEdge * d (d >= 1,
-// W > 0). A draw r lies in bucket r >> s, whose entry and the next one's
-// bracket the positions that can hold it; with buckets no wider than the
-// list's mean weight a bracket holds about two positions on average
-// whatever the weights are. Shared by the table builder and the walk steps.
-__host__ __device__ __forceinline__ int guide_shift(uint64_t W, int64_t d) {
-    const uint64_t kmax = (uint64_t)d * kGuideBucketsPerEdge, top = W - 1;
+// s the smallest shift that keeps K within per * d (d >= 1, W > 0). A draw r
+// lies in bucket r >> s. With four buckets per edge a quarter to a half of
+// an interval's end lies in a bucket on average whatever the weights are, and
+// 3 to 9% of the buckets meet more than two positions (with two per edge 9 to 26%).
+// Shared by the table builder and the kernels.
+__host__ __device__ __forceinline__ int guide_shift(uint64_t W, int64_t d, int per = kGuideBucketsPerEdge) {
+    const uint64_t kmax = (uint64_t)d * per, top = W - 1;
     if (top < kmax) return 0;
     // bit lengths: top >> s < kmax needs s >= len(top) - len(kmax), and at
     // most one more
@@ -326,8 +336,10 @@ __host__ __device__ __forceinline__ int guide_shift(uint64_t W, int64_t d) {
     while ((top >> s) >= kmax) ++s;
     return s;
 }
-// Entry 0 of list v's guide (first edge b).
-__host__ __device__ __forceinline__ int64_t guide_base(int64_t b, int64_t v) { return kGuideBucketsPerEdge * b + v; }
+// Bucket 0 of list v's guide (first edge b).
+__host__ __device__ __forceinline__ int64_t guide_base(int64_t b, int64_t v, int per = kGuideBucketsPerEdge) {
+    return per * b + v;
+}
 // Sets *flag to 1 if some edge (u, x) has no reverse edge (x, u); lists must
 // be sorted (each reverse edge is found by binary search).
 void launch_symmetric_check(RowPtr rowptr, const int32_t* col, int64_t n, int32_t* flag, hipStream_t s);

@@ -235,6 +235,7 @@ struct csaw_graph_s {
     WalkVertex* wvtx_deg = nullptr;
     WalkBucket* wgd_ew = nullptr;
     WalkBucket* wgd_deg = nullptr;
+    int32_t gper_ew = kGuideBucketsPerEdge, gper_deg = kGuideBucketsPerEdge;
     WalkHop* hops = nullptr;       // hop table of unbiased steps
     mutable std::mutex mu;               // lazy preparation + workspace pool
     std::vector<Workspace*> pool;
@@ -266,6 +267,8 @@ struct csaw_graph_s {
         g.wvtx_deg = wvtx_deg;
         g.wgd_ew = wgd_ew;
         g.wgd_deg = wgd_deg;
+        g.gper_ew = gper_ew;
+        g.gper_deg = gper_deg;
         g.hops = hops;
         if (!walk_guides.load()) {  // walks and long-list draws take the chunk tables
             g.wrec_ew = g.wrec_deg = nullptr;
@@ -402,11 +405,16 @@ csaw_status prepare_bias(csaw_graph g, int32_t kind, hipStream_t s) {
     return CSAW_OK;
 }
 
+size_t guide_bytes(csaw_graph g, int per) {
+    return (size_t)g->m * sizeof(WalkEdge) + (size_t)g->n * sizeof(WalkVertex) +
+           (size_t)(per * g->m + g->n) * sizeof(WalkBucket);
+}
+
 // The walk guide tables of a weight array whose bias tables exist (per-edge
 // prefix and neighbor records, 16 bytes per edge; per-vertex list records,
-// 16 bytes per vertex, when m < 2^32; buckets, 16 bytes each and at most two
-// per edge), built once; a graph without them walks through the chunk
-// tables.
+// 16 bytes per vertex, when m < 2^32; buckets, 16 bytes each and at most four
+// per edge, or two where four would be more than a third of the free device
+// memory), built once; a graph without them walks through the chunk tables.
 csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     std::lock_guard<std::mutex> lk(g->mu);
     const bool dg = kind == kNeighborDegree;
@@ -419,15 +427,18 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     WalkVertex* vtx = nullptr;
     WalkBucket* gd = nullptr;
     const bool small = g->m < (int64_t(1) << 32);  // vertex records hold 32-bit list offsets
+    const bool scarce = free_device_bytes && guide_bytes(g, kGuideBucketsPerEdge) > free_device_bytes() / 3;
+    const int per = scarce ? kGuideBucketsScarce : kGuideBucketsPerEdge;
     if (hipMalloc((void**)&rec, (size_t)g->m * sizeof(WalkEdge)) != hipSuccess ||
         (small && hipMalloc((void**)&vtx, (size_t)std::max<int64_t>(g->n, 1) * sizeof(WalkVertex)) != hipSuccess) ||
-        hipMalloc((void**)&gd, (size_t)(kGuideBucketsPerEdge * g->m + g->n) * sizeof(WalkBucket)) != hipSuccess) {
+        hipMalloc((void**)&gd, (size_t)(per * g->m + g->n) * sizeof(WalkBucket)) != hipSuccess) {
         (void)hipGetLastError();  // the caller may go on without the tables
         if (rec) (void)hipFree(rec);
         if (vtx) (void)hipFree(vtx);
         return fail(CSAW_ERR_OUT_OF_MEMORY, "walk guide tables: allocation failed");
     }
-    launch_walk_guides(g->rowptr, g->col, w, tot, g->n, rec, vtx, gd, s);
+    if (!scarce) launch_walk_guides(g->rowptr, g->col, w, tot, g->n, rec, vtx, gd, s);
+    else launch_walk_guides(g->rowptr, g->col, w, tot, g->n, rec, vtx, gd, per, s);
     const hipError_t e = hipGetLastError() != hipSuccess ? hipErrorLaunchFailure : hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(rec);
@@ -437,6 +448,7 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     }
     (dg ? g->wrec_deg : g->wrec_ew) = rec;
     (dg ? g->wvtx_deg : g->wvtx_ew) = vtx;
+    (dg ? g->gper_deg : g->gper_ew) = per;
     (dg ? g->wgd_deg : g->wgd_ew) = gd;
     return CSAW_OK;
 }
@@ -453,9 +465,7 @@ void guides_for_sampling(csaw_graph g, int32_t kind, hipStream_t s) {
         std::lock_guard<std::mutex> lk(g->mu);
         if (kind == kNeighborDegree ? g->wgd_deg : g->wgd_ew) return;
     }
-    const size_t bytes = (size_t)g->m * sizeof(WalkEdge) + (size_t)g->n * sizeof(WalkVertex) +
-                         (size_t)(kGuideBucketsPerEdge * g->m + g->n) * sizeof(WalkBucket);
-    if (bytes <= free_device_bytes() / 2 && prepare_walk_guides(g, kind, s) != CSAW_OK) t_err.clear();
+    if (guide_bytes(g, kGuideBucketsPerEdge) <= free_device_bytes() / 2 && prepare_walk_guides(g, kind, s) != CSAW_OK) t_err.clear();
 }
 
 // The hop table (16 bytes per edge), built for the call about to take `steps`

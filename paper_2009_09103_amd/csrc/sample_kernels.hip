@@ -1087,18 +1087,17 @@ __device__ __forceinline__ int32_t slot_search(const GraphDev& g, int32_t kind, 
         }
         return m;
     }
-    const WalkBucket* G = (ew ? g.wgd_ew : g.wgd_deg) + guide_base(beg, v);
-    const int sh = guide_shift(W, d);
+    const int per = ew ? g.gper_ew : g.gper_deg;
+    const int sh = guide_shift(W, d, per);
     const uint64_t k = r >> sh;
-    const bool last = k + 1 > (W - 1) >> sh;
-    const WalkBucket b0 = G[k], b1 = G[last ? k : k + 1];
-    int32_t lo = (int32_t)b0.pos;
-    const int32_t hi = last ? d - 1 : (int32_t)b1.pos;
-    if (hi == lo || (!last && hi == lo + 1)) {  // the buckets hold the bracket's prefixes and ids
-        const bool first = hi == lo || b0.S > r;
-        nb = first ? b0.col : b1.col;
-        return first ? lo : hi;
+    const WalkBucket b = ((ew ? g.wgd_ew : g.wgd_deg) + guide_base(beg, v, per))[k];
+    if ((uint32_t)(b.S >> 32) != ~0u) {
+        const bool second = (uint32_t)(r - (k << sh)) >= (uint32_t)b.S;
+        nb = second ? (int32_t)(b.S >> 32) : b.col;
+        return (int32_t)b.pos + (second ? 1 : 0);
     }
+    int32_t lo = (int32_t)b.pos;
+    const int32_t hi = d - 1;
     const WalkEdge* er = (ew ? g.wrec_ew : g.wrec_deg) + beg;
     constexpr int kProbe = 4;
     for (;;) {  // edge records from lo on (positions past hi read hi, whose prefix exceeds r)

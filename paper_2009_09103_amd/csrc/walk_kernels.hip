@@ -7,11 +7,10 @@
 //   - unbiased walks: one lane per walker (a step is two row-offset loads,
 //     one Philox draw and one neighbor load);
 //   - edge-weight and degree-biased walks through the graph's walk guide
-//     (exact per-edge prefixes and a bucket table per list; a step is three
-//     rounds of loads): one lane per walker in launches of at least
-//     kLaneWalkMin walkers, else one wavefront per walker (lists of at most
-//     512 scanned whole); with the guide off, one wavefront per walker
-//     through the chunk tables;
+//     (exact per-edge prefixes and a bucket table per list; a step is two
+//     rounds of loads, now and then three): one lane per walker in launches of at
+//     least kLaneWalkMin walkers, else one wavefront per walker; with the guide
+//     off, one wavefront per walker through the chunk tables;
 //   - other biased walks: one wavefront per walker; pass 1 streams the
 //     biases of N(v) into a coarse prefix table in LDS, r is drawn in [0, W),
 //     and pass 2 rescans only the group of the table that holds r.
@@ -721,47 +720,29 @@ __device__ __forceinline__ int32_t walk_step_long(const uint32_t* __restrict__ w
 }
 
 // First-order weighted step on a list longer than kWaveMaxD through its walk
-// guide, one wavefront per walker: r is drawn in [0, W) (W, the list's total,
-// came with the row offsets), its bucket k = r >> s gives the bracket
-// [G[k], G[k+1]] that holds the pick (every position before G[k] ends at or
-// below k * 2^s <= r, and G[k+1] ends past (k+1) * 2^s > r), and one load of
-// the bracket's exact prefixes and neighbor ids finds m = #{i : S_(i+1) <= r}
-// by ballot. Three dependent loads per step (row offsets and W, the bracket,
-// its prefixes), two when the bracket holds one or two positions (the
-// buckets carry their positions' prefixes and ids). Returns the neighbor,
-// or -2 when the bracket is wider than a
-// wavefront (many small weights in one bucket), which the caller takes
-// through the chunk tables.
-__device__ __forceinline__ int32_t walk_step_guide(const WalkEdge* __restrict__ er,
-                                                   const WalkBucket* __restrict__ gd, uint64_t r, uint64_t W,
-                                                   int64_t beg, int64_t d, int64_t v) {
+// guide, one wavefront per walker: r's bucket names the pick (one load after
+// the row offsets and the list's total) or the first position that can be it;
+// then the edge records from there on, 64 at a time, exact prefixes beside
+// neighbor ids. Returns the neighbor.
+__device__ __forceinline__ int32_t walk_step_guide(const WalkEdge* __restrict__ er, const WalkBucket* __restrict__ gd,
+                                                   int per, uint64_t r, uint64_t W, int64_t beg, int64_t d, int64_t v) {
     const int lane = lane_id();
-    const int sh = guide_shift(W, d);
-    const uint64_t K = ((W - 1) >> sh) + 1;
+    const int sh = guide_shift(W, d, per);
     const uint64_t k = r >> sh;
-    const WalkBucket* G = gd + guide_base(beg, v);
-    const bool last = k + 1 >= K;
-    const WalkBucket* q0 = G + k;
-    const WalkBucket* q1 = G + (last ? k : k + 1);
-    const WalkBucket b0{ld_uniform(&q0->S), ld_uniform(&q0->pos), ld_uniform(&q0->col)};
-    const WalkBucket b1{ld_uniform(&q1->S), ld_uniform(&q1->pos), ld_uniform(&q1->col)};
-    const int64_t lo = b0.pos;
-    const int64_t hi = last ? d - 1 : (int64_t)b1.pos;
-    // a bracket of one or two positions: the buckets hold their prefixes and ids
-    if (hi == lo) return b0.col;
-    if (!last && hi == lo + 1) return b0.S > r ? b0.col : b1.col;
-    const int64_t n = hi - lo + 1;
-    if (n > kWave) return -2;
-    // both loads issued at clamped positions, then the lanes past the
-    // bracket masked: guarded loads were waited for one after the other
-    const bool in = lane < n;
-    const int64_t j = beg + lo + (in ? lane : n - 1);
-    uint64_t S = er[j].S;
-    const int32_t y = er[j].col;
-    __builtin_amdgcn_sched_barrier(0);  // both loads in flight before either is used
-    S = in ? S : ~0ull;
-    const int c = __popcll(ballot(S <= r));
-    return readlane_i32(y, c);
+    const WalkBucket* q = gd + guide_base(beg, v, per) + k;
+    const WalkBucket b{ld_uniform(&q->S), ld_uniform(&q->pos), ld_uniform(&q->col)};
+    if ((uint32_t)(b.S >> 32) != ~0u)
+        return (uint32_t)(r - (k << sh)) >= (uint32_t)b.S ? (int32_t)(b.S >> 32) : b.col;
+    for (int64_t lo = b.pos;; lo += kWave) {
+        // both loads issued at clamped positions (the list's last prefix
+        // exceeds r): guarded loads were waited for one after the other
+        const int64_t j = beg + (lo + lane < d ? lo + lane : d - 1);
+        const uint64_t S = er[j].S;
+        const int32_t y = er[j].col;
+        __builtin_amdgcn_sched_barrier(0);  // both loads in flight before either is used
+        const int c = __popcll(ballot(S <= r));
+        if (c < kWave) return readlane_i32(y, c);
+    }
 }
 
 // node2vec step from v when the previous vertex t has a short list (fewer
@@ -892,12 +873,14 @@ __device__ __forceinline__ void walk_wave_body(const WalkParams& p) {
                             nx = walk_step_short(wts, p.g.col, reinterpret_cast<uint32_t*>(lds.tab), u, beg, (int32_t)d,
                                                  stop);
                         } else {
-                            nx = -2;
                             if (gd) {
                                 stop = wt == 0;
-                                if (!stop) nx = walk_step_guide(er, gd, range_reduce(u, wt), wt, beg, d, v);
+                                if (!stop)
+                                    nx = walk_step_guide(er, gd, dg ? p.g.gper_deg : p.g.gper_ew, range_reduce(u, wt), wt, beg,
+                                                         d, v);
+                            } else {
+                                nx = walk_step_long(wts, p.g.col, gt, ct, u, beg, d, stop);
                             }
-                            if (nx == -2 && !stop) nx = walk_step_long(wts, p.g.col, gt, ct, u, beg, d, stop);
                         }
                     } else {
                         m = walk_step_biased<false>(p, lds, key, c0, s, v, beg, d, t, tb, te, stop);
@@ -938,25 +921,25 @@ __global__ void __launch_bounds__(kBlock) k_walk_wave_n2v(WalkParams p) {
 // Weighted first-order walks through the walk guide, one lane per walker
 // (64 walkers per wavefront, each with its own chain of loads). A step:
 // the vertex's record, its list and total W (one 16-byte load; the Philox
-// word is formed meanwhile), r = floor(u W / 2^64), the bracket
-// [G[k], G[k+1]] of bucket k = r >> s (one load of two 16-byte buckets; a
-// bracket of one or two positions is decided by the buckets' own prefixes
-// and ids, about 80% of steps), else the edge records of the bracket's first
-// kLaneProbe positions, exact prefixes beside neighbor ids (one round):
-// m = lo + #{j : S_(lo+j+1) <= r}. The walk is bound by the 128-byte lines
-// these scattered reads pull from HBM, so each round reads one line where
-// it can. Positions
-// past the bracket's end are read at the end instead, whose prefix exceeds r,
-// so every load stays inside the list and needs no mask. A bracket longer
-// than the probe (rare: a run of small weights inside one bucket) takes
-// further rounds from where the last one stopped. A list of one edge skips
-// the bracket. The pick is the same m as a scan of the whole list.
-constexpr int kLaneProbe = 8;
-// A lane's round waits for the slowest of its wavefront's 64 scattered
-// loads, so an unloaded lane step takes longer than a wavefront step (3.3
-// against 2.0 us at 2,048 walkers); the lane kernel wins once a launch has
-// enough walkers to keep many lanes' chains in flight (measured: behind at
-// 8,192 walkers, ahead at 16,384).
+// word is formed meanwhile), r = floor(u W / 2^64), and r's bucket (one 16-byte
+// load), which names the pick nine times in ten; else the edge records of
+// kLaneProbe positions at a time from the bucket's first one on, exact prefixes
+// beside neighbor ids: m = lo + #{j : S_(lo+j+1) <= r}. The walk is bound by
+// the 128-byte lines these scattered reads pull from HBM and by the number of
+// scattered reads, so a step makes two where it can: 262,144 walkers x 80 on
+// 500M edges took 1.05 ms with pairs of buckets of one position each, two
+// per edge; 0.83 ms with this (0.91 with two buckets per edge, 0.76 with eight). (One 128-byte block per two to four positions, with each
+// neighbor's own list in it, is one line a step but three or more reads of it, and took
+// 1.36 ms; 2.5 ms reading the block whole.) Positions
+// past the list's end are read at its end instead, whose prefix exceeds r,
+// so every load stays inside the list and needs no mask. The pick is the same m
+// as a scan of the whole list.
+constexpr int kLaneProbe = 4;
+// A lane's round waits for the slowest of its wavefront's 64 scattered loads, so
+// an unloaded lane step takes longer than a wavefront's (3.1 against 1.4 us at
+// 2,048 walkers); the lane kernel wins once a launch has enough walkers to keep
+// many lanes' chains in flight (length 80 on 500M edges: 255 against 205 us at 8,192
+// walkers, 261 against 263 at 12,288, 276 against 338 at 16,384).
 constexpr int64_t kLaneWalkMin = 12288;
 
 template <bool kMoves>
@@ -965,6 +948,7 @@ __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
     const WalkVertex* __restrict__ vt = dg ? p.g.wvtx_deg : p.g.wvtx_ew;
     const WalkEdge* __restrict__ er = dg ? p.g.wrec_deg : p.g.wrec_ew;
     const WalkBucket* __restrict__ gd = dg ? p.g.wgd_deg : p.g.wgd_ew;
+    const int per = dg ? p.g.gper_deg : p.g.gper_ew;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t w0 = blockIdx.x * (int64_t)blockDim.x; w0 < p.num_walkers; w0 += stride) {
         const int64_t w = w0 + threadIdx.x;
@@ -1001,47 +985,28 @@ __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
                     asm volatile("" : "+v"(u));
                     if (d == 0 || W == 0) break;
                     const uint64_t r = range_reduce(u, W);
-                    int64_t lo = 0, hi = 0;
-                    int32_t nx = -1;
-                    bool done = false;
-                    if (d > 1) {
-                        const int sh = guide_shift(W, d);
-                        const uint64_t K = ((W - 1) >> sh) + 1;
-                        const uint64_t k = r >> sh;
-                        const WalkBucket* G = gd + guide_base(beg, v);
-                        const bool last = k + 1 >= K;
-                        const WalkBucket b0 = G[k], b1 = G[last ? k : k + 1];
-                        lo = b0.pos;
-                        hi = last ? d - 1 : (int64_t)b1.pos;
-                        // a bracket of one or two positions needs no edge record
-                        if (hi == lo) {
-                            nx = b0.col;
-                            done = true;
-                        } else if (!last && hi == lo + 1) {
-                            nx = b0.S > r ? b0.col : b1.col;
-                            done = true;
+                    const int sh = guide_shift(W, d, per);
+                    const uint64_t k = r >> sh;
+                    const WalkBucket bk = (gd + guide_base(beg, v, per))[k];
+                    int32_t nx = (uint32_t)(r - (k << sh)) >= (uint32_t)bk.S ? (int32_t)(bk.S >> 32) : bk.col;
+                    if ((uint32_t)(bk.S >> 32) == ~0u) {
+                        for (int64_t lo = bk.pos;; lo += kLaneProbe) {
+                            uint64_t S[kLaneProbe];
+                            int32_t y[kLaneProbe];
+#pragma unroll
+                            for (int j = 0; j < kLaneProbe; ++j) {
+                                const uint4 e = *(const uint4*)(er + beg + (lo + j < d ? lo + j : d - 1));
+                                S[j] = (uint64_t)e.x | ((uint64_t)e.y << 32);
+                                y[j] = (int32_t)e.z;
+                            }
+                            int c = 0;
+#pragma unroll
+                            for (int j = 0; j < kLaneProbe; ++j) c += S[j] <= r ? 1 : 0;
+                            nx = y[0];
+#pragma unroll
+                            for (int j = 1; j < kLaneProbe; ++j) nx = c == j ? y[j] : nx;
+                            if (c < kLaneProbe) break;
                         }
-                    }
-                    while (!done) {
-                        uint64_t S[kLaneProbe - 1];
-                        int32_t y[kLaneProbe];
-#pragma unroll
-                        for (int j = 0; j < kLaneProbe; ++j) {
-                            const int64_t q = beg + (lo + j < hi ? lo + j : hi);
-                            if (j < kLaneProbe - 1) S[j] = er[q].S;
-                            y[j] = er[q].col;
-                        }
-                        int c = 0;
-#pragma unroll
-                        for (int j = 0; j < kLaneProbe - 1; ++j) c += S[j] <= r ? 1 : 0;
-                        nx = y[0];
-#pragma unroll
-                        for (int j = 1; j < kLaneProbe; ++j) nx = c == j ? y[j] : nx;
-                        // keeps the id loads in this round: left to itself the
-                        // compiler sinks them past the loop, a round of their own
-                        asm volatile("" ::"v"(nx));
-                        if (c < kLaneProbe - 1 || lo + kLaneProbe - 1 >= hi) break;
-                        lo += kLaneProbe - 1;
                     }
                     v = nx;
                     run.push(path, v);
@@ -1057,6 +1022,61 @@ __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
             const int64_t ws = wave_sum_i64(my_steps);
             if (lane_id() == 0 && ws) atomicAdd(p.steps, (unsigned long long)ws);
         }
+    }
+}
+
+// The same, one wavefront per walker, for launches of too few walkers for the
+// lanes: what counts is one walker's chain of loads, the vertex's record and the
+// bucket (and one time in ten the edge records, 64 at a time), both read
+// through the scalar cache while the vector unit forms the draw. Path entries
+// are kept one per lane and written 64 at a time. 4,000 walkers x 2,000 on 500M
+// edges: 3.63 ms with row offsets and total read apart, pairs of buckets
+// and lists of at most 512 scanned whole, 3.55 with these buckets, 2.62 here.
+template <bool kMoves>
+__global__ void __launch_bounds__(kBlock) k_walk_wave_guide(WalkParams p) {
+    const int lane = lane_id();
+    const int wid = uniform_i32(threadIdx.x / kWave);
+    const bool dg = p.bias == kNeighborDegree;
+    const WalkVertex* __restrict__ vt = dg ? p.g.wvtx_deg : p.g.wvtx_ew;
+    const WalkEdge* __restrict__ er = dg ? p.g.wrec_deg : p.g.wrec_ew;
+    const WalkBucket* __restrict__ gd = dg ? p.g.wgd_deg : p.g.wgd_ew;
+    const int per = dg ? p.g.gper_deg : p.g.gper_ew;
+    const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+    for (int64_t w = blockIdx.x * (int64_t)kWavesPerBlock + wid; w < p.num_walkers; w += waves) {
+        const WalkerCtx wc = walker_ctx(p, w);
+        const Key key{(uint32_t)uniform_i32((int32_t)wc.key.k0), (uint32_t)uniform_i32((int32_t)wc.key.k1)};
+        const int32_t length = uniform_i32(wc.length);
+        const int64_t L1 = (int64_t)length + 1;
+        int32_t* path = wc.path;
+        int32_t v = uniform_i32(p.starts[w]);
+        if (v < 0 || (int64_t)v >= p.g.n) {
+            if (lane == 0) *p.bad_start = 1;
+            for (int64_t q = lane; q < L1; q += kWave) path[q] = -1;
+            continue;
+        }
+        const uint32_t c0 = (uint32_t)uniform_i32((int32_t)wc.c0);
+        const int32_t start = v;
+        int32_t mine = v;  // path entry i is kept by lane i % 64
+        int32_t s = 0;
+        for (; s < length; ++s) {
+            int32_t to;
+            if (kMoves && walk_move(p, key, c0, s, v, start, to)) {  // uniform: the draw depends on wave-uniform values
+                v = uniform_i32(to);
+            } else {
+                const uint64_t W = ld_uniform(&vt[v].W);
+                const int64_t beg = ld_uniform(&vt[v].beg), d = ld_uniform(&vt[v].d);
+                const uint64_t u = philox_vec(key, c0, (uint32_t)s, (uint32_t)v, 0u);
+                if (d == 0 || W == 0) break;
+                v = walk_step_guide(er, gd, per, range_reduce(u, W), W, beg, d, v);
+            }
+            const int32_t i = s + 1;
+            if (lane == (i & (kWave - 1))) mine = v;
+            if ((i & (kWave - 1)) == kWave - 1) path[i - (kWave - 1) + lane] = mine;
+        }
+        const int32_t i0 = s & ~(kWave - 1);  // entries [i0, s] are still in the lanes, unless they fill them
+        if ((s & (kWave - 1)) != kWave - 1 && lane <= s - i0) path[i0 + lane] = mine;
+        for (int64_t q = (int64_t)s + 1 + lane; q < L1; q += kWave) path[q] = -1;
+        if (lane == 0 && s) atomicAdd(wc.steps, (unsigned long long)s);
     }
 }
 
@@ -1077,18 +1097,35 @@ __global__ void __launch_bounds__(kBlock) k_symmetric_check(RowPtr rowptr, const
 }
 
 // Walk guide tables, one wavefront per list with a positive total: the inclusive prefix of every edge (64 at a time, one
-// scan each, carried), and for each bucket k < K of the list's guide the
-// position i whose interval [S_i, S_(i+1)) holds k * 2^s. Edge i covers the
-// buckets from ceil(S_i / 2^s) to ceil(S_(i+1) / 2^s) - 1 (none for a zero
-// weight), so every bucket is written once. A lane writes up to
+// scan each, carried), and the buckets of the list's guide. The edge whose
+// interval holds a bucket's start writes it: edge i those from
+// ceil(S_i / 2^s) to ceil(S_(i+1) / 2^s) - 1 (none for a zero
+// weight), so every bucket is written once; the second position of a bucket is
+// the next edge, if its interval reaches the bucket's end. A lane writes up to
 // kGuideLaneFill buckets itself; an edge heavier than that many buckets is
 // written by the whole wavefront, 64 buckets at a time.
 constexpr uint64_t kGuideLaneFill = 8;
+
+// Bucket k of a list of total W: position i holds its start and ends at S1, the
+// next position at S2.
+__device__ __forceinline__ WalkBucket guide_bucket(uint64_t k, int sh, uint64_t W, uint64_t S1, uint64_t S2, uint32_t i,
+                                                   int32_t y, int32_t y1) {
+    const uint64_t start = k << sh, full = start + (uint64_t(1) << sh), end = full < W ? full : W;
+    uint32_t bound = ~0u, second = ~0u;  // (searched in the edge records)
+    if (S1 >= end) {
+        second = 0u;  // one position: the bound is never reached
+    } else if (S2 >= end) {
+        bound = (uint32_t)(S1 - start);
+        second = (uint32_t)y1;
+    }
+    return WalkBucket{(uint64_t)bound | ((uint64_t)second << 32), i, y};
+}
+
 __global__ void __launch_bounds__(kBlock) k_walk_guides(RowPtr rowptr, const int32_t* __restrict__ col,
                                                         const uint32_t* __restrict__ w,
                                                         const uint64_t* __restrict__ wtot, int64_t n,
                                                         WalkEdge* __restrict__ rec, WalkVertex* __restrict__ vtx,
-                                                        WalkBucket* __restrict__ gd) {
+                                                        WalkBucket* __restrict__ gd, int per) {
     const int lane = lane_id();
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
     for (int64_t v = blockIdx.x * (int64_t)kWavesPerBlock + threadIdx.x / kWave; v < n; v += waves) {
@@ -1097,15 +1134,17 @@ __global__ void __launch_bounds__(kBlock) k_walk_guides(RowPtr rowptr, const int
         const uint64_t W = ld_uniform(wtot + v);
         if (vtx && lane == 0) vtx[v] = WalkVertex{W, (uint32_t)b, (uint32_t)d};
         if (W == 0) continue;
-        const int sh = guide_shift(W, d);
+        const int sh = guide_shift(W, d, per);
         const uint64_t K = ((W - 1) >> sh) + 1;
         const uint64_t low = (uint64_t(1) << sh) - 1;
-        WalkBucket* G = gd + guide_base(b, v);
+        WalkBucket* G = gd + guide_base(b, v, per);
         uint64_t run = 0;
         for (int64_t base = 0; base < d; base += kWave) {
             const int64_t i = base + lane;
             const uint64_t x = i < d ? (uint64_t)w[b + i] : 0ull;
             const int32_t y = i < d ? col[b + i] : 0;
+            const uint64_t x1 = i + 1 < d ? (uint64_t)w[b + i + 1] : 0ull;  // the next edge
+            const int32_t y1 = i + 1 < d ? col[b + i + 1] : 0;
             const uint64_t incl = run + wave_incl_scan_u64(x);
             const uint64_t excl = incl - x;
             const uint64_t k0 = (excl >> sh) + ((excl & low) != 0);
@@ -1115,13 +1154,15 @@ __global__ void __launch_bounds__(kBlock) k_walk_guides(RowPtr rowptr, const int
             if (i < d) {
                 rec[b + i] = WalkEdge{incl, y, (uint32_t)x};
                 if (nk <= kGuideLaneFill)
-                    for (uint64_t k = k0; k < k1; ++k) G[k] = WalkBucket{incl, (uint32_t)i, y};
+                    for (uint64_t k = k0; k < k1; ++k) G[k] = guide_bucket(k, sh, W, incl, incl + x1, (uint32_t)i, y, y1);
             }
             for (uint64_t wide = ballot(nk > kGuideLaneFill); wide; wide &= wide - 1) {
                 const int src = __ffsll((unsigned long long)wide) - 1;
                 const uint64_t a0 = readlane_u64(k0, src), a1 = readlane_u64(k1, src);
-                const WalkBucket e{readlane_u64(incl, src), (uint32_t)(base + src), readlane_i32(y, src)};
-                for (uint64_t k = a0 + lane; k < a1; k += kWave) G[k] = e;
+                const uint64_t si = readlane_u64(incl, src), sx = readlane_u64(x1, src);
+                const int32_t sy = readlane_i32(y, src), sy1 = readlane_i32(y1, src);
+                for (uint64_t k = a0 + lane; k < a1; k += kWave)
+                    G[k] = guide_bucket(k, sh, W, si, si + sx, (uint32_t)(base + src), sy, sy1);
             }
             run = readlane_u64(incl, kWave - 1);
         }
@@ -1139,10 +1180,15 @@ void launch_walk_hops(RowPtr rowptr, const int32_t* col, int64_t m, WalkHop* hop
 
 void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, const uint64_t* wtot, int64_t n,
                         WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, hipStream_t s) {
+    launch_walk_guides(rowptr, col, w, wtot, n, rec, vtx, gd, kGuideBucketsPerEdge, s);
+}
+
+void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, const uint64_t* wtot, int64_t n,
+                        WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, int per, hipStream_t s) {
     if (n <= 0) return;
     int64_t g = (n + kWavesPerBlock - 1) / kWavesPerBlock;
     if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_walk_guides, dim3((unsigned)g), dim3(kBlock), 0, s, rowptr, col, w, wtot, n, rec, vtx, gd);
+    hipLaunchKernelGGL(k_walk_guides, dim3((unsigned)g), dim3(kBlock), 0, s, rowptr, col, w, wtot, n, rec, vtx, gd, per);
 }
 
 void launch_symmetric_check(RowPtr rowptr, const int32_t* col, int64_t n, int32_t* flag, hipStream_t s) {
@@ -1172,8 +1218,12 @@ void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev) 
             else launch_kernel(k_walk_wave_n2v<false>, dim3((unsigned)g), dim3(kBlock), s, ev, p);
         } else {
             const bool dg = p.bias == kNeighborDegree;
-            if ((dg ? p.g.wgd_deg : p.g.wgd_ew) && (dg ? p.g.wrec_deg : p.g.wrec_ew) &&
-                (dg ? p.g.wvtx_deg : p.g.wvtx_ew) && p.num_walkers >= kLaneWalkMin) {
+            const bool guide = (dg ? p.g.wgd_deg : p.g.wgd_ew) && (dg ? p.g.wrec_deg : p.g.wrec_ew) &&
+                               (dg ? p.g.wvtx_deg : p.g.wvtx_ew);
+            if (guide && p.num_walkers < kLaneWalkMin) {
+                launch_kernel(moves ? k_walk_wave_guide<true> : k_walk_wave_guide<false>, dim3((unsigned)g), dim3(kBlock), s,
+                              ev, p);
+            } else if (guide) {
                 int64_t gl = (p.num_walkers + kBlock - 1) / kBlock;
                 if (gl > grid) gl = grid;
                 if (moves) launch_kernel(k_walk_lane<true>, dim3((unsigned)gl), dim3(kBlock), s, ev, p);
