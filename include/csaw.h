@@ -76,7 +76,10 @@ typedef enum {
  *                    vertex, w_common if it is adjacent to the previous
  *                    vertex, w_outward otherwise (node2vec's second-order
  *                    bias, Section II-A); the first step is unbiased.
- *                    Requires sorted adjacency lists.                      */
+ *                    Requires sorted adjacency lists. The graph's first such
+ *                    csaw_walk builds a rank index of the lists (2 bytes per
+ *                    edge, 4 per vertex) where half of the free device memory
+ *                    holds it; without it steps merge lists, to the same picks. */
 typedef enum {
     CSAW_BIAS_UNIFORM = 0,
     CSAW_BIAS_EDGE_WEIGHT = 1,

@@ -111,6 +111,11 @@ struct GraphDev {
     const WalkBucket* wgd_deg;
     int32_t gper_ew = kGuideBucketsPerEdge, gper_deg = kGuideBucketsPerEdge;  // buckets per edge, per weight array
     const WalkHop* hops = nullptr;  // m, or null
+    // rank index of the sorted lists (null until the first node2vec walk):
+    // list v starting at edge b owns rank[rank_base(b, v) + k], k <= K
+    // (rank_log): the number of its entries below k << rank_shift
+    const uint32_t* rank = nullptr;
+    int32_t repeats = 0;            // some list holds a neighbor more than once (set with rank)
 };
 
 constexpr int kWaveMaxD = 512;   // longest weighted list of the wavefront kernels
@@ -315,10 +320,25 @@ void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, co
                         WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, hipStream_t s);
 // The hop table of a graph (weak: see free_device_bytes).
 __attribute__((weak)) void launch_walk_hops(RowPtr rowptr, const int32_t* col, int64_t m, WalkHop* hops, hipStream_t s);
+// The rank index of a graph's sorted lists; *repeats becomes 1 where a list holds
+// a neighbor twice (weak: see free_device_bytes).
+__attribute__((weak)) void launch_walk_ranks(RowPtr rowptr, const int32_t* col, int64_t n, uint32_t* rank,
+                                             int32_t* repeats, hipStream_t s);
 // The same with at most per d buckets (weak: see free_device_bytes).
 __attribute__((weak)) void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w,
                                               const uint64_t* wtot, int64_t n, WalkEdge* rec, WalkVertex* vtx,
                                               WalkBucket* gd, int per, hipStream_t s);
+
+// Rank index of a list of d >= kRankMinD entries: K = 2^rank_log <= d / 2 equal
+// ranges of ids over [0, 2^(bit length of n - 1)), 4 bytes each: m / 2 + n
+// words at most. Shared by the table builder and the kernels.
+constexpr int64_t kRankMinD = 64;
+__host__ __device__ __forceinline__ int rank_log(int64_t d) { return d > 1 ? 62 - __builtin_clzll((uint64_t)d) : 0; }
+__host__ __device__ __forceinline__ int rank_shift(int64_t n, int64_t d) {
+    const int bits = n > 1 ? 64 - __builtin_clzll((uint64_t)(n - 1)) : 0;
+    return bits > rank_log(d) ? bits - rank_log(d) : 0;
+}
+__host__ __device__ __forceinline__ int64_t rank_base(int64_t b, int64_t v) { return b / 2 + v; }
 
 // Buckets of a list's walk guide: width 2^s, K = ((W - 1) >> s) + 1 of them,
 // s the smallest shift that keeps K within per * d (d >= 1, W > 0). A draw r

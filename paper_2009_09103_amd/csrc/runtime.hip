@@ -237,6 +237,8 @@ struct csaw_graph_s {
     WalkBucket* wgd_deg = nullptr;
     int32_t gper_ew = kGuideBucketsPerEdge, gper_deg = kGuideBucketsPerEdge;
     WalkHop* hops = nullptr;       // hop table of unbiased steps
+    uint32_t* rank = nullptr;      // rank index of the lists (node2vec)
+    int32_t repeats = 0;           // some list holds a neighbor more than once (known with rank)
     mutable std::mutex mu;               // lazy preparation + workspace pool
     std::vector<Workspace*> pool;
     std::atomic<int32_t> bound16{kDefaultBound16}, bound32{kDefaultBound32};  // sub-wave buckets
@@ -270,6 +272,8 @@ struct csaw_graph_s {
         g.gper_ew = gper_ew;
         g.gper_deg = gper_deg;
         g.hops = hops;
+        g.rank = rank;
+        g.repeats = repeats;
         if (!walk_guides.load()) {  // walks and long-list draws take the chunk tables
             g.wrec_ew = g.wrec_deg = nullptr;
             g.wvtx_ew = g.wvtx_deg = nullptr;
@@ -493,6 +497,35 @@ void prepare_hops(csaw_graph g, int64_t steps, int64_t weight, hipStream_t s) {
         return;
     }
     g->hops = hops;
+}
+
+// The rank index (2 bytes per edge, 4 per vertex), built by a graph's first
+// node2vec walk where it takes at most half of the free device memory (one
+// pass over the column ids, 3.2 ms on 500M edges; that first walk has just
+// looked up the reverse of every edge, 85 ms); without it node2vec steps merge the two
+// lists.
+void prepare_ranks(csaw_graph g, hipStream_t s) {
+    if (!launch_walk_ranks || !free_device_bytes || g->m <= 0 || !g->col || g->max_deg >= (int64_t(1) << 30)) return;
+    std::lock_guard<std::mutex> lk(g->mu);
+    const size_t bytes = (size_t)(rank_base(g->m, g->n) + 1) * sizeof(uint32_t);
+    if (g->rank || bytes > free_device_bytes() / 2) return;
+    uint32_t* rank = nullptr;
+    if (hipMalloc((void**)&rank, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    int32_t h = 0;
+    bool ok = hipMemsetAsync(g->dflag, 0, sizeof(int32_t), s) == hipSuccess;
+    if (ok) launch_walk_ranks(g->rowptr, g->col, g->n, rank, g->dflag, s);
+    ok = ok && hipGetLastError() == hipSuccess &&
+         hipMemcpyAsync(&h, g->dflag, sizeof(int32_t), hipMemcpyDeviceToHost, s) == hipSuccess;
+    ok = hipStreamSynchronize(s) == hipSuccess && ok;
+    if (!ok) {
+        (void)hipFree(rank);
+        return;
+    }
+    g->repeats = h;
+    g->rank = rank;
 }
 
 int64_t sat_mul(int64_t a, int64_t b) {
@@ -775,7 +808,7 @@ csaw_status csaw_graph_destroy(csaw_graph g) {
     if (g->ctab_ew) (void)hipFree(g->ctab_ew);
     if (g->ctab_deg) (void)hipFree(g->ctab_deg);
     for (void* q : {(void*)g->wrec_ew, (void*)g->wrec_deg, (void*)g->wvtx_ew, (void*)g->wvtx_deg, (void*)g->wgd_ew,
-                    (void*)g->wgd_deg, (void*)g->hops})
+                    (void*)g->wgd_deg, (void*)g->hops, (void*)g->rank})
         if (q) (void)hipFree(q);
     delete g;
     return CSAW_OK;
@@ -1644,6 +1677,9 @@ static csaw_status walk_call(csaw_graph g, const csaw_walk_args* a, int32_t* pat
     if (a->num_walkers == 0) return CSAW_OK;
     if (!scratch && (a->bias_kind == kUniform || a->bias_kind == kMetropolis))
         prepare_hops(g, sat_mul(a->num_walkers, a->length), 1, s);
+    if (!scratch && a->bias_kind == kNode2vec && a->length > 1 &&
+        (a->w_return != a->w_common || a->w_common != a->w_outward))
+        prepare_ranks(g, s);
     Lease rel{g, nullptr, s};
     char* dev = scratch;
     char* host = nullptr;

@@ -15,8 +15,10 @@
 //     biases of N(v) into a coarse prefix table in LDS, r is drawn in [0, W),
 //     and pass 2 rescans only the group of the table that holds r.
 //   - node2vec: the bias of x in N(v) needs "is x adjacent to the previous
-//     vertex t"; adjacency lists are sorted, so N(v) is merged with N(t)
-//     (or, for a much longer N(t), each candidate binary-searches it).
+//     vertex t"; adjacency lists are sorted, so the shorter of N(v) and N(t)
+//     is looked up in the longer one through the graph's rank index, or, where
+//     the graph has none, N(v) is merged with N(t) (or, for a much longer N(t), each
+//     candidate binary-searches it).
 #include "device_common.h"
 #include "kernels.h"
 
@@ -1080,6 +1082,449 @@ __global__ void __launch_bounds__(kBlock) k_walk_wave_guide(WalkParams p) {
     }
 }
 
+// node2vec through the rank index. A step needs, of the common neighbors of v
+// and the previous vertex t, how many there are and where those up to the
+// pick stand in N(v). The entries of the shorter list are looked up in the longer
+// one (on R-MAT 24 a step's lists have 900 and 8,500 entries on average), where
+// a merge reads both. With C(j) = common candidates below position j of
+// N(v) and T(j) = copies of t below j, the exclusive prefix is
+// S(j) = w_out (j - C - T) + w_common C + w_return T, and S fixes the pick without
+// another pass: the last common candidate that begins at or below the draw gives C, the
+// rest is a division.
+// 65,536 walkers of length 80 on 500M edges: 95.4 ms merging, 34 with every
+// entry looked up in memory where the longer list has 3 times the entries and a merge elsewhere,
+// 31 with every entry looked up, 28 with the dense stretches staged in LDS,
+// 25.0 with the next chunks' loads issued a block ahead, 24.3 at six waves per
+// SIMD (five or seven: 25.1, 25.3). The vector unit is then busy 45% of the
+// time, the address units 54%, and 87 GB come from beyond the L2s (3.6 TB/s).
+constexpr int kRankQ = 4;                        // chunks of 64 entries looked up together
+constexpr uint32_t kRankWin = 256 * kRankQ;      // entries of the longer list staged for them
+struct RankStep {
+    const int32_t* sh;     // the shorter list
+    uint32_t ns;
+    const int32_t* lg;     // the longer one
+    uint32_t nl, lg_at;    // its entries; its first edge (low bits)
+    const uint32_t* rank;  // its rank index (nl >= kRankMinD)
+    int bits;              // the index's shift
+    bool of_t;             // the shorter list is N(t)
+    int32_t t;
+    int32_t* win;          // LDS, kRankWin entries
+};
+struct alignas(4) RankPair {
+    uint32_t lo, hi;
+};
+struct alignas(16) RankQuad {
+    int32_t e[4];
+};
+
+// Entry i of a list: 32-bit byte offsets (lists are shorter than 2^30).
+__device__ __forceinline__ int32_t list_at(const int32_t* list, uint32_t i) {
+    return *(const int32_t*)((const char*)list + (i << 2));
+}
+
+// The stretch of the longer list that ids x0 to x1 span, from the index.
+__device__ __forceinline__ void rank_span(const RankStep& st, int32_t x0, int32_t x1, uint32_t& lo, uint32_t& len) {
+    lo = 0;
+    len = st.nl;
+    if (st.nl >= kRankMinD) {
+        lo = ld_uniform(st.rank + ((uint32_t)x0 >> st.bits));
+        len = ld_uniform(st.rank + (((uint32_t)x1 >> st.bits) + 1)) - lo;
+    }
+}
+
+// Where n entries x of the shorter list (an entry a lane, Q chunks) stand in the
+// longer one, and whether they are in it (a copy, if it is repeated); they span its
+// entries [lo, lo + len). Where that is up to four times as many as they are, the
+// stretch is staged in LDS and searched there: each line is read once (up to
+// twice as many: 28.1 against 25.0 ms, eight times: the 8 KB a wave that needs cost more
+// than it gave). Otherwise every entry has its own range from the index, which
+// in lists of 10,000 leaves four to five of 13 halvings, Q loads in flight.
+// ahead() issues the loads of the chunks that follow.
+template <int Q, typename Ahead>
+__device__ __forceinline__ void rank_find(const RankStep& st, uint32_t n, const int32_t (&x)[Q], uint32_t lo, uint32_t len,
+                                          uint32_t (&pos)[Q], bool (&hit)[Q], const Ahead& ahead) {
+    const uint32_t lane = lane_id();
+    if (len <= 256 * Q - 4) {
+        // whole 16-byte quads; what lies outside the stretch becomes -1 and the largest int
+        const uint32_t skew = (st.lg_at + lo) & 3u, top = skew + len;
+        const int32_t* from = st.lg + (int64_t)lo - skew;
+        const int log = top < 256 ? 8 : 32 - __builtin_clz(top);  // 2^log > top
+        RankQuad y[Q];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            const uint32_t i = (k * kWave + lane) * 4;
+            if (k * 256u < top) y[k] = *(const RankQuad*)((const char*)from + ((i < top ? i : 0u) << 2));
+        }
+        ahead();
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            if (k * 256u < (1u << log)) {
+                const uint32_t i = (k * kWave + lane) * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) y[k].e[j] = i + j >= top ? INT32_MAX : (i + j < skew ? -1 : y[k].e[j]);
+                *(RankQuad*)(st.win + i) = y[k];
+            }
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) pos[q] = 0;
+        for (uint32_t step = 1u << (log - 1); step; step >>= 1) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) pos[q] += st.win[pos[q] + step - 1] < x[q] ? step : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            hit[q] = q * kWave + lane < n && st.win[pos[q]] == x[q];
+            pos[q] += lo - skew;
+        }
+        wave_lds_sync();
+        return;
+    }
+    ahead();
+    uint32_t hi[Q];
+    RankPair r[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) r[q] = *(const RankPair*)((const char*)st.rank + (((uint32_t)x[q] >> st.bits) << 2));
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        pos[q] = r[q].lo;
+        hi[q] = q * kWave + lane < n ? r[q].hi : r[q].lo;
+        hit[q] = false;
+    }
+    while (true) {
+        bool more = false;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) more |= pos[q] < hi[q];
+        if (ballot(more) == 0) break;
+        uint32_t mid[Q];
+        int32_t y[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            mid[q] = pos[q] < hi[q] ? (pos[q] + hi[q]) >> 1 : 0u;
+            y[q] = list_at(st.lg, mid[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const bool open = pos[q] < hi[q], eq = open && y[q] == x[q], lt = y[q] < x[q];
+            hit[q] |= eq;
+            hi[q] = open && !lt ? mid[q] : hi[q];
+            pos[q] = eq ? mid[q] : (open && lt ? mid[q] + 1 : pos[q]);
+        }
+    }
+}
+
+// The copies of x around position pos of the longer list (one of them): pos
+// becomes the first.
+__device__ __forceinline__ uint32_t rank_run(const RankStep& st, int32_t x, uint32_t& pos) {
+    uint32_t lo = 0, hi = pos, lo2 = pos + 1, hi2 = st.nl;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (list_at(st.lg, mid) < x) lo = mid + 1;
+        else hi = mid;
+    }
+    while (lo2 < hi2) {
+        const uint32_t mid = (lo2 + hi2) >> 1;
+        if (list_at(st.lg, mid) <= x) lo2 = mid + 1;
+        else hi2 = mid;
+    }
+    pos = lo;
+    return lo2 - lo;
+}
+
+// The copies of t in the longer list, N(v), by the whole wavefront: one load
+// where its range has at most 64 entries, else one more for each 64-fold.
+template <bool kRepeats>
+__device__ __forceinline__ void rank_find_t(const RankStep& st, uint32_t& pos_t, uint32_t& n_t) {
+    const uint32_t lane = lane_id();
+    uint32_t lo = 0, hi = st.nl;
+    if (st.nl >= kRankMinD) {
+        const uint32_t k = (uint32_t)st.t >> st.bits;
+        lo = ld_uniform(st.rank + k);
+        hi = ld_uniform(st.rank + (k + 1));
+    }
+    while (hi - lo > (uint32_t)kWave) {  // the first entry >= t lies in [lo, hi]
+        const uint32_t seg = (hi - lo + kWave - 1) / kWave, i = lo + lane * seg;
+        const uint32_t below = (uint32_t)__popcll(ballot(i < hi && list_at(st.lg, i < hi ? i : lo) < st.t));
+        if (below == 0) {
+            hi = lo + 1;
+        } else {
+            hi = lo + below * seg + 1 < hi ? lo + below * seg + 1 : hi;
+            lo += (below - 1) * seg + 1;
+        }
+    }
+    const uint32_t i = lo + lane;
+    const int32_t y = i < hi ? list_at(st.lg, i) : INT32_MAX;
+    pos_t = lo + (uint32_t)__popcll(ballot(y < st.t));
+    n_t = (uint32_t)__popcll(ballot(y == st.t));
+    if (kRepeats && n_t) {
+        n_t = rank_run(st, st.t, pos_t);
+        pos_t = (uint32_t)uniform_i32((int32_t)pos_t);
+        n_t = (uint32_t)uniform_i32((int32_t)n_t);
+    }
+}
+
+// Q chunks of the shorter list from entry base on, an entry a lane.
+template <int Q>
+__device__ __forceinline__ uint32_t rank_load(const RankStep& st, uint32_t base, int32_t (&x)[Q]) {
+    const uint32_t lane = lane_id();
+    const uint32_t n = st.ns - base < (uint32_t)(Q * kWave) ? st.ns - base : (uint32_t)(Q * kWave);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t i = q * kWave + lane;
+        x[q] = list_at(st.sh, base + (i < n ? i : 0u));
+    }
+    return n;
+}
+
+// Their positions in N(v), and cnt[q] = common candidates there (t itself is
+// none), from their places in the longer list. Where the shorter list is N(v), adds to the copies
+// of t and sets the first one's position.
+template <bool kRepeats, int Q>
+__device__ __forceinline__ void rank_count(const RankStep& st, uint32_t base, const int32_t (&x)[Q], const bool (&hit)[Q],
+                                           uint32_t (&pos)[Q], uint32_t (&cnt)[Q], uint32_t& pos_t, uint32_t& n_t) {
+    const uint32_t lane = lane_id();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t i = base + q * kWave + lane;
+        cnt[q] = hit[q] && x[q] != st.t ? 1u : 0u;
+        if (!st.of_t) {
+            pos[q] = i;
+            const uint64_t at_t = ballot(i < st.ns && x[q] == st.t);
+            if (at_t) {
+                if (n_t == 0) pos_t = base + q * kWave + __ffsll((unsigned long long)at_t) - 1;
+                n_t += (uint32_t)__popcll(at_t);
+            }
+        } else if (kRepeats) {
+            uint32_t run = 0;
+            if (hit[q]) run = rank_run(st, x[q], pos[q]);
+            const bool again = i > 0 && i < st.ns && list_at(st.sh, i - 1) == x[q];  // counted at its first copy
+            cnt[q] = again || x[q] == st.t ? 0u : run;
+            if (again) pos[q] += run;
+        }
+    }
+}
+
+// One chunk, its loads one after the other.
+template <bool kRepeats>
+__device__ __forceinline__ void rank_chunk(const RankStep& st, uint32_t base, uint32_t& pos, uint32_t& cnt, uint32_t& pos_t,
+                                           uint32_t& n_t) {
+    int32_t x[1];
+    uint32_t at[1], c[1], lo, len;
+    bool hit[1];
+    const uint32_t n = rank_load(st, base, x);
+    rank_span(st, ld_uniform(st.sh + base), ld_uniform(st.sh + (base + n - 1)), lo, len);
+    rank_find(st, n, x, lo, len, at, hit, [] {});
+    rank_count<kRepeats>(st, base, x, hit, at, c, pos_t, n_t);
+    pos = at[0];
+    cnt = c[0];
+}
+
+// floor(a / w) where it is below 2^30: inv = 1 / w in double gives it to within one.
+__device__ __forceinline__ uint32_t small_quotient(uint64_t a, uint32_t w, double inv) {
+    uint32_t q = (uint32_t)((double)a * inv);
+    if ((uint64_t)q * w > a) --q;
+    else if ((uint64_t)(q + 1) * w <= a) ++q;
+    return q;
+}
+
+// Lane k keeps the first position of chunk k << g and the common candidates
+// before it (g > 0 above 4,096 entries), so one chunk in 64 is looked
+// up again to find the pick, or none if it is among the last ones looked up.
+template <bool kRepeats>
+__device__ __forceinline__ uint32_t walk_step_rank(const WalkParams& p, const RankStep& st, uint64_t u, uint32_t d,
+                                                   const double (&inv)[3], bool& stop) {
+    const int lane = lane_id();
+    const uint32_t chunks = (st.ns + kWave - 1) / kWave;
+    int g = 0;
+    while (chunks > (uint32_t)kWave << g) ++g;
+    const uint32_t low = (1u << g) - 1;
+    uint32_t pos_t = 0, n_t = 0, c = 0;
+    uint32_t at_pos = 0, at_c = 0;
+    if (st.of_t) rank_find_t<kRepeats>(st, pos_t, n_t);
+    // chunk k is done: its table entry, its common candidates
+    const auto take = [&](uint32_t k, uint32_t pos, uint32_t cnt) {
+        if ((k & low) == 0) {
+            const uint32_t first = readlane_u32(pos, 0);
+            if (lane == (int)(k >> g)) {
+                at_pos = first;
+                at_c = c;
+            }
+        }
+        c += kRepeats ? (uint32_t)readlane_u32(wave_incl_scan_u32(cnt), kWave - 1)
+                        : (uint32_t)__popcll(ballot(cnt != 0));
+    };
+    uint32_t pos[kRankQ], cnt[kRankQ];  // of the last chunks looked up, from chunk kept on
+    uint32_t kept = 0, k = 0;
+    if (chunks > 1) {
+        int32_t xn[kRankQ];
+        uint32_t lo, len, n = rank_load(st, 0, xn);
+        rank_span(st, ld_uniform(st.sh), ld_uniform(st.sh + (n - 1)), lo, len);
+        const auto first = [&](uint32_t at) { return ld_uniform(st.sh + (at < st.ns ? at : st.ns - 1)); };
+        int32_t x0 = first(kRankQ * kWave), x1 = first(2 * kRankQ * kWave - 1);
+        for (; k + 1 < chunks; k += kRankQ) {
+            int32_t x[kRankQ];
+            bool hit[kRankQ];
+#pragma unroll
+            for (int q = 0; q < kRankQ; ++q) x[q] = xn[q];
+            const uint32_t base = k * kWave, m = n, lo1 = lo, len1 = len;
+            rank_find(st, m, x, lo1, len1, pos, hit, [&] {
+                if (k + kRankQ + 1 < chunks) {
+                    n = rank_load(st, base + kRankQ * kWave, xn);
+                    rank_span(st, x0, x1, lo, len);
+                    x0 = first(base + 2 * kRankQ * kWave);
+                    x1 = first(base + 3 * kRankQ * kWave - 1);
+                }
+            });
+            rank_count<kRepeats>(st, base, x, hit, pos, cnt, pos_t, n_t);
+#pragma unroll
+            for (int q = 0; q < kRankQ; ++q)
+                if (k + q < chunks) take(k + q, pos[q], cnt[q]);
+            kept = k;
+        }
+    }
+    if (k < chunks) {
+        rank_chunk<kRepeats>(st, k * kWave, pos[0], cnt[0], pos_t, n_t);
+        take(k, pos[0], cnt[0]);
+        kept = k;
+    }
+    const uint32_t wo = p.w_outward, wc = p.w_common, wr = p.w_return;
+    const uint64_t W = (uint64_t)wo * (d - c - n_t) + (uint64_t)wc * c + (uint64_t)wr * n_t;
+    stop = W == 0;
+    if (stop) return 0;
+    const uint64_t r = range_reduce(u, W);
+    const auto prefix = [&](uint32_t j, uint32_t C) {
+        const uint32_t T = j <= pos_t ? 0u : (j - pos_t < n_t ? j - pos_t : n_t);
+        return (uint64_t)wo * (j - C - T) + (uint64_t)wc * C + (uint64_t)wr * T;
+    };
+    const int sel = __popcll(ballot((uint32_t)lane << g < chunks && prefix(at_pos, at_c) <= r)) - 1;
+    uint32_t j0 = 0, C0 = 0;  // C0 common candidates below j0, none from there to the pick
+    if (sel >= 0) {
+        j0 = readlane_u32(at_pos, sel);
+        uint32_t C = C0 = readlane_u32(at_c, sel);
+        const uint32_t end = ((uint32_t)sel + 1) << g;
+        for (uint32_t k1 = (uint32_t)sel << g; k1 < end && k1 < chunks; ++k1) {
+            uint32_t pos1 = pos[0], cnt1 = cnt[0];
+            if (k1 < kept) {
+                uint32_t unused_p = 0, unused_n = 1;
+                rank_chunk<kRepeats>(st, k1 * kWave, pos1, cnt1, unused_p, unused_n);
+            } else {
+#pragma unroll
+                for (int q = 1; q < kRankQ; ++q)
+                    if (k1 == kept + q) {
+                        pos1 = pos[q];
+                        cnt1 = cnt[q];
+                    }
+            }
+            const uint64_t one = ballot(cnt1 != 0);
+            if (one == 0) continue;
+            uint32_t before, all;  // common candidates before this lane's; all of them
+            if (kRepeats) {
+                const uint32_t incl = wave_incl_scan_u32(cnt1);
+                before = C + incl - cnt1;
+                all = readlane_u32(incl, kWave - 1);
+            } else {
+                before = C + (uint32_t)__popcll(one & ((1ull << lane) - 1));
+                all = (uint32_t)__popcll(one);
+            }
+            const uint64_t below = ballot(cnt1 != 0 && prefix(pos1, before) <= r);
+            if (below) {
+                const int i = 63 - __builtin_clzll(below);
+                const uint32_t ji = readlane_u32(pos1, i), ni = readlane_u32(cnt1, i), Ci = readlane_u32(before, i);
+                const uint64_t Si = prefix(ji, Ci);
+                if (r < Si + (uint64_t)wc * ni) return ji + small_quotient(r - Si, wc, inv[1]);
+                j0 = ji + ni;
+                C0 = Ci + ni;
+            }
+            if (below != one) break;
+            C += all;
+        }
+    }
+    uint64_t rem = r - prefix(j0, C0);
+    if (n_t && pos_t >= j0) {
+        const uint64_t gap = (uint64_t)wo * (pos_t - j0), run = (uint64_t)wr * n_t;
+        if (rem >= gap) {
+            rem -= gap;
+            if (rem < run) return pos_t + small_quotient(rem, wr, inv[2]);
+            rem -= run;
+            j0 = pos_t + n_t;
+        }
+    }
+    return j0 + small_quotient(rem, wo, inv[0]);
+}
+
+template <bool kMoves, bool kRepeats>
+__global__ void __launch_bounds__(kBlock, 6) k_walk_n2v_rank(WalkParams p) {
+    __shared__ __align__(16) int32_t win[kWavesPerBlock][kRankWin];
+    const int lane = lane_id();
+    const double inv[3] = {1.0 / p.w_outward, 1.0 / p.w_common, 1.0 / p.w_return};
+    const int wid = uniform_i32(threadIdx.x / kWave);
+    const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+    for (int64_t w = blockIdx.x * (int64_t)kWavesPerBlock + wid; w < p.num_walkers; w += waves) {
+        const WalkerCtx wc = walker_ctx(p, w);
+        const Key key{(uint32_t)uniform_i32((int32_t)wc.key.k0), (uint32_t)uniform_i32((int32_t)wc.key.k1)};
+        const int32_t length = uniform_i32(wc.length);
+        const int64_t L1 = (int64_t)length + 1;
+        int32_t* path = wc.path;
+        int32_t v = uniform_i32(p.starts[w]);
+        if (v < 0 || (int64_t)v >= p.g.n) {
+            if (lane == 0) *p.bad_start = 1;
+            for (int64_t q = lane; q < L1; q += kWave) path[q] = -1;
+            continue;
+        }
+        const uint32_t c0 = (uint32_t)uniform_i32((int32_t)wc.c0);
+        const int32_t start = v;
+        int32_t mine = v;  // path entry i is kept by lane i % 64
+        int32_t t = -1;
+        int64_t tb = 0;
+        uint32_t dt = 0;
+        int32_t s = 0;
+        for (; s < length; ++s) {
+            int32_t to;
+            if (kMoves && walk_move(p, key, c0, s, v, start, to)) {  // uniform: the draw depends on wave-uniform values
+                v = uniform_i32(to);
+                t = -1;
+            } else {
+                int64_t beg, d64;
+                row_uniform(p.g.rowptr, v, beg, d64);
+                const uint64_t u = philox_vec(key, c0, (uint32_t)s, (uint32_t)v, 0u);
+                const uint32_t d = (uint32_t)d64;
+                if (d == 0) break;
+                uint32_t m;
+                if (t < 0) {  // no previous vertex: every bias is 1
+                    m = (uint32_t)range_reduce(u, (uint64_t)d);
+                } else {
+                    RankStep st;
+                    st.of_t = d > dt;
+                    st.sh = p.g.col + (st.of_t ? tb : beg);
+                    st.ns = st.of_t ? dt : d;
+                    const int64_t lb = st.of_t ? beg : tb;
+                    st.lg = p.g.col + lb;
+                    st.lg_at = (uint32_t)lb;
+                    st.nl = st.of_t ? d : dt;
+                    st.rank = p.g.rank + rank_base(lb, st.of_t ? v : t);
+                    st.bits = rank_shift(p.g.n, st.nl);
+                    st.t = t;
+                    st.win = win[wid];
+                    bool stop;
+                    m = walk_step_rank<kRepeats>(p, st, u, d, inv, stop);
+                    if (stop) break;
+                }
+                t = v;
+                tb = beg;
+                dt = d;
+                v = ld_uniform(p.g.col + beg + uniform_i32((int32_t)m));
+            }
+            const int32_t i = s + 1;
+            if (lane == (i & (kWave - 1))) mine = v;
+            if ((i & (kWave - 1)) == kWave - 1) path[i - (kWave - 1) + lane] = mine;
+        }
+        const int32_t i0 = s & ~(kWave - 1);  // entries [i0, s] are still in the lanes, unless they fill them
+        if ((s & (kWave - 1)) != kWave - 1 && lane <= s - i0) path[i0 + lane] = mine;
+        for (int64_t q = (int64_t)s + 1 + lane; q < L1; q += kWave) path[q] = -1;
+        if (lane == 0 && s) atomicAdd(wc.steps, (unsigned long long)s);
+    }
+}
+
 // One wavefront per vertex u, a lane per edge (u, x): is u in the sorted N(x)?
 __global__ void __launch_bounds__(kBlock) k_symmetric_check(RowPtr rowptr, const int32_t* __restrict__ col,
                                                             int64_t n, int32_t* __restrict__ flag) {
@@ -1094,6 +1539,54 @@ __global__ void __launch_bounds__(kBlock) k_symmetric_check(RowPtr rowptr, const
         }
         if (ballot(missing) && lane == 0) atomicOr(flag, 1);
     }
+}
+
+// Rank index, one wavefront per list of at least kRankMinD entries: entry i
+// writes its position at the ranges that begin above entry i - 1 and not above
+// entry i, the last one also the length at those behind it. Entries are taken
+// kRankPer a lane, so that long lists have several loads in flight; wide gaps
+// are written by the whole wavefront. Every list is looked over for repeated entries.
+constexpr int kRankPer = 4;
+constexpr uint32_t kRankLaneFill = 16;
+__global__ void __launch_bounds__(kBlock) k_walk_ranks(RowPtr rowptr, const int32_t* __restrict__ col, int64_t n,
+                                                       uint32_t* __restrict__ rank, int32_t* __restrict__ repeats) {
+    const int lane = lane_id();
+    const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+    bool twice = false;
+    for (int64_t v = blockIdx.x * (int64_t)kWavesPerBlock + uniform_i32(threadIdx.x / kWave); v < n; v += waves) {
+        const int64_t b = uniform_i64(rowptr[v]), d = uniform_i64(rowptr[v + 1]) - b;
+        if (d < 2) continue;
+        const bool own = d >= kRankMinD;
+        const int sh = rank_shift(n, d);
+        const uint32_t K = 1u << rank_log(d);
+        uint32_t* R = rank + rank_base(b, v);
+        for (int64_t base = 0; base <= d; base += kRankPer * kWave) {
+            int32_t x[kRankPer], y[kRankPer];
+#pragma unroll
+            for (int q = 0; q < kRankPer; ++q) {
+                const int64_t i = base + q * kWave + lane;
+                x[q] = i < d ? col[b + i] : 0;
+                y[q] = i > 0 && i <= d ? col[b + i - 1] : 0;
+            }
+#pragma unroll
+            for (int q = 0; q < kRankPer; ++q) {
+                const int64_t i = base + q * kWave + lane;
+                twice |= i > 0 && i < d && x[q] == y[q];
+                const uint32_t k0 = i == 0 ? 0u : ((uint32_t)y[q] >> sh) + 1u;
+                const uint32_t k1 = i < d ? ((uint32_t)x[q] >> sh) + 1u : K + 1u;
+                const uint32_t nk = own && i <= d && k1 > k0 ? k1 - k0 : 0u;
+                if (nk <= kRankLaneFill)
+                    for (uint32_t k = k0; k < k0 + nk; ++k) R[k] = (uint32_t)i;
+                for (uint64_t wide = ballot(nk > kRankLaneFill); wide; wide &= wide - 1) {
+                    const int src = __ffsll((unsigned long long)wide) - 1;
+                    const uint32_t a0 = readlane_u32(k0, src), a1 = readlane_u32(k1, src);
+                    const uint32_t at = (uint32_t)(base + q * kWave + src);
+                    for (uint32_t k = a0 + lane; k < a1; k += kWave) R[k] = at;
+                }
+            }
+        }
+    }
+    if (ballot(twice) && lane == 0) atomicOr(repeats, 1);
 }
 
 // Walk guide tables, one wavefront per list with a positive total: the inclusive prefix of every edge (64 at a time, one
@@ -1178,6 +1671,13 @@ void launch_walk_hops(RowPtr rowptr, const int32_t* col, int64_t m, WalkHop* hop
     hipLaunchKernelGGL(k_walk_hops, dim3((unsigned)g), dim3(kBlock), 0, s, rowptr, col, m, hops);
 }
 
+void launch_walk_ranks(RowPtr rowptr, const int32_t* col, int64_t n, uint32_t* rank, int32_t* repeats, hipStream_t s) {
+    if (n <= 0) return;
+    int64_t g = (n + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (g > 65536) g = 65536;
+    hipLaunchKernelGGL(k_walk_ranks, dim3((unsigned)g), dim3(kBlock), 0, s, rowptr, col, n, rank, repeats);
+}
+
 void launch_walk_guides(RowPtr rowptr, const int32_t* col, const uint32_t* w, const uint64_t* wtot, int64_t n,
                         WalkEdge* rec, WalkVertex* vtx, WalkBucket* gd, hipStream_t s) {
     launch_walk_guides(rowptr, col, w, wtot, n, rec, vtx, gd, kGuideBucketsPerEdge, s);
@@ -1213,7 +1713,11 @@ void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev) 
         int64_t g = (p.num_walkers + kWavesPerBlock - 1) / kWavesPerBlock;
         if (g > grid) g = grid;
         const bool moves = (p.restart | p.jump) != 0;
-        if (p.bias == kNode2vec) {
+        if (p.bias == kNode2vec && p.g.rank) {
+            launch_kernel(p.g.repeats ? (moves ? k_walk_n2v_rank<true, true> : k_walk_n2v_rank<false, true>)
+                                      : (moves ? k_walk_n2v_rank<true, false> : k_walk_n2v_rank<false, false>),
+                          dim3((unsigned)g), dim3(kBlock), s, ev, p);
+        } else if (p.bias == kNode2vec) {
             if (moves) launch_kernel(k_walk_wave_n2v<true>, dim3((unsigned)g), dim3(kBlock), s, ev, p);
             else launch_kernel(k_walk_wave_n2v<false>, dim3((unsigned)g), dim3(kBlock), s, ev, p);
         } else {
