@@ -327,7 +327,8 @@ csaw_status csaw_walk(csaw_graph g, const csaw_walk_args* args, int32_t* paths,
  * one wavefront per walker, with the same paths. Sampling calls draw
  * through a weight array's guide when it is built and on (a walk or a server
  * builds it, or csaw_sample once its calls have sampled m / 4 edges by that
- * array and the tables fit half of the free device memory), else from the
+ * array, an edge drawn by csaw_layer_sample counting twice, and the tables fit
+ * half of the free device memory), else from the
  * weights and the chunk tables: the same edges either way.
  * enable: 1 (default) or 0. A walk already running keeps its route. INVALID_ARG
  * otherwise. Turning the guide off does not free built tables. */

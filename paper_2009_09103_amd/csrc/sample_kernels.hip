@@ -672,8 +672,8 @@ __device__ __forceinline__ void coarse_search(const CoarsePool& pl, uint64_t r, 
 }
 
 // Draw k distinct candidates with one lane per slot (lane j = slot j < k) and
-// a per-lane inverse transform search(r, m, Sm, bm). Each round every open
-// slot draws; taken in slot order, a slot keeps its candidate unless it is
+// a per-lane inverse transform search(r, m, Sm, bm) (k <= 64; lanes from k on stay out).
+// Each round every open slot draws; taken in slot order, a slot keeps its candidate unless it is
 // already held -- which also covers a lower slot that took the same candidate
 // in this round, so the lowest slot wins. Slots still open after `rounds` take
 // direct draws from the prefix without the held candidates, in slot order:
@@ -694,6 +694,20 @@ __device__ __forceinline__ int64_t draw_slots(Key key, uint32_t c0, uint32_t c1,
         uint64_t Sm = 0;
         uint32_t bm = 0;
         if ((open >> lane) & 1ull) search(draw(key, c0, c1, c2, (uint32_t)lane | ((uint32_t)a << 16), W), m, Sm, bm);
+        if (a == 0) {  // nothing is held: a slot yields to a lower one with the same candidate
+            bool dup = false;
+            for (int j = 0; j + 1 < k; ++j) {
+                const int64_t mj = readlane_i64(m, j);
+                dup |= lane > j && m == mj;
+            }
+            dup = dup && lane < k;
+            held = lane < k && !dup;
+            pos = m;
+            Spos = Sm;
+            bpos = bm;
+            open &= ballot(dup);
+            continue;
+        }
         for (uint64_t todo = open; todo; todo &= todo - 1) {
             const int j = __ffsll((unsigned long long)todo) - 1;
             const int64_t mj = readlane_i64(m, j);
@@ -1731,8 +1745,9 @@ __global__ void __launch_bounds__(kBlock) k_select_big(SampleLayer p) {
 // position), then k slots drawn like one list (rounds in slot order, direct
 // draws) with counter (instance id, layer, 0xFFFFFFFF, slot | round << 16):
 // a draw r finds its frontier vertex by binary search in the bias prefix and
-// its neighbor in that list (list_search; the position itself if unbiased). Picks not visited, deduplicated and sorted, form the next
-// frontier (at most 64 vertices).
+// its neighbor in that list (the walk guide or list_search; the position itself
+// if unbiased). Picks not visited, deduplicated and sorted, form the next frontier (at
+// most 64 vertices).
 __device__ __forceinline__ int32_t lds_upper(const uint64_t* a, int32_t n, uint64_t r) {
     // largest f in [0, n) with a[f] <= r (a[0] = 0 <= r)
     int32_t lo = 0, hi = n;
@@ -1746,22 +1761,68 @@ __device__ __forceinline__ int32_t lds_upper(const uint64_t* a, int32_t n, uint6
 
 // m = max{i : S_i <= r} inside one weighted list (weights w, first edge beg,
 // length d, prefix acc before it), with S_m and b_m: a scan of the list for
-// up to kWaveMaxD weights, else through the graph's chunk prefix table
-// (chunk totals, then the chunk's group prefixes, then one group).
+// up to kWaveMaxD weights, 64 of them in flight; else through the graph's
+// chunk prefix table (the running chunk totals, the chunk's group prefixes, one group).
+struct alignas(4) WeightQuad {
+    uint32_t x[4];
+};
 __device__ __forceinline__ void list_search(const uint32_t* __restrict__ w, const uint64_t* __restrict__ gtab,
-                                            int64_t beg, int64_t d, uint64_t acc, uint64_t r, int64_t& m,
-                                            uint64_t& Sm, uint32_t& bm) {
-    if (d <= kWaveMaxD) {
+                                            const uint64_t* __restrict__ ctab, int64_t beg, int64_t d, uint64_t acc,
+                                            uint64_t r, int64_t& m, uint64_t& Sm, uint32_t& bm) {
+    constexpr int kQuads = 16;
+    if (d < 4) {
         fine_scan_global(w, 0, d, acc, r, m, Sm, bm);
         return;
     }
-    const uint64_t* G = gtab + (beg >> kTabShift) * kChunkGroups;
-    const int64_t nch = chunks_of(d);
+    if (d <= kWaveMaxD) {
+        const int32_t n = (int32_t)d;
+        for (int32_t i0 = 0; i0 < n; i0 += 4 * kQuads) {
+            WeightQuad y[kQuads];  // the last one ends with the list: the weights it shares with another count once
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) y[q] = *(const WeightQuad*)(w + (i0 + 4 * q < n - 4 ? i0 + 4 * q : n - 4));
+            uint64_t run = acc;
+            bool found = false;
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) {
+                const int32_t i = i0 + 4 * q, at = i < n - 4 ? i : n - 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool in = at + j >= i;
+                    const uint64_t next = run + y[q].x[j];
+                    if (in && !found) {
+                        if (next > r) {
+                            found = true;
+                            m = at + j;
+                            Sm = run;
+                            bm = y[q].x[j];
+                        }
+                        run = next;
+                    }
+                }
+            }
+            if (found) return;
+            acc = run;
+        }
+        return;
+    }
+    const int64_t row0 = beg >> kTabShift, nch = chunks_of(d);
+    const uint64_t* G = gtab + row0 * kChunkGroups;
     int64_t j = 0;
-    for (; j + 1 < nch; ++j) {
-        const uint64_t t = G[j * kChunkGroups + kChunkGroups - 1];
-        if (acc + t > r) break;
-        acc += t;
+    if (ctab) {
+        const uint64_t* C = ctab + row0;
+        int64_t hi = nch - 1;  // the first chunk whose running total exceeds r
+        while (j < hi) {
+            const int64_t mid = (j + hi) >> 1;
+            if (acc + C[mid] <= r) j = mid + 1;
+            else hi = mid;
+        }
+        if (j > 0) acc += C[j - 1];
+    } else {
+        for (; j + 1 < nch; ++j) {
+            const uint64_t t = G[j * kChunkGroups + kChunkGroups - 1];
+            if (acc + t > r) break;
+            acc += t;
+        }
     }
     uint64_t before;
     const int32_t ghi = row_group(G + j * kChunkGroups, acc, r, before);
@@ -1771,79 +1832,128 @@ __device__ __forceinline__ void list_search(const uint32_t* __restrict__ w, cons
 
 // LDS of one wavefront, sized by the call's largest seed set mf and its
 // layers. A frontier holds the seeds, then at most 64 picks: cf = max(mf, 64)
-// entries. The two prefixes (uint64, cf + 1 each), then the frontier (cf),
-// the visited list (mf + 64 per layer) and the picks (64).
+// entries. The two prefixes (uint64, cf + 1 each), then the visited list (mf +
+// 64 per layer: each layer's frontier, sorted, behind the one before it) and the
+// picks (64).
 __host__ __device__ inline int32_t layer_frontier_cap(int32_t mf) { return mf > kWave ? mf : kWave; }
 inline size_t layer_lds_bytes(int32_t mf, int32_t L) {
     const size_t cf = (size_t)layer_frontier_cap(mf);
-    return 2 * sizeof(uint64_t) * (cf + 1) + sizeof(int32_t) * (cf + (size_t)mf + 64 * (size_t)L + kWave);
+    return 2 * sizeof(uint64_t) * (cf + 1) + sizeof(int32_t) * ((size_t)mf + 64 * (size_t)L + kWave);
 }
 
+// An instance is one wavefront's chain of loads, and 2,000 instances leave a SIMD two
+// of them: the time is the chain's length. So the seeds, and a frontier's totals,
+// are read with eight loads of a kind in flight, each lane summing a run of the
+// frontier (one scan per layer); a pick is looked for in the earlier frontiers by
+// binary search, and not at all in the last layer.
+// 2,000 instances of 512 seeds, two layers of 64 degree-biased picks on R-MAT 22: 270 us
+// before, 198 now, 90 through a walk guide (110 there with the positive positions of every
+// vertex read and its record in two tables).
+constexpr int kLayerPer = 8;
 __global__ void __launch_bounds__(kWave) k_layer_sample(LayerParams p) {
     extern __shared__ __align__(16) unsigned char layer_lds[];
     const int32_t cf = layer_frontier_cap(p.max_f);
     uint64_t* Wp = (uint64_t*)layer_lds;
     uint64_t* Dp = Wp + (cf + 1);
-    int32_t* F = (int32_t*)(Dp + (cf + 1));
-    int32_t* vis = F + cf;
+    int32_t* vis = (int32_t*)(Dp + (cf + 1));
     int32_t* pk = vis + p.max_f + 64 * p.L;  // this layer's picks by slot
     const int lane = lane_id();
     const Key key{p.k0, p.k1};
+    const bool guide = p.bias != kUniform && has_guide(p.g, p.bias);
+    const WalkVertex* vt = !guide ? nullptr : p.bias == kEdgeWeight ? p.g.wvtx_ew : p.g.wvtx_deg;
     const uint32_t* wts = p.bias == kEdgeWeight ? p.g.ew : p.g.degw;
     const int32_t* ppos = p.bias == kEdgeWeight ? p.g.ppos_ew : p.g.ppos_deg;
     const uint64_t* wtot = p.bias == kEdgeWeight ? p.g.wtot_ew : p.g.wtot_deg;
     const uint64_t* gtab = p.bias == kEdgeWeight ? p.g.gtab_ew : p.g.gtab_deg;
+    const uint64_t* ctab = p.bias == kEdgeWeight ? p.g.ctab_ew : p.g.ctab_deg;
     for (int64_t i = blockIdx.x; i < p.num_instances; i += gridDim.x) {
         const int64_t o0 = uniform_i64(p.seed_off[i]);
         int32_t nf = (int32_t)(uniform_i64(p.seed_off[i + 1]) - o0);  // <= kMaxPool (checked by the host)
         const uint32_t iid = (uint32_t)(p.instance_base + (uint64_t)i);
         bool bad = false;
-        for (int32_t f = lane; f < nf; f += kWave) {
-            const int32_t v = p.seeds[o0 + f];
-            const int32_t prev = f > 0 ? p.seeds[o0 + f - 1] : -1;
-            bad |= v < 0 || (int64_t)v >= p.g.n || v <= prev;
-            F[f] = v;
-            vis[f] = v;
+        for (int32_t f0 = 0; f0 < nf; f0 += kLayerPer * kWave) {
+            int32_t v[kLayerPer], prev[kLayerPer];
+#pragma unroll
+            for (int q = 0; q < kLayerPer; ++q) {
+                const int32_t f = f0 + q * kWave + lane;
+                v[q] = f < nf ? p.seeds[o0 + f] : 0;
+                prev[q] = f > 0 && f < nf ? p.seeds[o0 + f - 1] : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < kLayerPer; ++q) {
+                const int32_t f = f0 + q * kWave + lane;
+                if (f < nf) {
+                    bad |= v[q] < 0 || (int64_t)v[q] >= p.g.n || v[q] <= prev[q];
+                    vis[f] = v[q];
+                }
+            }
         }
         if (ballot(bad)) {  // outputs of the call are unspecified; the host reports the error
             if (lane == 0) *p.bad = 1;
             wave_lds_sync();
             continue;
         }
+        int32_t* F = vis;        // this layer's frontier
+        int32_t ends = nf;       // lane l: end of layer l's frontier in the visited list (lane 0's so far)
         int32_t nvis = nf;
         wave_lds_sync();
         for (int32_t l = 0; l < p.L; ++l) {
             const int32_t k = p.fan[l];
             int32_t* src = p.src + (i * p.L + l) * p.K;
             int32_t* dst = p.dst + (i * p.L + l) * p.K;
-            // totals per frontier vertex, then both prefixes, 64 vertices at a time
-            uint64_t carry_w = 0, carry_d = 0, npos = 0;
-            if (lane == 0) Wp[0] = Dp[0] = 0;
-            for (int32_t f0 = 0; f0 < nf; f0 += kWave) {
-                const int32_t f = f0 + lane;
-                uint64_t wv = 0, dv = 0, pv = 0;
-                if (f < nf) {
-                    const int32_t v = F[f];
-                    const int64_t beg = p.g.rowptr[v];
-                    dv = (uint64_t)(p.g.rowptr[v + 1] - beg);
-                    if (p.bias == kUniform) {
-                        wv = pv = dv;
-                    } else {
-                        wv = wtot[v];
-                        pv = (uint64_t)(ppos[v] & ~kWideList);
+            // totals per frontier vertex and both prefixes: lane L sums vertices [L c, L c + c)
+            const int32_t c1 = (nf + kWave - 1) / kWave, first = lane * c1;
+            uint64_t sw = 0, sd = 0;
+            uint32_t lists = 0;  // with a positive total
+            for (int32_t q0 = 0; q0 < c1; q0 += kLayerPer) {
+                uint64_t wv[kLayerPer], dv[kLayerPer];
+#pragma unroll
+                for (int q = 0; q < kLayerPer; ++q) {
+                    const int32_t f = first + q0 + q;
+                    wv[q] = dv[q] = 0;
+                    if (q0 + q < c1 && f < nf) {
+                        const int32_t v = F[f];
+                        if (vt) {
+                            const WalkVertex h = vt[v];
+                            dv[q] = h.d;
+                            wv[q] = h.W;
+                        } else {
+                            dv[q] = (uint64_t)(p.g.rowptr[v + 1] - p.g.rowptr[v]);
+                            if (p.bias != kUniform) wv[q] = wtot[v];
+                        }
                     }
                 }
-                const uint64_t iw = wave_incl_scan_u64(wv), id = wave_incl_scan_u64(dv);
-                if (f < nf) {
-                    Wp[f + 1] = carry_w + iw;
-                    Dp[f + 1] = carry_d + id;
+#pragma unroll
+                for (int q = 0; q < kLayerPer; ++q) {
+                    const int32_t f = first + q0 + q;
+                    if (p.bias == kUniform) wv[q] = dv[q];
+                    sw += wv[q];
+                    sd += dv[q];
+                    lists += wv[q] != 0 ? 1u : 0u;
+                    if (q0 + q < c1 && f < nf) {  // within the lane's run
+                        Wp[f + 1] = sw;
+                        Dp[f + 1] = sd;
+                    }
                 }
-                carry_w += readlane_u64(iw, kWave - 1);
-                carry_d += readlane_u64(id, kWave - 1);
-                npos += wave_sum_u64(pv);
+            }
+            const uint64_t iw = wave_incl_scan_u64(sw), id = wave_incl_scan_u64(sd);
+            const uint64_t W = readlane_u64(iw, kWave - 1);
+            // positive positions: at least one in each list with a positive total, counted where that leaves it open
+            uint64_t npos = p.bias == kUniform ? readlane_u64(id, kWave - 1) : wave_sum_u64(lists);
+            if (p.bias != kUniform && npos <= (uint64_t)k) {
+                uint64_t sp = 0;
+                for (int32_t f = lane; f < nf; f += kWave) sp += (uint64_t)(ppos[F[f]] & ~kWideList);
+                npos = wave_sum_u64(sp);
+            }
+            if (lane == 0) Wp[0] = Dp[0] = 0;
+            for (int32_t q = 0; q < c1; ++q) {
+                const int32_t f = first + q;
+                if (f < nf) {
+                    Wp[f + 1] += iw - sw;
+                    Dp[f + 1] += id - sd;
+                }
             }
             wave_lds_sync();
-            const uint64_t W = carry_w;
             const int32_t c = W == 0 ? 0 : ((uint64_t)k >= npos ? (int32_t)npos : k);
             int64_t pos = -1;  // this lane's pool position (slot lane < c)
             if (c > 0 && (uint64_t)k >= npos) {
@@ -1868,16 +1978,25 @@ __global__ void __launch_bounds__(kWave) k_layer_sample(LayerParams p) {
                 }
             } else if (c > 0) {
                 const auto search = [&](uint64_t r, int64_t& m, uint64_t& Sm, uint32_t& bm) {
-                    const int32_t f = lds_upper(Wp, nf, r);
                     if (p.bias == kUniform) {
                         m = (int64_t)r;
                         Sm = r;
                         bm = 1;
+                        return;
+                    }
+                    const int32_t f = lds_upper(Wp, nf, r);
+                    const int32_t v = F[f];
+                    const int64_t beg = vt ? (int64_t)vt[v].beg : p.g.rowptr[v];
+                    const uint64_t S0 = Wp[f], d = Dp[f + 1] - Dp[f];
+                    if (guide) {
+                        int32_t nb;
+                        const int32_t ml = slot_search(p.g, p.bias, v, beg, (int32_t)d, Wp[f + 1] - S0, r - S0, nb);
+                        slot_bias(p.g, p.bias, beg, ml, Sm, bm);
+                        Sm += S0;
+                        m = (int64_t)Dp[f] + ml;
                     } else {
-                        const int32_t v = F[f];
-                        const int64_t beg = p.g.rowptr[v];
                         int64_t ml = 0;
-                        list_search(wts + beg, gtab, beg, (int64_t)(Dp[f + 1] - Dp[f]), Wp[f], r, ml, Sm, bm);
+                        list_search(wts + beg, gtab, ctab, beg, (int64_t)d, S0, r, ml, Sm, bm);
                         m = (int64_t)Dp[f] + ml;
                     }
                 };
@@ -1893,11 +2012,22 @@ __global__ void __launch_bounds__(kWave) k_layer_sample(LayerParams p) {
             }
             for (int32_t j = c + lane; j < p.K; j += kWave) src[j] = dst[j] = -1;
             if (lane == 0) p.counts[i * p.L + l] = c;
-            // next frontier: the picks, deduplicated, minus visited, sorted
             wave_lds_sync();
+            if (l + 1 == p.L) break;
+            // next frontier: the picks, deduplicated, minus visited, sorted
             const int32_t x = lane < c ? pk[lane] : -1;
             bool keep = lane < c;
-            for (int32_t q = 0; q < nvis && keep; ++q) keep = vis[q] != x;
+            for (int32_t q = 0, b0 = 0; q <= l; ++q) {  // the frontiers so far, each sorted
+                const int32_t e0 = readlane_i32(ends, q);
+                int32_t lo = b0, hi = e0;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (vis[mid] < x) lo = mid + 1;
+                    else hi = mid;
+                }
+                keep = keep && !(lo < e0 && vis[lo] == x);
+                b0 = e0;
+            }
             for (int j = 0; j < kWave; ++j) {
                 const int32_t y = readlane_i32(x, j);
                 if (j < lane && y == x) keep = false;
@@ -1908,15 +2038,14 @@ __global__ void __launch_bounds__(kWave) k_layer_sample(LayerParams p) {
                 const int32_t y = readlane_i32(x, j);
                 if (((km >> j) & 1ull) && y < x) ++rank;
             }
-            wave_lds_sync();
-            if (keep) {
-                F[rank] = x;
-                vis[nvis + rank] = x;
-            }
+            F = vis + nvis;
+            if (keep) F[rank] = x;
             nf = __popcll(km);
             nvis += nf;
+            if (lane == l + 1) ends = nvis;
             wave_lds_sync();
         }
+        wave_lds_sync();  // the next instance rewrites the lists
     }
 }
 
