@@ -132,6 +132,7 @@ struct SampleCtl {
     int32_t overflow;
     int32_t unsupported;
     int32_t lookback_stuck;
+    uint32_t tickets[kMaxLayers + 1][2];  // blocks started, per frontier build: its own, its compaction's
 };
 
 static_assert(sizeof(SampleCtl) % 4 == 0, "control block is copied in 32-bit words");
@@ -170,6 +171,7 @@ struct FrontierBuild {
     int64_t nsw;
     int64_t* dirty;                  // [frontier capacity]
     int64_t nb_dirty;                // blocks of the compaction
+    bool ordered = false;            // blocks take tickets (a call whose chain gave up by block index)
 };
 
 struct SampleLayer {

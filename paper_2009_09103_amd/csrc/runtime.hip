@@ -955,6 +955,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     for (int32_t i = 0; i < ni; ++i) h_key[i] = a->rng_seeds ? a->rng_seeds[i] : a->rng_seed;
     std::memcpy(H + t_soff, a->seed_offsets, ((size_t)ni + 1) * sizeof(int64_t));
     SampleCtl* h_ctl = (SampleCtl*)(H + o_hctl);
+    bool ordered = streamer != nullptr;  // frontier builds in start order (the first try goes by block index)
     // every device step of the call, enqueued on stream s
     auto enqueue = [&](hipStream_t s) -> csaw_status {
         // one kernel clears the control block and look-back words and copies
@@ -992,6 +993,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         fb.offsets = out->offsets;
         fb.ctl = ctl;
         fb.status = d_status;
+        fb.ordered = ordered;
         auto build = [&](int32_t l, LaunchEvents ev) {
             fb.layer = l;
             fb.fanout = d_fan + (size_t)l * ni;
@@ -1051,8 +1053,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                 continue;
             }
             // the long-list path and the slot kernel touch disjoint outputs:
-            // run them side by side (scratch calls: one after the other)
-            const bool beside = big_path && !scratch;
+            // run them side by side (scratch calls and second tries: one after the other)
+            const bool beside = big_path && !scratch && !ordered;
             hipStream_t aux = beside ? ws->aux : s;
             if (beside) {
                 HIP_OR_FAIL(hipEventRecord(ws->fork, s));
@@ -1147,6 +1149,13 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         } else {
             if ((st = enqueue(s)) != CSAW_OK) return st;
         }
+        HIP_OR_FAIL(hipStreamSynchronize(s));
+    }
+    if (h_ctl->lookback_stuck && !ordered) {  // beside other calls' builds: once more, in order
+        ordered = true;
+        launch_fill_u32(bitmaps, 0u, lay.bitmap_words, s);
+        if ((st = enqueue(s)) != CSAW_OK) return st;
+        if (scratch) HIP_OR_FAIL(hipMemcpyAsync(h_ctl, ctl, sizeof(SampleCtl), hipMemcpyDeviceToHost, s));
         HIP_OR_FAIL(hipStreamSynchronize(s));
     }
     // a frontier build that gave up its look-back wrote entries at unknown

@@ -200,7 +200,8 @@ __device__ __forceinline__ int64_t chunks_of(int64_t d) { return (d + kChunk - 1
 // in one 64-bit word, so a reader never sees a value without its flag.
 constexpr uint64_t kStatusValid = 1ull << 48;
 constexpr uint64_t kStatusMask = kStatusValid - 1;
-constexpr uint32_t kSpinLimit = 1u << 20;
+constexpr uint32_t kSpinLimit = 1u << 20;       // half a second, in order
+constexpr uint32_t kSpinLimitIndex = 1u << 15;  // 17 ms, by block index
 
 __device__ __forceinline__ uint64_t status_pack(int64_t v, uint32_t epoch) {
     return ((uint64_t)v & kStatusMask) | kStatusValid | ((uint64_t)(epoch & 0x7FFF) << 49);
@@ -215,6 +216,11 @@ __device__ __forceinline__ uint64_t status_load(unsigned long long* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Entries of a layer's frontier; none where a build gave up, whose entries are not whole.
+__device__ __forceinline__ int64_t frontier_size(const SampleCtl* ctl, int32_t layer) {
+    return ctl->lookback_stuck ? 0 : ctl->fcount[layer];
+}
+
 // Next set bit of a word (cleared from it), or -1.
 __device__ __forceinline__ int32_t pop_bit(uint32_t& bits) {
     if (!bits) return -1;
@@ -223,15 +229,33 @@ __device__ __forceinline__ int32_t pop_bit(uint32_t& bits) {
     return b;
 }
 
+// Place of this block in the chain of a frontier build's blocks, whose later ones
+// wait for the earlier ones. The block index is such a place as long as the chip
+// takes blocks in its order; beside other kernels each XCD does so by
+// itself, and the waiting blocks of two chains can fill one XCD each while
+// either waits for a block that the other one keeps out (two builds of 2,048
+// and 4,096 blocks, once in about 2,000 bursts of a server's requests). So the wait
+// of such a chain is short; a call whose chain gave up runs again in order: blocks
+// take tickets as they start and wait for blocks that run. Tickets in every call
+// would cost it a queue at one address, 8 us for 512 blocks.
+__device__ __forceinline__ int64_t chain_place(uint32_t* tickets, bool ordered) {
+    if (!ordered) return blockIdx.x;
+    __shared__ uint32_t ticket;
+    if (threadIdx.x == 0) ticket = atomicAdd(tickets, 1u);
+    __syncthreads();
+    return ticket;
+}
+
 // Decoupled look-back of block b for two running totals (a, c), called by
 // the 64 lanes of one wavefront: publishes b's aggregates, then sums its
 // predecessors' published values 64 blocks at a time, nearest first; a
-// predecessor's inclusive prefix ends the walk (blocks are dispatched in
-// index order, so predecessors are resident or done). The spin is bounded and
+// predecessor's inclusive prefix ends the walk (predecessors run or are done:
+// chain_place). The spin is bounded and
 // reports through *stuck instead of hanging. Publishes b's inclusive prefix
 // and returns the exclusive ones (every lane).
 __device__ __forceinline__ void lookback2(unsigned long long* status, int64_t b, int64_t tot_a, int64_t tot_c,
-                                          uint32_t epoch, int32_t* stuck, int64_t& pa, int64_t& pc) {
+                                          uint32_t epoch, bool ordered, int32_t* stuck, int64_t& pa, int64_t& pc) {
+    const uint32_t limit = ordered ? kSpinLimit : kSpinLimitIndex;
     const int lane = lane_id();
     unsigned long long* st = status + 4 * b;
     if (b > 0 && lane == 0) {
@@ -268,7 +292,7 @@ __device__ __forceinline__ void lookback2(unsigned long long* status, int64_t b,
         const int first = incl ? __ffsll((unsigned long long)incl) - 1 : kWave;  // nearest inclusive
         const uint64_t upto = first >= kWave - 1 ? ~0ull : ((2ull << first) - 1);
         if (notready & upto) {  // a nearer predecessor has published nothing yet
-            if (++spins > kSpinLimit) {  // never expected: report instead of hanging
+            if (++spins > limit) {  // the call runs again in order, or (then never expected) reports it
                 if (lane == 0) *stuck = 1;
                 break;
             }
@@ -317,112 +341,61 @@ __device__ __forceinline__ void block_excl_scan4(int64_t (&x)[4], int64_t (&tot)
     __syncthreads();
 }
 
-// Frontier build of one layer, one pass: each thread takes G*V consecutive
-// bitmap words (G loads of V words of next and of visited; small bitmaps use
-// one word per thread for the most parallel blocks, large ones many, so that
-// the number of blocks, each a short latency-bound chain of loads, stays
-// small); it counts the new bits (entries), their edge counts min(k, P)
+// Frontier build of one layer, one pass: each thread takes one bitmap word, of all
+// of them (dense) or of those in the dirty list (sparse); it counts the new bits (entries), their edge counts min(k, P)
 // (edges) and their long-list route (the words and the list fields are
 // loaded again in the write pass rather than held in registers across the
 // scan, which keeps occupancy up); a block scan plus a decoupled look-back
-// over the blocks before it give global positions (blocks are dispatched in
-// index order, so predecessors are resident or done; the spin is bounded and
-// reports instead of hanging). The thread then writes its entries in
+// over the blocks before it give global positions. The thread then writes its entries in
 // (instance, vertex) order with count, edge offset, list fields and route,
 // sets visited |= next, clears next, and the first word of an instance writes
 // that instance's segment offset. The last block writes the layer's totals
 // and the output base of the next layer.
-template <int G, int V, bool kBurn, bool kSparse>
+template <bool kBurn, bool kSparse>
 __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
-    static_assert(V == 1 || V == 4, "one word or one 16-byte group per load");
-    static_assert(!kSparse || (G == 1 && V == 1), "the dirty list gives one word per thread");
     __shared__ int64_t s_base_e, s_base_g;
     const int tid = threadIdx.x;
-    const int64_t b = blockIdx.x;
     // dense: every word of the bitmaps; sparse: the words of the dirty list
     // (grid sized by capacity, blocks past the list end at once)
     int64_t nwords = fb.nwords, nb = fb.nb;
     if (kSparse) {
+        if (fb.ctl->lookback_stuck) return;  // the list is not whole
         nwords = fb.ctl->ndirty[fb.layer];
         nb = nwords > 0 ? (nwords + kBlock - 1) / kBlock : 1;
-        if (b >= nb) return;
+        if (blockIdx.x >= nb) return;
     }
-    const int64_t w0 = (b * kBlock + tid) * (G * V);  // first word of the thread (nwords is a multiple of 4)
-    const int64_t wself = kSparse ? (w0 < nwords ? fb.dirty[w0] : 0) : w0;  // the thread's bitmap word
+    const int64_t b = chain_place(&fb.ctl->tickets[fb.layer][0], fb.ordered);
+    const int64_t w0 = b * kBlock + tid;  // the thread's word, or dirty word
+    const int64_t iw = kSparse ? (w0 < nwords ? fb.dirty[w0] : 0) : w0;
     const int64_t out_base = fb.ctl->out_base[fb.layer];
-    uint32_t raws[G][V], viss[G][V];
-    if (V == 4) {
-        // next first; visited only where next has bits (large bitmaps are sparse)
-        uint4 r4[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t iw = w0 + V * g;
-            r4[g] = iw < fb.nwords ? *(const uint4*)(fb.next + iw) : make_uint4(0u, 0u, 0u, 0u);
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t iw = w0 + V * g;
-            const bool any = (r4[g].x | r4[g].y | r4[g].z | r4[g].w) != 0u;
-            const uint4 v4 = any ? *(const uint4*)(fb.visited + iw) : make_uint4(0u, 0u, 0u, 0u);
-            const uint32_t rr[4] = {r4[g].x, r4[g].y, r4[g].z, r4[g].w}, vv[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-            for (int q = 0; q < V; ++q) {
-                raws[g][q] = rr[q];
-                viss[g][q] = vv[q];
-            }
+    const uint32_t raw = w0 < nwords ? fb.next[iw] : 0u, vis = w0 < nwords ? fb.visited[iw] : 0u;
+    const uint32_t w = raw & ~vis;  // picks of visited vertices are not new
+    const int64_t inst = iw / fb.nwp;
+    const int32_t vbase = (int32_t)((iw - inst * fb.nwp) * 32);
+    int32_t k = 0, kind = 0;
+    uint64_t key = 0;
+    uint32_t iid = 0;
+    if (w) {
+        k = fb.fanout[inst];
+        kind = fb.bias[inst];
+        if (kBurn) {
+            key = fb.inst_key[inst];
+            iid = fb.inst_id[inst];
         }
     }
-    if (V == 1) {
+    int64_t cnt4[4] = {__popc(w), 0, 0, 0};  // entries, edges, long lists, (unused)
+    for (uint32_t bits = w; bits;) {  // four bits at a time so that their loads overlap
+        int32_t bv[4];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t iw = w0 + g, wd = kSparse ? wself : iw;
-            raws[g][0] = iw < nwords ? fb.next[wd] : 0u;
-            viss[g][0] = iw < nwords ? fb.visited[wd] : 0u;
-        }
-    }
-    int64_t cnt4[4] = {0, 0, 0, 0};  // entries, edges, long lists, (unused)
-    {
-        int64_t inst_k = -1;
-        int32_t k = 0, kind = 0;
-        uint64_t key = 0;
-        uint32_t iid = 0;
+        for (int t = 0; t < 4; ++t) bv[t] = pop_bit(bits);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-#pragma unroll
-            for (int q = 0; q < V; ++q) {
-                const uint32_t w = raws[g][q] & ~viss[g][q];  // picks of visited vertices are not new
-                if (!w) continue;
-                const int64_t iw = kSparse ? wself : w0 + V * g + q;
-                const int64_t inst = iw / fb.nwp;
-                if (inst != inst_k) {
-                    inst_k = inst;
-                    k = fb.fanout[inst];
-                    kind = fb.bias[inst];
-                    if (kBurn) {
-                        key = fb.inst_key[inst];
-                        iid = fb.inst_id[inst];
-                    }
-                }
-                const int32_t vbase = (int32_t)((iw - inst * fb.nwp) * 32);
-                cnt4[0] += __popc(w);
-                uint32_t bits = w;
-                while (bits) {  // four bits at a time so that their loads overlap
-                    int32_t bv[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) bv[t] = pop_bit(bits);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        int32_t route = kRouteWave, pinfo = 0;
-                        int64_t beg = 0, d = 0;
-                        int32_t c = 0;
-                        if (bv[t] >= 0) {
-                            const int32_t kv = neighbor_size<kBurn>(k, fb.burn, key, iid, fb.layer, vbase + bv[t]);
-                            c = entry_count(fb.g, kv, kind, vbase + bv[t], route, beg, d, pinfo, fb.ctl);
-                            cnt4[1] += c;
-                            if (route == kRouteBig) ++cnt4[2];
-                        }
-                    }
-                }
+        for (int t = 0; t < 4; ++t) {
+            int32_t route = kRouteWave, pinfo = 0;
+            int64_t beg = 0, d = 0;
+            if (bv[t] >= 0) {
+                const int32_t kv = neighbor_size<kBurn>(k, fb.burn, key, iid, fb.layer, vbase + bv[t]);
+                cnt4[1] += entry_count(fb.g, kv, kind, vbase + bv[t], route, beg, d, pinfo, fb.ctl);
+                if (route == kRouteBig) ++cnt4[2];
             }
         }
     }
@@ -439,7 +412,7 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
     if (tid < kWave) {  // wave 0: publish, then look back 64 predecessors per step
         int64_t pe = 0, pg = 0;
         lookback2(fb.status, b, tot_e, tot_g, kSparse ? 2u * fb.layer + 2u : (uint32_t)fb.layer + 1u,
-                  &fb.ctl->lookback_stuck, pe, pg);
+                  fb.ordered, &fb.ctl->lookback_stuck, pe, pg);
         if (tid == 0) {
             s_base_e = pe;
             s_base_g = pg;
@@ -448,97 +421,44 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
     __syncthreads();
     int64_t pos = s_base_e + ex_e;
     int64_t eoff = s_base_g + ex_g;
-    int64_t inst_k = -1;
-    int32_t k = 0, kind = 0;
-    uint64_t key = 0;
-    uint32_t iid = 0;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        if (w0 + V * g >= nwords) break;
-        const int64_t iw4 = kSparse ? wself : w0 + V * g;
-        // the words again (L2): keeping them in registers across the scan
-        // costs occupancy
-        if (V == 4) {
-            const uint4 r4 = *(const uint4*)(fb.next + iw4);
-            const bool any = (r4.x | r4.y | r4.z | r4.w) != 0u;
-            const uint4 v4 = any ? *(const uint4*)(fb.visited + iw4) : make_uint4(0u, 0u, 0u, 0u);
-            const uint32_t rr[4] = {r4.x, r4.y, r4.z, r4.w}, vv[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-            for (int q = 0; q < V; ++q) {
-                raws[g][q] = rr[q];
-                viss[g][q] = vv[q];
-            }
-        } else {
-            raws[g][0] = fb.next[iw4];
-            viss[g][0] = fb.visited[iw4];
-        }
-        uint32_t newv[V];
-        bool any_raw = false, any_new = false;
-#pragma unroll
-        for (int q = 0; q < V; ++q) {
-            const int64_t iw = iw4 + q;
-            const uint32_t w = raws[g][q] & ~viss[g][q];
-            newv[q] = viss[g][q] | w;
-            any_raw |= raws[g][q] != 0u;
-            any_new |= w != 0u;
-            const int64_t inst = iw / fb.nwp;
-            const int64_t local = iw - inst * fb.nwp;
-            if (fb.offsets && fb.layer < fb.num_layers) {
-                if (!kSparse) {
-                    if (local == 0) fb.offsets[(int64_t)fb.layer * fb.num_instances + inst] = out_base + eoff;
-                } else {
-                    // the first dirty word of an instance starts its segment, and
-                    // those of the instances since the previous dirty word's (empty)
-                    const int64_t prev = w0 > 0 ? fb.dirty[w0 - 1] / fb.nwp : -1;
-                    for (int64_t i = prev + 1; i <= inst; ++i)
-                        fb.offsets[(int64_t)fb.layer * fb.num_instances + i] = out_base + eoff;
-                }
-            }
-            if (!w) continue;
-            if (inst != inst_k) {
-                inst_k = inst;
-                k = fb.fanout[inst];
-                kind = fb.bias[inst];
-                if (kBurn) {
-                    key = fb.inst_key[inst];
-                    iid = fb.inst_id[inst];
-                }
-            }
-            const int32_t vbase = (int32_t)(local * 32);
-            uint32_t bits = w;
-            while (bits) {
-                int32_t bv[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) bv[t] = pop_bit(bits);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    if (bv[t] < 0) continue;
-                    const int32_t v = vbase + bv[t];
-                    int32_t route, c, pinfo;
-                    int64_t beg, d;
-                    c = entry_count(fb.g, neighbor_size<kBurn>(k, fb.burn, key, iid, fb.layer, v), kind, v, route, beg, d,
-                                    pinfo, fb.ctl);
-                    fb.fv[pos] = v;
-                    fb.fi[pos] = (int32_t)inst;
-                    fb.cnt[pos] = c;
-                    fb.off[pos] = eoff;
-                    fb.fbeg[pos] = beg;
-                    fb.fdeg[pos] = (int32_t)d;
-                    fb.fpos[pos] = pinfo;
-                    if (route == kRouteBig) fb.bigs[s_big_base + ex_big++] = (int32_t)pos;
-                    ++pos;
-                    eoff += c;
-                }
+    if (w0 < nwords) {
+        if (fb.offsets && fb.layer < fb.num_layers) {
+            if (!kSparse) {
+                if (vbase == 0) fb.offsets[(int64_t)fb.layer * fb.num_instances + inst] = out_base + eoff;
+            } else {
+                // the first dirty word of an instance starts its segment, and
+                // those of the instances since the previous dirty word's (empty)
+                const int64_t prev = w0 > 0 ? fb.dirty[w0 - 1] / fb.nwp : -1;
+                for (int64_t i = prev + 1; i <= inst; ++i)
+                    fb.offsets[(int64_t)fb.layer * fb.num_instances + i] = out_base + eoff;
             }
         }
-        if (V == 4) {
-            if (any_new) *(uint4*)(fb.visited + iw4) = make_uint4(newv[0], newv[V > 1 ? 1 : 0], newv[V > 2 ? 2 : 0],
-                                                                  newv[V > 3 ? 3 : 0]);
-            if (any_raw) *(uint4*)(fb.next + iw4) = make_uint4(0u, 0u, 0u, 0u);  // also words that held only visited picks
-        } else {
-            if (any_new) fb.visited[iw4] = newv[0];
-            if (any_raw) fb.next[iw4] = 0u;
+        for (uint32_t bits = w; bits;) {
+            int32_t bv[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) bv[t] = pop_bit(bits);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (bv[t] < 0) continue;
+                const int32_t v = vbase + bv[t];
+                int32_t route, c, pinfo;
+                int64_t beg, d;
+                c = entry_count(fb.g, neighbor_size<kBurn>(k, fb.burn, key, iid, fb.layer, v), kind, v, route, beg, d, pinfo,
+                                fb.ctl);
+                fb.fv[pos] = v;
+                fb.fi[pos] = (int32_t)inst;
+                fb.cnt[pos] = c;
+                fb.off[pos] = eoff;
+                fb.fbeg[pos] = beg;
+                fb.fdeg[pos] = (int32_t)d;
+                fb.fpos[pos] = pinfo;
+                if (route == kRouteBig) fb.bigs[s_big_base + ex_big++] = (int32_t)pos;
+                ++pos;
+                eoff += c;
+            }
         }
+        if (w) fb.visited[iw] = vis | w;
+        if (raw) fb.next[iw] = 0u;  // also words that held only visited picks
     }
     if (b == nb - 1) {  // last block: totals, and the bases of the layers after this one
         const int64_t te = s_base_e + tot_e, tg = s_base_g + tot_g;
@@ -571,7 +491,7 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
 __global__ void __launch_bounds__(kBlock) k_dirty_compact(FrontierBuild fb) {
     __shared__ int64_t s_base;
     const int tid = threadIdx.x;
-    const int64_t b = blockIdx.x;
+    const int64_t b = chain_place(&fb.ctl->tickets[fb.layer][1], fb.ordered);
     const int64_t nsumm = (int64_t)fb.num_instances * fb.nsw;
     const int64_t i0 = (b * kBlock + tid) * 4;
     const uint4 s4 = i0 < nsumm ? *(const uint4*)(fb.summ + i0) : make_uint4(0u, 0u, 0u, 0u);
@@ -581,7 +501,7 @@ __global__ void __launch_bounds__(kBlock) k_dirty_compact(FrontierBuild fb) {
     block_excl_scan4(cnt4, tot4);
     if (tid < kWave) {
         int64_t pa = 0, pc = 0;
-        lookback2(fb.status, b, tot4[0], 0, 2u * fb.layer + 1u, &fb.ctl->lookback_stuck, pa, pc);
+        lookback2(fb.status, b, tot4[0], 0, 2u * fb.layer + 1u, fb.ordered, &fb.ctl->lookback_stuck, pa, pc);
         if (tid == 0) s_base = pa;
     }
     __syncthreads();
@@ -1284,7 +1204,7 @@ __global__ void __launch_bounds__(kBlock, 5) k_select_slots(SampleLayer p) {
     const int wid = uniform_i32(threadIdx.x / kWave);
     SlotRun<kWeighted>& L = runs[wid];
     const int lane = lane_id();
-    const int64_t fcount = p.ctl->fcount[p.layer];
+    const int64_t fcount = frontier_size(p.ctl, p.layer);
     const int64_t out_base = p.ctl->out_base[p.layer];
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
     const int64_t wave = blockIdx.x * (int64_t)kWavesPerBlock + wid;
@@ -1498,7 +1418,7 @@ __global__ void __launch_bounds__(kBlock, 5) k_select_slots(SampleLayer p) {
 __global__ void __launch_bounds__(kBlock) k_select_wave(SampleLayer p) {
     const int wid = uniform_i32(threadIdx.x / kWave);
     const int lane = lane_id();
-    const int64_t fcount = p.ctl->fcount[p.layer];
+    const int64_t fcount = frontier_size(p.ctl, p.layer);
     const int64_t out_base = p.ctl->out_base[p.layer];
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
     const int64_t wave = blockIdx.x * (int64_t)kWavesPerBlock + wid;
@@ -1718,7 +1638,7 @@ __global__ void __launch_bounds__(kBlock) k_select_big(SampleLayer p) {
     __shared__ uint64_t tabs[kWavesPerBlock][kBigTab + 1];
     const int wid = uniform_i32(threadIdx.x / kWave);
     const int lane = lane_id();
-    const int64_t nb = (int64_t)p.ctl->nbig[p.layer];
+    const int64_t nb = p.ctl->lookback_stuck ? 0 : (int64_t)p.ctl->nbig[p.layer];
     const int64_t out_base = p.ctl->out_base[p.layer];
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
     const int64_t wave = blockIdx.x * (int64_t)kWavesPerBlock + wid;
@@ -2067,7 +1987,7 @@ __global__ void k_clear_visited(ClearVisited c) {
         __threadfence_system();
     }
     for (int l = 0; l < c.num_layers; ++l) {
-        const int64_t fcount = c.fcount[l];
+        const int64_t fcount = frontier_size(c.ctl, l);
         const int32_t* __restrict__ fv = c.fv[l];
         const int32_t* __restrict__ fi = c.fi[l];
         for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < fcount;
@@ -2088,7 +2008,7 @@ __global__ void __launch_bounds__(kBlock) k_partition_work(const int32_t* __rest
     __shared__ unsigned long long s_work[2 * kMaxPartitions];
     for (int i = threadIdx.x; i < 2 * kMaxPartitions; i += blockDim.x) s_work[i] = 0ull;
     __syncthreads();
-    const int64_t fcount = ctl->fcount[layer];
+    const int64_t fcount = frontier_size(ctl, layer);
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < fcount;
          e += (int64_t)gridDim.x * blockDim.x) {
         const int64_t v = fv[e];
@@ -2157,30 +2077,20 @@ void launch_mark_seeds(const int32_t* seeds, int64_t num_seeds, const int64_t* s
                        num_seeds, seed_offsets, ni, n, next, nwp, summ, nsw, ctl);
 }
 
-// Bitmap words per thread of the frontier build: one up to 2^20 words (one
-// instance of a 2^25-vertex graph), 16 above.
-static int frontier_build_words(int64_t words) { return words > (int64_t(1) << 20) ? 16 : 1; }
-
 int64_t frontier_build_blocks(int64_t words) {
-    const int64_t per = (int64_t)kBlock * frontier_build_words(words);
-    const int64_t nb = (words + per - 1) / per;
+    const int64_t nb = (words + kBlock - 1) / kBlock;
     return nb > 0 ? nb : 1;
 }
 
 void launch_frontier_build(const FrontierBuild& fb, hipStream_t s, LaunchEvents ev) {
     if (fb.summ) {  // sparse: compact the summary, then one thread per dirty word
         hipLaunchKernelGGL(k_dirty_compact, dim3((unsigned)fb.nb_dirty), dim3(kBlock), 0, s, fb);
-        launch_kernel(fb.burn ? k_frontier_build<1, 1, true, true> : k_frontier_build<1, 1, false, true>,
-                      dim3((unsigned)fb.nb), dim3(kBlock), s, ev, fb);
-        return;
+        launch_kernel(fb.burn ? k_frontier_build<true, true> : k_frontier_build<false, true>, dim3((unsigned)fb.nb),
+                      dim3(kBlock), s, ev, fb);
+    } else {
+        launch_kernel(fb.burn ? k_frontier_build<true, false> : k_frontier_build<false, false>, dim3((unsigned)fb.nb),
+                      dim3(kBlock), s, ev, fb);
     }
-    const bool wide = frontier_build_words(fb.nwords) == 16;
-    if (fb.burn)
-        launch_kernel(wide ? k_frontier_build<4, 4, true, false> : k_frontier_build<1, 1, true, false>,
-                      dim3((unsigned)fb.nb), dim3(kBlock), s, ev, fb);
-    else
-        launch_kernel(wide ? k_frontier_build<4, 4, false, false> : k_frontier_build<1, 1, false, false>,
-                      dim3((unsigned)fb.nb), dim3(kBlock), s, ev, fb);
 }
 
 int64_t sparse_build_blocks(int64_t capacity) {
