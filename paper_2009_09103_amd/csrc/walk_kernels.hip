@@ -79,6 +79,21 @@ __device__ __forceinline__ WalkerCtx walker_ctx(const WalkParams& p, int64_t w) 
     return c;
 }
 
+// Adds each lane's steps to its request's counter (every lane of the wavefront calls
+// it; its lanes may belong to several requests): one atomic per request, since
+// atomics to one address pass one after the other, some 13 ns apart. With one per lane
+// seven walk requests of 188,672 walkers took 2.45 ms, 0.46 with these.
+__device__ __forceinline__ void count_steps(int64_t steps, unsigned long long* counter) {
+    for (uint64_t todo = ballot(steps != 0); todo;) {
+        const int lead = __ffsll((unsigned long long)todo) - 1;
+        const uint64_t to = readlane_u64((uint64_t)(uintptr_t)counter, lead);
+        const bool mine = steps != 0 && (uint64_t)(uintptr_t)counter == to;
+        const int64_t sum = wave_sum_i64(mine ? steps : 0);
+        if (lane_id() == lead) atomicAdd(counter, (unsigned long long)sum);
+        todo &= ~ballot(mine);
+    }
+}
+
 // A lane's path entries, written kPathRun at a time in 16-byte stores: a 4-byte
 // store into a row of its own per step leaves each line part written in the L2
 // when it is evicted, over and over; a run of a line's length reaches its line
@@ -189,8 +204,8 @@ __global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
             }
             my_steps = s;
         }
-        if (p.batch.req) {  // lanes of one wave may belong to different requests
-            if (my_steps) atomicAdd(my_counter, (unsigned long long)my_steps);
+        if (p.batch.req) {
+            count_steps(my_steps, my_counter);
         } else {
             const int64_t ws = wave_sum_i64(my_steps);
             if (lane_id() == 0 && ws) atomicAdd(p.steps, (unsigned long long)ws);
@@ -1018,8 +1033,8 @@ __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
             }
             my_steps = s;
         }
-        if (p.batch.req) {  // lanes of one wave may belong to different requests
-            if (my_steps) atomicAdd(my_counter, (unsigned long long)my_steps);
+        if (p.batch.req) {
+            count_steps(my_steps, my_counter);
         } else {
             const int64_t ws = wave_sum_i64(my_steps);
             if (lane_id() == 0 && ws) atomicAdd(p.steps, (unsigned long long)ws);
