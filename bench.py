@@ -52,7 +52,7 @@ WAVE_MAX_D = 512  # longer (or 2^32-heavy) weighted lists that need draws take t
 
 
 def small_bucket(c, d, k, take, wflag, long_, bound):
-    """Entries served by the sub-wave kernel (select_small) under the bucket
+    """Entries of a small size (key select_small) under the bucket
     bound max(bound16, bound32): take-all and weighted lists of at most
     `bound` candidates, unbiased draws of at most `bound` slots."""
     if bound <= 0:
@@ -61,11 +61,18 @@ def small_bucket(c, d, k, take, wflag, long_, bound):
     return (c > 0) & ~long_ & (size <= bound)
 
 
+def slot_bytes(alg):
+    """The same bytes by the kernels that move them: one draws the entries of
+    both sizes, beside the long lists (which it draws too where the weight
+    array has its walk guide)."""
+    return {"select_slots": alg["select_small"] + alg["select_wave"], "select_big": alg["select_big"]}
+
+
 def path_bytes(rowptr, ppos, seeds, dst, offsets, fanouts, weighted, bound=0):
     """Algorithmic bytes of one call, per kernel, from the graph and the
     call's own output. Per frontier vertex: 8 (frontier entry) + 16 (row-offset
-    pair) bytes of metadata. Lists drawn by the wavefront kernels (select_small
-    for the sub-wave buckets, select_wave for the rest) add 4*deg if the bias
+    pair) bytes of metadata. Lists drawn slot by slot (keys select_small up to
+    the bucket bound, select_wave for the rest) add 4*deg if the bias
     reads a weight array; a long weighted list (select_big) reads one 8-byte
     group prefix per 16 weights from the graph's chunk prefix table (built once
     per graph, so not part of a call). Every emitted edge costs 12 (neighbor id
@@ -190,12 +197,13 @@ def bench_degree_biased(args):
         for k in alg:
             alg[k] += bytes_of[s][k]
     torch.cuda.synchronize()
-    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_small", "select_wave", "select_big",
-                                                "frontier_build", "visited_clear")}
+    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_big", "frontier_build",
+                                                "visited_clear")}
     csaw.profile_enable(False)
     csaw.profile_reset()
-    sel_ms, sel_n = times["select_wave"]
-    achieved = alg["select_wave"] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
+    alg = slot_bytes(alg)
+    sel_ms, sel_n = times["select_slots"]
+    achieved = alg["select_slots"] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
     per_kernel = {k: {"alg_bytes_per_step": alg[k] / args.steps, "ms_per_step": times[k][0] / args.steps,
                       "GB_per_s": alg[k] / (times[k][0] / 1e3) / 1e9 if times[k][0] > 0 else 0.0}
                   for k in alg}
@@ -223,9 +231,9 @@ def bench_degree_biased(args):
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic("traffic_select_degree_biased_rmat22.md"),
-                     "kernel": "select_wave (k_select)", "launches": sel_n,
+                     "kernel": "select_slots (k_select_slots)", "launches": sel_n,
                      "avg_launch_us": sel_ms / max(sel_n, 1) * 1e3,
-                     "alg_bytes_per_launch": alg["select_wave"] / max(sel_n, 1)},
+                     "alg_bytes_per_launch": alg["select_slots"] / max(sel_n, 1)},
         "roofline_step": {"alg_bytes": step_bytes, "achieved": step_bytes / (dt / args.steps) / 1e9,
                           "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": step_bytes / (dt / args.steps) / 1e9 / HBM_PEAK_GBS},
@@ -318,12 +326,13 @@ def bench_batched(args):
     csaw.profile_enable(True)
     g.sample(offs, seeds_d, fanouts, bias, rng_seed=1, rounds=args.rounds, out=(src, dst, offsets))
     torch.cuda.synchronize()
-    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_small", "select_wave", "select_big",
-                                                "frontier_build", "visited_clear")}
+    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_big", "frontier_build",
+                                                "visited_clear")}
     csaw.profile_enable(False)
     csaw.profile_reset()
-    sel_ms, sel_n = times["select_wave"]
-    achieved = alg["select_wave"] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
+    alg = slot_bytes(alg)
+    sel_ms, sel_n = times["select_slots"]
+    achieved = alg["select_slots"] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
     step_bytes = sum(alg.values())
     # plain: one call per instance (same ids, same seed)
     per = []
@@ -353,9 +362,9 @@ def bench_batched(args):
         "config": {"workload": rec["name"], "instances": ni, "seeds": int(len(seeds)),
                    "edges_per_step": int(edges), "tuning": tuning, "rounds": args.rounds or 8},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "select_wave (k_select)",
+                     "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "select_slots (k_select_slots)",
                      "launches": sel_n, "avg_launch_us": sel_ms / max(sel_n, 1) * 1e3,
-                     "alg_bytes_per_launch": alg["select_wave"] / max(sel_n, 1)},
+                     "alg_bytes_per_launch": alg["select_slots"] / max(sel_n, 1)},
         "roofline_step": {"alg_bytes": step_bytes, "achieved": step_bytes / dt / 1e9, "peak": HBM_PEAK_GBS,
                           "unit": "GB/s", "frac": step_bytes / dt / 1e9 / HBM_PEAK_GBS},
         "kernels": {k: {"alg_bytes_per_step": alg[k], "ms_per_step": times[k][0],
@@ -571,7 +580,7 @@ def bench_served(args):
     trace = inputs.request_trace(rp, col, args.requests, best["qps"], rec["trace_rng"], rec["sample_fraction"])
     _, results = run_server(csaw, g, trace, served_kw, profile=True)
     kernels = {}
-    for name in ("walk", "select_wave", "select_big", "select_small", "frontier_build", "frontier_init",
+    for name in ("walk", "select_slots", "select_big", "frontier_build", "frontier_init",
                  "visited_clear"):
         ms, n = csaw.profile_read(name)
         kernels[name] = {"ms": ms, "launches": n}
@@ -720,11 +729,11 @@ def bench_forest_fire(args):
     for _ in range(args.steps):
         g.sample(offs, seeds_d, fan, csaw.UNIFORM, **call)
     torch.cuda.synchronize()
-    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_small", "select_wave", "select_big",
-                                                "frontier_build", "visited_clear")}
+    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_big", "frontier_build",
+                                                "visited_clear")}
     csaw.profile_enable(False)
     csaw.profile_reset()
-    sel_ms = (times["select_small"][0] + times["select_wave"][0]) / args.steps
+    sel_ms = times["select_slots"][0] / args.steps
     achieved = alg / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
     return {
         "metric": "sampled edges/sec (SEPS), forest fire sampling",
@@ -735,7 +744,7 @@ def bench_forest_fire(args):
                    "depth": 2, "cap": 64, "edges_per_step": int(edges), "tuning": tuning},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "select_small + select_wave (k_select_small, k_select)",
+                     "kernel": "select_slots (k_select_slots)",
                      "ms_per_step": sel_ms, "alg_bytes_per_step": alg},
         "kernel_ms_per_step": {k: v[0] / args.steps for k, v in times.items()},
     }

@@ -332,7 +332,7 @@ class Graph:
                         capacity=None, stream=None, out=None, instance_ids=None, rng_seeds=None, reps=3, rounds=0,
                         burn=0):
         """Autotuner (csaw_autotune_sample): times the call under each
-        sub-wave bucket setting, keeps the fastest on the graph. Returns
+        setting of the bounds, keeps the fastest on the graph. Returns
         (SampleResult, (bound16, bound32))."""
         t = Tuning()
         res = self._run_sample(lambda a, o: lib.csaw_autotune_sample(self._h, a, o, int(reps), _stream(stream),
