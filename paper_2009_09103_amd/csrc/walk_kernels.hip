@@ -4,8 +4,9 @@
 // A walk is a chain of one-draw selections (NeighborSize 1, with
 // replacement). The step loop runs inside the kernel: walkers are
 // independent, so no host round trip is needed between steps.
-//   - unbiased walks: one lane per walker (a step is two row-offset loads,
-//     one Philox draw and one neighbor load);
+//   - unbiased walks: one lane per walker (a step is one Philox draw and one
+//     load of the picked edge's record, its neighbor and that one's list, or
+//     without the hop table a neighbor load and two row-offset loads);
 //   - edge-weight and degree-biased walks through the graph's walk guide
 //     (exact per-edge prefixes and a bucket table per list; a step is two
 //     rounds of loads, now and then three): one lane per walker in launches of at
@@ -1629,6 +1630,26 @@ __device__ __forceinline__ WalkBucket guide_bucket(uint64_t k, int sh, uint64_t 
     return WalkBucket{(uint64_t)bound | ((uint64_t)second << 32), i, y};
 }
 
+// Edge i of a list and the next one (zeros past the end). A hub's list is one wavefront's
+// serial work and sets the time of the build, so edges are loaded 256 at a time, one
+// such step ahead: R-MAT 22 (longest list 163,000) 5.6 ms, 6.9 with 64 at a time.
+constexpr int kGuidePer = 4;
+struct GuideEdges {
+    uint32_t x, x1;
+    int32_t y, y1;
+};
+__device__ __forceinline__ void load_edges(const uint32_t* __restrict__ w, const int32_t* __restrict__ col, int64_t d,
+                                           int64_t base, GuideEdges (&e)[kGuidePer]) {
+#pragma unroll
+    for (int q = 0; q < kGuidePer; ++q) {
+        const int64_t i = base + q * kWave + lane_id();
+        e[q].x = i < d ? w[i] : 0u;
+        e[q].y = i < d ? col[i] : 0;
+        e[q].x1 = i + 1 < d ? w[i + 1] : 0u;
+        e[q].y1 = i + 1 < d ? col[i + 1] : 0;
+    }
+}
+
 __global__ void __launch_bounds__(kBlock) k_walk_guides(RowPtr rowptr, const int32_t* __restrict__ col,
                                                         const uint32_t* __restrict__ w,
                                                         const uint64_t* __restrict__ wtot, int64_t n,
@@ -1647,32 +1668,40 @@ __global__ void __launch_bounds__(kBlock) k_walk_guides(RowPtr rowptr, const int
         const uint64_t low = (uint64_t(1) << sh) - 1;
         WalkBucket* G = gd + guide_base(b, v, per);
         uint64_t run = 0;
-        for (int64_t base = 0; base < d; base += kWave) {
-            const int64_t i = base + lane;
-            const uint64_t x = i < d ? (uint64_t)w[b + i] : 0ull;
-            const int32_t y = i < d ? col[b + i] : 0;
-            const uint64_t x1 = i + 1 < d ? (uint64_t)w[b + i + 1] : 0ull;  // the next edge
-            const int32_t y1 = i + 1 < d ? col[b + i + 1] : 0;
-            const uint64_t incl = run + wave_incl_scan_u64(x);
-            const uint64_t excl = incl - x;
-            const uint64_t k0 = (excl >> sh) + ((excl & low) != 0);
-            uint64_t k1 = (incl >> sh) + ((incl & low) != 0);
-            k1 = k1 < K ? k1 : K;
-            const uint64_t nk = i < d && k1 > k0 ? k1 - k0 : 0;
-            if (i < d) {
-                rec[b + i] = WalkEdge{incl, y, (uint32_t)x};
-                if (nk <= kGuideLaneFill)
-                    for (uint64_t k = k0; k < k1; ++k) G[k] = guide_bucket(k, sh, W, incl, incl + x1, (uint32_t)i, y, y1);
+        GuideEdges ahead[kGuidePer];
+        load_edges(w + b, col + b, d, 0, ahead);
+        for (int64_t base = 0; base < d; base += kGuidePer * kWave) {
+            GuideEdges at[kGuidePer];
+#pragma unroll
+            for (int q = 0; q < kGuidePer; ++q) at[q] = ahead[q];
+            load_edges(w + b, col + b, d, base + kGuidePer * kWave, ahead);
+#pragma unroll
+            for (int q = 0; q < kGuidePer; ++q) {
+                if (base + q * kWave >= d) break;
+                const int64_t i = base + q * kWave + lane;
+                const uint64_t x = at[q].x, x1 = at[q].x1;
+                const int32_t y = at[q].y, y1 = at[q].y1;
+                const uint64_t incl = run + wave_incl_scan_u64(x);
+                const uint64_t excl = incl - x;
+                const uint64_t k0 = (excl >> sh) + ((excl & low) != 0);
+                uint64_t k1 = (incl >> sh) + ((incl & low) != 0);
+                k1 = k1 < K ? k1 : K;
+                const uint64_t nk = i < d && k1 > k0 ? k1 - k0 : 0;
+                if (i < d) {
+                    rec[b + i] = WalkEdge{incl, y, (uint32_t)x};
+                    if (nk <= kGuideLaneFill)
+                        for (uint64_t k = k0; k < k1; ++k) G[k] = guide_bucket(k, sh, W, incl, incl + x1, (uint32_t)i, y, y1);
+                }
+                for (uint64_t wide = ballot(nk > kGuideLaneFill); wide; wide &= wide - 1) {
+                    const int src = __ffsll((unsigned long long)wide) - 1;
+                    const uint64_t a0 = readlane_u64(k0, src), a1 = readlane_u64(k1, src);
+                    const uint64_t si = readlane_u64(incl, src), sx = readlane_u64(x1, src);
+                    const int32_t sy = readlane_i32(y, src), sy1 = readlane_i32(y1, src);
+                    for (uint64_t k = a0 + lane; k < a1; k += kWave)
+                        G[k] = guide_bucket(k, sh, W, si, si + sx, (uint32_t)(base + q * kWave + src), sy, sy1);
+                }
+                run = readlane_u64(incl, kWave - 1);
             }
-            for (uint64_t wide = ballot(nk > kGuideLaneFill); wide; wide &= wide - 1) {
-                const int src = __ffsll((unsigned long long)wide) - 1;
-                const uint64_t a0 = readlane_u64(k0, src), a1 = readlane_u64(k1, src);
-                const uint64_t si = readlane_u64(incl, src), sx = readlane_u64(x1, src);
-                const int32_t sy = readlane_i32(y, src), sy1 = readlane_i32(y1, src);
-                for (uint64_t k = a0 + lane; k < a1; k += kWave)
-                    G[k] = guide_bucket(k, sh, W, si, si + sx, (uint32_t)(base + src), sy, sy1);
-            }
-            run = readlane_u64(incl, kWave - 1);
         }
     }
 }
