@@ -326,7 +326,7 @@ csaw_status csaw_walk(csaw_graph g, const csaw_walk_args* args, int32_t* paths,
  * built in a caller memory call) walks take the chunk tables with
  * one wavefront per walker, with the same paths. Sampling calls draw
  * through a weight array's guide when it is built and on (a walk or a server
- * builds it, or csaw_sample once its calls have sampled m / 4 edges by that
+ * builds it, or csaw_sample once its calls have sampled m edges by that
  * array, an edge drawn by csaw_layer_sample counting twice, and the tables fit
  * half of the free device memory), else from the
  * weights and the chunk tables: the same edges either way.

@@ -204,6 +204,7 @@ struct SampleLayer {
     int32_t rounds;                  // repeated-sampling rounds (0: every slot by direct draw)
     uint32_t burn;                   // forest fire threshold (0: fixed fanout)
     int32_t weighted;                // some instance draws by weight
+    bool wave_only = false;          // every instance does, by kinds without a guide, and no lane scans a list
     int32_t vlo, vhi;                // entries of vertices in [vlo, vhi) only (out-of-memory schedule)
 };
 

@@ -458,13 +458,13 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
 }
 
 // Sampling and layer sampling draw through the walk guide too, but do without it until
-// their weighted draws have paid for it: building it costs about what m / 4
-// sampled edges gain (R-MAT 22, 65M edges: 4 ms and 4 GB of allocations against
-// 0.2 ms per million edges), and it is left out where it would take more than
-// half of the device memory that is free. A failure leaves the chunk tables.
+// their weighted draws have paid for it: building it costs about what m sampled
+// edges gain (R-MAT 22, 65M edges: 6 ms and 5 GB of allocations against 0.1 to 0.2 ms
+// per million edges), and it is left out where it would take more than half of the
+// device memory that is free. A failure leaves the chunk tables.
 void guides_for_sampling(csaw_graph g, int32_t kind, hipStream_t s) {
     const std::atomic<int64_t>& drawn = kind == kNeighborDegree ? g->drawn_deg : g->drawn_ew;
-    if (!g->walk_guides.load() || drawn.load() < g->m / 4 || !free_device_bytes) return;
+    if (!g->walk_guides.load() || drawn.load() < g->m || !free_device_bytes) return;
     {
         std::lock_guard<std::mutex> lk(g->mu);
         if (kind == kNeighborDegree ? g->wgd_deg : g->wgd_ew) return;
@@ -1033,6 +1033,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         p.rounds = P.rounds;
         p.burn = a->burn_threshold;
         p.weighted = P.uses_deg || P.uses_ew;
+        p.wave_only = big_path && b16 <= 0 && b32 <= 0 && !(P.uses_deg && gd.wgd_deg) && !(P.uses_ew && gd.wgd_ew) &&
+                      std::none_of(P.bias.begin(), P.bias.end(), [](int32_t k) { return k == kUniform; });
         p.vlo = 0;  // every vertex (an out-of-memory schedule narrows it per partition)
         p.vhi = INT32_MAX;
         int computed_layers = 1;  // frontiers F_0 .. F_{computed_layers-1} exist

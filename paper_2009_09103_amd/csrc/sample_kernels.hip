@@ -1414,7 +1414,11 @@ __global__ void __launch_bounds__(kBlock, 5) k_select_slots(SampleLayer p) {
 // its prefix in registers. Each wavefront takes a contiguous share of the
 // frontier, loaded 64 entries at a time; a share holds few such entries when
 // the call is mixed, and the launch is left out when every weighted kind of
-// the call has its guide.
+// the call has its guide. kTake: the take-all lists too, where every instance
+// draws by such a kind and no list is scanned by a lane: the slot kernel would
+// have nothing else to do (8,192 seeds, 456,000 degree-biased edges on R-MAT 22: 0.252
+// ms a call with it, 0.233 without).
+template <bool kTake>
 __global__ void __launch_bounds__(kBlock) k_select_wave(SampleLayer p) {
     const int wid = uniform_i32(threadIdx.x / kWave);
     const int lane = lane_id();
@@ -1429,10 +1433,19 @@ __global__ void __launch_bounds__(kBlock) k_select_wave(SampleLayer p) {
         const int n = (int)(hi - e0 < kWave ? hi - e0 : kWave);
         EntryRun R;
         load_run(p, e0 + lane, lane < n, out_base, R);
-        uint64_t todo = ballot(R.c != 0 && R.o + R.c <= p.capacity && !slot_served(p, R) && R.d <= kWaveMaxD &&
-                               !(R.pinfo & kWideList));
+        if (kTake && R.c != 0 && R.o + R.c > p.capacity) p.ctl->overflow = 1;
+        uint64_t todo = ballot(R.c != 0 && R.o + R.c <= p.capacity &&
+                               (slot_served(p, R) ? kTake : R.d <= kWaveMaxD && !(R.pinfo & kWideList)));
         for (; todo; todo &= todo - 1) {
-            const EntryInfo E = run_entry(R, __ffsll((unsigned long long)todo) - 1);
+            const int i = __ffsll((unsigned long long)todo) - 1;
+            if (kTake && readlane_i32(R.k, i) < 0) {
+                const int32_t info = R.kind | kInfoTake | (R.do_claim ? kInfoClaim : 0) |
+                                     (R.kind != kUniform && (R.pinfo & ~kWideList) != R.d ? kInfoZeros : 0);
+                take_all_entry(p, readlane_i32(R.v, i), readlane_i32(R.inst, i), readlane_i32(info, i),
+                               readlane_i64(R.o, i), readlane_i64(R.beg, i), readlane_i32(R.d, i));
+                continue;
+            }
+            const EntryInfo E = run_entry(R, i);
             const Key key{(uint32_t)E.key, (uint32_t)(E.key >> 32)};
             const uint32_t* w = (E.kind == kEdgeWeight ? p.g.ew : p.g.degw) + E.beg;
             const uint32_t c1 = (uint32_t)p.layer, c2 = (uint32_t)E.v;
@@ -2105,7 +2118,8 @@ int64_t dirty_compact_blocks(int64_t summary_words) {
 }
 
 void launch_select(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev) {
-    launch_kernel(p.weighted ? k_select_slots<true> : k_select_slots<false>, dim3(grid), dim3(kBlock), s, ev, p);
+    launch_kernel(p.wave_only ? k_select_wave<true> : p.weighted ? k_select_slots<true> : k_select_slots<false>, dim3(grid),
+                  dim3(kBlock), s, ev, p);
 }
 
 void launch_layer_sample(const LayerParams& p, hipStream_t s, LaunchEvents ev) {
@@ -2128,7 +2142,7 @@ void launch_chunk_table(RowPtr rowptr, const uint32_t* w, int64_t n, uint64_t* t
 }
 
 void launch_select_big(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev) {
-    hipLaunchKernelGGL(k_select_wave, dim3(grid), dim3(kBlock), 0, s, p);
+    if (!p.wave_only) hipLaunchKernelGGL(k_select_wave<false>, dim3(grid), dim3(kBlock), 0, s, p);
     launch_kernel(k_select_big, dim3(grid), dim3(kBlock), s, ev, p);
 }
 
