@@ -902,6 +902,10 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     const std::vector<size_t>& o_fi = lay.o_fi;
     // weighted draws from lists without a walk guide
     const bool big_path = (P.uses_deg && !gd.wgd_deg) || (P.uses_ew && !gd.wgd_ew);
+    // every instance draws that way: it depends on the kinds themselves, which are no part of the call's shape
+    const bool wave_only = big_path && b16 <= 0 && b32 <= 0 && !(P.uses_deg && gd.wgd_deg) &&
+                           !(P.uses_ew && gd.wgd_ew) &&
+                           std::none_of(P.bias.begin(), P.bias.end(), [](int32_t k) { return k == kUniform; });
     const size_t o_hctl = align_up(tab_bytes, 64);
     Workspace* ws = nullptr;
     char* A = nullptr;
@@ -1033,8 +1037,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         p.rounds = P.rounds;
         p.burn = a->burn_threshold;
         p.weighted = P.uses_deg || P.uses_ew;
-        p.wave_only = big_path && b16 <= 0 && b32 <= 0 && !(P.uses_deg && gd.wgd_deg) && !(P.uses_ew && gd.wgd_ew) &&
-                      std::none_of(P.bias.begin(), P.bias.end(), [](int32_t k) { return k == kUniform; });
+        p.wave_only = wave_only;
         p.vlo = 0;  // every vertex (an out-of-memory schedule narrows it per partition)
         p.vhi = INT32_MAX;
         int computed_layers = 1;  // frontiers F_0 .. F_{computed_layers-1} exist
@@ -1131,6 +1134,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                 key.push_back((int64_t)(intptr_t)q);
             key.push_back((int64_t)P.uses_deg);
             key.push_back((int64_t)P.uses_ew);
+            key.push_back((int64_t)wave_only);  // chooses the kernels
             hipGraphExec_t exec = ws->find_graph(key);
             if (!exec) {
                 HIP_OR_FAIL(hipStreamBeginCapture(ws->capture, hipStreamCaptureModeRelaxed));

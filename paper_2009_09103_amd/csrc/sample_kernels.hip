@@ -1435,7 +1435,7 @@ __global__ void __launch_bounds__(kBlock) k_select_wave(SampleLayer p) {
         load_run(p, e0 + lane, lane < n, out_base, R);
         if (kTake && R.c != 0 && R.o + R.c > p.capacity) p.ctl->overflow = 1;
         uint64_t todo = ballot(R.c != 0 && R.o + R.c <= p.capacity &&
-                               (slot_served(p, R) ? kTake : R.d <= kWaveMaxD && !(R.pinfo & kWideList)));
+                               (slot_served(p, R) ? kTake && R.k < 0 : R.d <= kWaveMaxD && !(R.pinfo & kWideList)));
         for (; todo; todo &= todo - 1) {
             const int i = __ffsll((unsigned long long)todo) - 1;
             if (kTake && readlane_i32(R.k, i) < 0) {
