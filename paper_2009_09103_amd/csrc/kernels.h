@@ -131,7 +131,10 @@ struct SampleCtl {
     int32_t bad_seed;
     int32_t overflow;
     int32_t unsupported;
-    int32_t lookback_stuck;
+    int32_t lookback_stuck;  // a frontier build gave up its chain: entries at unknown positions
+    int32_t list_stuck;      // a compaction did: its dirty list has holes (written by compactions alone, so that the
+                             // build behind one reads the same value in every wavefront)
+    __host__ __device__ bool gave_up() const { return (lookback_stuck | list_stuck) != 0; }
     uint32_t tickets[kMaxLayers + 1][2];  // blocks started, per frontier build: its own, its compaction's
 };
 
@@ -139,6 +142,8 @@ static_assert(sizeof(SampleCtl) % 4 == 0, "control block is copied in 32-bit wor
 
 // One frontier build: next bitmap -> sorted frontier entries with their edge
 // counts, edge offsets, kernel routes and per-instance segment offsets.
+constexpr uint32_t kSpinLimit = 1u << 20;       // half a second, in order
+constexpr uint32_t kSpinLimitIndex = 1u << 15;  // 17 ms, by block index
 struct FrontierBuild {
     GraphDev g;
     uint32_t* next;
@@ -172,6 +177,7 @@ struct FrontierBuild {
     int64_t* dirty;                  // [frontier capacity]
     int64_t nb_dirty;                // blocks of the compaction
     bool ordered = false;            // blocks take tickets (a call whose chain gave up by block index)
+    uint32_t spins = 0;              // looks at a predecessor that has published nothing (0: none, every block gives up)
 };
 
 struct SampleLayer {

@@ -197,6 +197,15 @@ bool graphs_enabled() {
     return on;
 }
 
+// Looks that a frontier build's chain by block index takes at a block that has
+// published nothing before the call runs again in order. CSAW_CHAIN_SPINS in the
+// environment of csaw_graph_create sets another number for that graph's calls; with
+// 0 every build of more than one block gives up, which takes the second try.
+uint32_t first_spins() {
+    const char* e = std::getenv("CSAW_CHAIN_SPINS");
+    return e && *e ? (uint32_t)std::strtoul(e, nullptr, 10) : kSpinLimitIndex;
+}
+
 struct Carver {
     size_t off = 0;
     template <class T>
@@ -245,6 +254,7 @@ struct csaw_graph_s {
     std::atomic<int32_t> walk_guides{1};  // weighted walks build and use the walk guides
     std::atomic<int64_t> drawn_ew{0}, drawn_deg{0};  // edges that sampling calls drew, per weight array
     std::atomic<int64_t> hopped{0};                  // unbiased steps asked for (see prepare_hops)
+    uint32_t chain_spins = first_spins();
 
     GraphDev dev() const {
         std::lock_guard<std::mutex> lk(mu);  // a table may be appearing under another call
@@ -998,6 +1008,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         fb.ctl = ctl;
         fb.status = d_status;
         fb.ordered = ordered;
+        fb.spins = ordered ? kSpinLimit : g->chain_spins;
         auto build = [&](int32_t l, LaunchEvents ev) {
             fb.layer = l;
             fb.fanout = d_fan + (size_t)l * ni;
@@ -1157,7 +1168,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         }
         HIP_OR_FAIL(hipStreamSynchronize(s));
     }
-    if (h_ctl->lookback_stuck && !ordered) {  // beside other calls' builds: once more, in order
+    if (h_ctl->gave_up() && !ordered) {  // beside other calls' builds: once more, in order
         ordered = true;
         launch_fill_u32(bitmaps, 0u, lay.bitmap_words, s);
         if ((st = enqueue(s)) != CSAW_OK) return st;
@@ -1167,7 +1178,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     // a frontier build that gave up its look-back wrote entries at unknown
     // positions, so the bitmaps may not be clean: the workspace is dropped
     // (Lease) instead of going back to the pool
-    if (h_ctl->lookback_stuck) return fail(CSAW_ERR_DEVICE, "frontier build did not complete its block chain");
+    if (h_ctl->gave_up()) return fail(CSAW_ERR_DEVICE, "frontier build did not complete its block chain");
     rel.clean = true;
     out->num_edges = L > 0 ? h_ctl->out_base[L] : 0;
     if (out->num_edges < 0) return fail(CSAW_ERR_DEVICE, "the device reported a negative edge count");

@@ -200,8 +200,6 @@ __device__ __forceinline__ int64_t chunks_of(int64_t d) { return (d + kChunk - 1
 // in one 64-bit word, so a reader never sees a value without its flag.
 constexpr uint64_t kStatusValid = 1ull << 48;
 constexpr uint64_t kStatusMask = kStatusValid - 1;
-constexpr uint32_t kSpinLimit = 1u << 20;       // half a second, in order
-constexpr uint32_t kSpinLimitIndex = 1u << 15;  // 17 ms, by block index
 
 __device__ __forceinline__ uint64_t status_pack(int64_t v, uint32_t epoch) {
     return ((uint64_t)v & kStatusMask) | kStatusValid | ((uint64_t)(epoch & 0x7FFF) << 49);
@@ -218,7 +216,7 @@ __device__ __forceinline__ uint64_t status_load(unsigned long long* p) {
 
 // Entries of a layer's frontier; none where a build gave up, whose entries are not whole.
 __device__ __forceinline__ int64_t frontier_size(const SampleCtl* ctl, int32_t layer) {
-    return ctl->lookback_stuck ? 0 : ctl->fcount[layer];
+    return ctl->gave_up() ? 0 : ctl->fcount[layer];
 }
 
 // Next set bit of a word (cleared from it), or -1.
@@ -251,11 +249,11 @@ __device__ __forceinline__ int64_t chain_place(uint32_t* tickets, bool ordered) 
 // predecessors' published values 64 blocks at a time, nearest first; a
 // predecessor's inclusive prefix ends the walk (predecessors run or are done:
 // chain_place). The spin is bounded and
-// reports through *stuck instead of hanging. Publishes b's inclusive prefix
-// and returns the exclusive ones (every lane).
+// reports through *stuck instead of hanging; the prefixes are then those of the
+// nearer predecessors, so positions formed from them are too small and stay inside
+// their arrays. Publishes b's inclusive prefix and returns the exclusive ones (every lane).
 __device__ __forceinline__ void lookback2(unsigned long long* status, int64_t b, int64_t tot_a, int64_t tot_c,
-                                          uint32_t epoch, bool ordered, int32_t* stuck, int64_t& pa, int64_t& pc) {
-    const uint32_t limit = ordered ? kSpinLimit : kSpinLimitIndex;
+                                          uint32_t epoch, uint32_t limit, int32_t* stuck, int64_t& pa, int64_t& pc) {
     const int lane = lane_id();
     unsigned long long* st = status + 4 * b;
     if (b > 0 && lane == 0) {
@@ -288,7 +286,7 @@ __device__ __forceinline__ void lookback2(unsigned long long* status, int64_t b,
             }
         }
         const uint64_t incl = ballot(flag == 2);
-        const uint64_t notready = ballot(flag == 0);
+        const uint64_t notready = ballot(flag == 0 || limit == 0);
         const int first = incl ? __ffsll((unsigned long long)incl) - 1 : kWave;  // nearest inclusive
         const uint64_t upto = first >= kWave - 1 ? ~0ull : ((2ull << first) - 1);
         if (notready & upto) {  // a nearer predecessor has published nothing yet
@@ -359,7 +357,7 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
     // (grid sized by capacity, blocks past the list end at once)
     int64_t nwords = fb.nwords, nb = fb.nb;
     if (kSparse) {
-        if (fb.ctl->lookback_stuck) return;  // the list is not whole
+        if (fb.ctl->list_stuck) return;  // the list is not whole (uniform: no block of this launch writes it)
         nwords = fb.ctl->ndirty[fb.layer];
         nb = nwords > 0 ? (nwords + kBlock - 1) / kBlock : 1;
         if (blockIdx.x >= nb) return;
@@ -412,7 +410,7 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
     if (tid < kWave) {  // wave 0: publish, then look back 64 predecessors per step
         int64_t pe = 0, pg = 0;
         lookback2(fb.status, b, tot_e, tot_g, kSparse ? 2u * fb.layer + 2u : (uint32_t)fb.layer + 1u,
-                  fb.ordered, &fb.ctl->lookback_stuck, pe, pg);
+                  fb.spins, &fb.ctl->lookback_stuck, pe, pg);
         if (tid == 0) {
             s_base_e = pe;
             s_base_g = pg;
@@ -501,7 +499,7 @@ __global__ void __launch_bounds__(kBlock) k_dirty_compact(FrontierBuild fb) {
     block_excl_scan4(cnt4, tot4);
     if (tid < kWave) {
         int64_t pa = 0, pc = 0;
-        lookback2(fb.status, b, tot4[0], 0, 2u * fb.layer + 1u, fb.ordered, &fb.ctl->lookback_stuck, pa, pc);
+        lookback2(fb.status, b, tot4[0], 0, 2u * fb.layer + 1u, fb.spins, &fb.ctl->list_stuck, pa, pc);
         if (tid == 0) s_base = pa;
     }
     __syncthreads();
@@ -1651,7 +1649,7 @@ __global__ void __launch_bounds__(kBlock) k_select_big(SampleLayer p) {
     __shared__ uint64_t tabs[kWavesPerBlock][kBigTab + 1];
     const int wid = uniform_i32(threadIdx.x / kWave);
     const int lane = lane_id();
-    const int64_t nb = p.ctl->lookback_stuck ? 0 : (int64_t)p.ctl->nbig[p.layer];
+    const int64_t nb = p.ctl->gave_up() ? 0 : (int64_t)p.ctl->nbig[p.layer];
     const int64_t out_base = p.ctl->out_base[p.layer];
     const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
     const int64_t wave = blockIdx.x * (int64_t)kWavesPerBlock + wid;
