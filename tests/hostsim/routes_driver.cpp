@@ -4,12 +4,17 @@
 //   driver replay     calls of one shape and one set of buffers whose instances
 //                     change their bias kinds: a captured launch sequence
 //                     serves only calls of the kernels that it holds
+//   driver retry      frontier builds that give up their chain: the call runs
+//                     again in order, pooled and in caller memory, and leaves a
+//                     clean workspace
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
 
 namespace hipsim_hooks {
-extern std::atomic<int64_t> misrouted;
+extern std::atomic<int64_t> misrouted, in_order;
+extern std::atomic<int32_t> stuck_layer;
+extern std::atomic<bool> stuck_list;
 }  // namespace hipsim_hooks
 
 namespace {
@@ -53,9 +58,9 @@ struct Call {
         a.rng_seed = 7;
         return a;
     }
-    void check(const Host& h, csaw_graph g, const std::vector<int32_t>& bias, hipStream_t s) {
+    void check(const Host& h, csaw_graph g, const std::vector<int32_t>& bias, hipStream_t s, bool noalloc = false) {
         csaw_sample_args a = args(bias);
-        OK(csaw_sample(g, &a, &out, s));
+        OK(noalloc ? csaw_sample_noalloc(g, &a, &out, s) : csaw_sample(g, &a, &out, s));
         Edges e;
         e.src.assign(out.src, out.src + out.num_edges);
         e.dst.assign(out.dst, out.dst + out.num_edges);
@@ -85,11 +90,38 @@ void scenario_replay() {
     (void)hipStreamDestroy(s);
 }
 
+void scenario_retry() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_graph(1 << 12, 16 << 12, 33);
+    Dev d = upload(h, s);
+    Call c(h, d.g, 6, 20, {5, 3, 2}), other(h, d.g, 2, 30, {4, 4, 3});
+    for (int32_t kind : {CSAW_BIAS_UNIFORM, CSAW_BIAS_EDGE_WEIGHT}) {
+        const std::vector<int32_t> bias(6, kind);
+        c.check(h, d.g, bias, s, true);
+        for (int32_t layer = 0; layer < 3; ++layer)
+            for (bool list : {false, true})
+                for (bool noalloc : {false, true}) {
+                    hipsim_hooks::stuck_list = list;
+                    hipsim_hooks::stuck_layer = layer;
+                    hipsim_hooks::in_order = 0;
+                    c.check(h, d.g, bias, s, noalloc);
+                    CHECK(hipsim_hooks::in_order.load() == 3);
+                    hipsim_hooks::stuck_layer = -1;
+                    other.check(h, d.g, std::vector<int32_t>(2, kind), s, noalloc);  // the same workspace
+                    CHECK(hipsim_hooks::in_order.load() == 3);
+                }
+    }
+    OK(csaw_graph_destroy(d.g));
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "replay") scenario_replay();
+    else if (what == "retry") scenario_retry();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;

@@ -4,11 +4,16 @@
 #include "../../paper_2009_09103_amd/csrc/kernels.h"
 
 #define launch_select placeholder_select
+#define launch_frontier_build placeholder_build
 #include "kernels_sim.cpp"
 #undef launch_select
+#undef launch_frontier_build
 
 namespace hipsim_hooks {
 std::atomic<int64_t> misrouted{0};  // unbiased draws given to the kernel that draws by weight alone
+std::atomic<int32_t> stuck_layer{-1};  // builds of this layer give up their chain by block index ...
+std::atomic<bool> stuck_list{false};   // ... in the compaction
+std::atomic<int64_t> in_order{0};      // builds whose blocks take tickets
 }  // namespace hipsim_hooks
 
 namespace csaw {
@@ -23,6 +28,19 @@ void launch_select(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents e
         }
     });
     placeholder_select(p, grid, s, ev);
+}
+
+// A build that gives up leaves bits behind that the second try must not see.
+void launch_frontier_build(const FrontierBuild& fb, hipStream_t s, LaunchEvents ev) {
+    placeholder_build(fb, s, ev);
+    hipsim::enqueue(s, [fb] {
+        if (fb.ordered) {
+            ++hipsim_hooks::in_order;
+        } else if (fb.layer == hipsim_hooks::stuck_layer.load()) {
+            (hipsim_hooks::stuck_list.load() ? fb.ctl->list_stuck : fb.ctl->lookback_stuck) = 1;
+            std::fill(fb.visited, fb.visited + fb.nwords, 0x55555555u);
+        }
+    });
 }
 
 }  // namespace csaw
