@@ -7,12 +7,16 @@
 //   driver retry      frontier builds that give up their chain: the call runs
 //                     again in order, pooled and in caller memory, and leaves a
 //                     clean workspace
+//   driver tables     the guides, the hop table and the rank index appear under
+//                     calls of four threads, and are left out where memory is
+//                     short; every call gives the same results
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
 
 namespace hipsim_hooks {
-extern std::atomic<int64_t> misrouted, in_order;
+extern std::atomic<int64_t> misrouted, in_order, queries, guides, hops, ranks, with_guide, with_hops, with_rank;
+extern std::atomic<size_t> device_limit;
 extern std::atomic<int32_t> stuck_layer;
 extern std::atomic<bool> stuck_list;
 }  // namespace hipsim_hooks
@@ -116,12 +120,155 @@ void scenario_retry() {
     (void)hipStreamDestroy(s);
 }
 
+// An undirected graph (lists sorted, weights out-degrees) with lists of more than 64 entries.
+Host make_symmetric(int64_t n, int64_t draws, uint64_t seed) {
+    Host h = make_graph(n, draws, seed);
+    std::vector<std::set<int32_t>> adj(n);
+    for (int64_t u = 0; u < n; ++u)
+        for (int64_t e = h.rp[u]; e < h.rp[u + 1]; ++e) {
+            adj[u].insert(h.col[e]);
+            adj[h.col[e]].insert((int32_t)u);
+        }
+    h.col.clear();
+    for (int64_t u = 0; u < n; ++u) {
+        h.rp[u + 1] = h.rp[u] + (int64_t)adj[u].size();
+        h.col.insert(h.col.end(), adj[u].begin(), adj[u].end());
+    }
+    h.ew.assign(h.col.size(), 0);
+    for (size_t e = 0; e < h.col.size(); ++e) h.ew[e] = (uint32_t)(h.rp[h.col[e] + 1] - h.rp[h.col[e]]);
+    return h;
+}
+
+// A device limit that hipMalloc and the library's own query agree on (0: none).
+void limit_device(size_t bytes) {
+    hipsim::set_device_limit(bytes);
+    hipsim_hooks::device_limit = bytes;
+}
+
+struct Walks {
+    std::vector<int32_t> starts;
+    int32_t* dstarts = nullptr;
+    int32_t* paths = nullptr;
+    int32_t length;
+
+    Walks(const Host& h, int64_t walkers, int32_t len, uint64_t seed) : starts(pick_seeds(h, walkers, seed)), length(len) {
+        dstarts = dev_copy(starts);
+        paths = dev_copy(std::vector<int32_t>(starts.size() * (length + 1), -1));
+    }
+    ~Walks() {
+        (void)hipFree(dstarts);
+        (void)hipFree(paths);
+    }
+    void check(const Host& h, csaw_graph g, int32_t kind, hipStream_t s) {
+        csaw_walk_args w{};
+        w.bias_kind = kind;
+        w.num_walkers = (int64_t)starts.size();
+        w.starts = dstarts;
+        w.length = length;
+        w.rng_seed = 5;
+        w.w_return = 1;
+        w.w_common = 2;
+        w.w_outward = 4;
+        int64_t steps = 0, count = 0;
+        OK(csaw_walk(g, &w, paths, &steps, s));
+        for (size_t k = 0; k < starts.size(); ++k)
+            for (int32_t t = 0; t < length; ++t) {
+                const int32_t u = paths[k * (length + 1) + t], v = paths[k * (length + 1) + t + 1];
+                if (v < 0) break;
+                CHECK(std::binary_search(h.col.begin() + h.rp[u], h.col.begin() + h.rp[u + 1], v));
+                ++count;
+            }
+        CHECK(count == steps);
+    }
+};
+
+// One call of every kind that may build or use a table.
+struct Client {
+    const Host& h;
+    csaw_graph g;
+    hipStream_t s = nullptr;
+    Call call;
+    Walks walks;
+    std::vector<int64_t> offs{0, 40, 80};
+    int32_t* pool;
+    int32_t* out[3];
+
+    Client(const Host& hh, csaw_graph gg, uint64_t seed) : h(hh), g(gg), call(hh, gg, 4, 40, {10, 5}), walks(hh, 200, 30, seed) {
+        CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+        const std::vector<int32_t> one = pick_seeds(h, 40, seed + 1);
+        std::vector<int32_t> two = one;
+        two.insert(two.end(), one.begin(), one.end());
+        pool = dev_copy(two);
+        for (auto& o : out) o = dev_copy(std::vector<int32_t>(2 * 64, 0));
+    }
+    ~Client() {
+        (void)hipFree(pool);
+        for (auto* o : out) (void)hipFree(o);
+        (void)hipStreamDestroy(s);
+    }
+    void round() {
+        for (int32_t kind : {CSAW_BIAS_EDGE_WEIGHT, CSAW_BIAS_NEIGHBOR_DEGREE}) {
+            call.check(h, g, std::vector<int32_t>(4, kind), s);
+            csaw_layer_args a{};
+            a.num_instances = 2;
+            a.seed_offsets = offs.data();
+            a.seeds = pool;
+            a.num_layers = 1;
+            const int32_t fan = 64;
+            a.fanouts = &fan;
+            a.bias_kind = kind;
+            OK(csaw_layer_sample(g, &a, out[0], out[1], out[2], s));
+        }
+        for (int32_t kind : {CSAW_BIAS_UNIFORM, CSAW_BIAS_NODE2VEC, CSAW_BIAS_EDGE_WEIGHT}) walks.check(h, g, kind, s);
+        csaw_mdrw_args a{};
+        a.num_instances = 2;
+        a.pool_offsets = offs.data();
+        a.pool = pool;
+        a.budget = 64;
+        int64_t total = 0;
+        OK(csaw_mdrw(g, &a, out[0], out[1], nullptr, &total, s));
+    }
+};
+
+void scenario_tables() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_symmetric(1 << 10, 6 << 10, 35);
+    {
+        Dev d = upload(h, s);
+        std::vector<std::thread> threads;
+        for (int t = 0; t < 4; ++t)
+            threads.emplace_back([&, t] {
+                Client c(h, d.g, 40 + t);
+                for (int rep = 0; rep < 12; ++rep) c.round();
+            });
+        for (auto& t : threads) t.join();
+        CHECK(hipsim_hooks::guides.load() == 2 && hipsim_hooks::hops.load() == 1 && hipsim_hooks::ranks.load() == 1);
+        CHECK(hipsim_hooks::with_guide.load() > 0 && hipsim_hooks::with_hops.load() > 0 && hipsim_hooks::with_rank.load() > 0);
+        OK(csaw_graph_destroy(d.g));
+    }
+    {
+        Dev d = upload(h, s);
+        OK(csaw_set_walk_guides(d.g, 0));  // weighted walks through the chunk tables
+        Client c(h, d.g, 50);
+        c.round();
+        hipsim_hooks::guides = hipsim_hooks::hops = hipsim_hooks::ranks = 0;
+        limit_device(hipsim::device_bytes_in_use() + (size_t(4) << 10));
+        for (int rep = 0; rep < 12; ++rep) c.round();
+        CHECK(hipsim_hooks::guides.load() == 0 && hipsim_hooks::hops.load() == 0 && hipsim_hooks::ranks.load() == 0);
+        limit_device(0);
+        OK(csaw_graph_destroy(d.g));
+    }
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "replay") scenario_replay();
     else if (what == "retry") scenario_retry();
+    else if (what == "tables") scenario_tables();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;

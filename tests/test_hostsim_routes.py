@@ -1,6 +1,6 @@
 """The routes that the runtime picks for a call, on the host-only build of the
 library (tests/hostsim): launchers that note calls given to a kernel that
-cannot serve them, under AddressSanitizer + UBSan and under ThreadSanitizer."""
+cannot serve them and read the tables that they are given, under AddressSanitizer + UBSan and under ThreadSanitizer."""
 import os
 import shutil
 
@@ -21,7 +21,7 @@ def drivers(tmp_path_factory):
         return {k: sim.build(k, out) for k in sim.FLAGS}
 
 
-@pytest.mark.parametrize("scenario", ["replay", "retry"])
+@pytest.mark.parametrize("scenario", ["replay", "retry", "tables"])
 @pytest.mark.parametrize("kind", ["asan", "tsan"])
 def test_routes_under_sanitizers(drivers, kind, scenario):
     sim.run(drivers[kind], scenario)
