@@ -2021,8 +2021,15 @@ csaw_status prepare_bias_tables(csaw_graph g, int32_t kind, hipStream_t stream) 
     if (kind == kEdgeWeight && !g->ew) return fail(CSAW_ERR_INVALID_ARG, "EDGE_WEIGHT bias without edge weights");
     if (kind != kEdgeWeight && kind != kNeighborDegree) return CSAW_OK;
     HIP_OR_FAIL(hipSetDevice(g->device));
-    const csaw_status st = prepare_bias(g, kind, stream);
-    return st != CSAW_OK || !g->walk_guides.load() ? st : prepare_walk_guides(g, kind, stream);
+    return prepare_bias(g, kind, stream);
+}
+
+void prepare_guides(csaw_graph g, int32_t kind, hipStream_t stream) {
+    {
+        std::lock_guard<std::mutex> lk(g->mu);
+        if (!g->walk_guides.load() || !(kind == kNeighborDegree ? g->ppos_deg : g->ppos_ew)) return;
+    }
+    if (prepare_walk_guides(g, kind, stream) != CSAW_OK) t_err.clear();
 }
 
 }  // namespace csaw

@@ -750,10 +750,13 @@ csaw_status csaw_server_create(csaw_graph g, const csaw_server_config* cfg, csaw
     // edge-weight and degree tables are built before serving, so that no
     // request builds them (and allocates) while others run
     if (st == CSAW_OK && !s->execs.empty()) {
-        // (edge weights, which served walks draw by, first: the later tables
-        // take their compact form where memory is short)
-        (void)csaw::prepare_bias_tables(g, CSAW_BIAS_EDGE_WEIGHT, s->execs[0].st);
         st = csaw::prepare_bias_tables(g, CSAW_BIAS_NEIGHBOR_DEGREE, s->execs[0].st);
+        if (st == CSAW_OK) (void)csaw::prepare_bias_tables(g, CSAW_BIAS_EDGE_WEIGHT, s->execs[0].st);
+        // then the guides, which requests do without where memory is short:
+        // edge weights, which served walks draw by, first
+        if (st == CSAW_OK)
+            for (int32_t kind : {CSAW_BIAS_EDGE_WEIGHT, CSAW_BIAS_NEIGHBOR_DEGREE})
+                csaw::prepare_guides(g, kind, s->execs[0].st);
     }
     if (st != CSAW_OK) {
         s->free_execs();

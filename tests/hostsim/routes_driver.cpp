@@ -10,6 +10,7 @@
 //   driver tables     the guides, the hop table and the rank index appear under
 //                     calls of four threads, and are left out where memory is
 //                     short; every call gives the same results
+//   driver room       a server on a device with room for one walk guide, or none
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
@@ -262,6 +263,33 @@ void scenario_tables() {
     (void)hipStreamDestroy(s);
 }
 
+// A server needs its executors' memory and the degree tables; the walk guides are built where they fit.
+void scenario_room() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_symmetric(1 << 12, 16 << 12, 36);
+    const size_t n = (size_t)h.n, m = h.col.size();
+    const size_t degree = 4 * m + 12 * n + (m / 512 + 1) * (64 + 1) * 8;  // weights, counts, totals, chunk tables
+    const size_t guide = 16 * m + 16 * n + 16 * (2 * m + n);              // two buckets per edge
+    for (const int fit : {1, 2, 0}) {
+        Dev d = upload(h, s);
+        auto trace = make_trace(h, 12, 60, 300, 12, 37);
+        csaw_server_config cfg{};
+        cfg.memory_budget_bytes = int64_t(8) << 20;
+        cfg.num_streams = 2;
+        hipsim_hooks::guides = 0;
+        limit_device(hipsim::device_bytes_in_use() + (size_t)cfg.memory_budget_bytes + degree + fit * guide + guide / 2);
+        csaw_server srv = nullptr;
+        OK(csaw_server_create(d.g, &cfg, &srv));
+        CHECK(hipsim_hooks::guides.load() == fit);
+        limit_device(0);  // (the checks below make calls of their own)
+        run_trace(d, srv, trace, 1, s);
+        OK(csaw_server_destroy(srv));
+        OK(csaw_graph_destroy(d.g));
+    }
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -269,6 +297,7 @@ int main(int argc, char** argv) {
     if (what == "replay") scenario_replay();
     else if (what == "retry") scenario_retry();
     else if (what == "tables") scenario_tables();
+    else if (what == "room") scenario_room();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;
