@@ -330,6 +330,11 @@ csaw_status csaw_walk(csaw_graph g, const csaw_walk_args* args, int32_t* paths,
  * array, an edge drawn by csaw_layer_sample counting twice, and the tables fit
  * half of the free device memory), else from the
  * weights and the chunk tables: the same edges either way.
+ * Tables that calls built to draw faster -- the guides, and the hop table and
+ * rank index of csaw_walk -- are given back when a call, a graph or a server
+ * of the library cannot get its device memory otherwise. The graph's calls then
+ * do without: of these only walk guides are built again, with two buckets per
+ * edge. A weighted walk whose guide does not fit takes the chunk tables.
  * enable: 1 (default) or 0. A walk already running keeps its route. INVALID_ARG
  * otherwise. Turning the guide off does not free built tables. */
 csaw_status csaw_set_walk_guides(csaw_graph g, int32_t enable);
@@ -448,8 +453,9 @@ csaw_status csaw_sample_streamed(csaw_pgraph g, const csaw_sample_args* args, cs
 
 /* Device scratch of the calls (each graph's workspaces: per-call frontier and
  * edge-count arrays, instance bitmaps) comes from alloc_fn (bytes, user),
- * which returns a device pointer or NULL (the call then fails with
- * OUT_OF_MEMORY); a buffer is returned with the free_fn that was set when it
+ * which returns a device pointer or NULL (it is asked again if the device's
+ * graphs held tables that they could give back, csaw_set_walk_guides; else the
+ * call fails with OUT_OF_MEMORY); a buffer is returned with the free_fn that was set when it
  * was allocated, once no work uses it (at a workspace's growth or at
  * csaw_graph_destroy), so a pair must stay valid until every graph that used
  * it is destroyed. Both NULL (the default): hipMalloc / hipFree. The graph's

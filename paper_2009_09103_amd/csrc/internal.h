@@ -12,6 +12,10 @@
 
 namespace csaw {
 
+// hipMalloc; where it fails, the tables that the device's graphs can do without
+// are freed and it is tried again (for callers without a graph's lock).
+hipError_t device_malloc(void** p, size_t bytes);
+
 // Device bytes of a walk call's counters in caller scratch.
 constexpr size_t kWalkScratch = 512;
 

@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -109,6 +110,11 @@ struct DevAllocator {
 std::mutex g_alloc_mu;
 DevAllocator g_alloc;
 
+// Frees the tables that graphs of the current device can do without, where
+// that leaves `bytes` free; false if it freed nothing. For a caller without such
+// a table or a graph's lock.
+bool give_back(size_t bytes);
+
 hipError_t dev_alloc(DevAllocator& from, void** p, size_t bytes) {
     DevAllocator a;
     {
@@ -116,8 +122,12 @@ hipError_t dev_alloc(DevAllocator& from, void** p, size_t bytes) {
         a = g_alloc;
     }
     from = a;
-    if (!a.alloc) return hipMalloc(p, bytes);
+    if (!a.alloc) return device_malloc(p, bytes);
     *p = a.alloc(bytes, a.user);
+    if (!*p && give_back(0)) {
+        (void)hipGetLastError();
+        *p = a.alloc(bytes, a.user);
+    }
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 
@@ -216,6 +226,40 @@ struct Carver {
     }
 };
 
+// Tables of a graph that calls draw faster with and can do without: built by
+// calls, read by those that took them (TableUse), freed with the graph or where
+// device memory is short (give_back).
+struct Tables {
+    WalkEdge* wrec_ew = nullptr;   // walk guides: per-edge prefixes and neighbors,
+    WalkEdge* wrec_deg = nullptr;  // per-vertex lists and totals, bucket brackets
+    WalkVertex* wvtx_ew = nullptr;
+    WalkVertex* wvtx_deg = nullptr;
+    WalkBucket* wgd_ew = nullptr;
+    WalkBucket* wgd_deg = nullptr;
+    int32_t gper_ew = kGuideBucketsPerEdge, gper_deg = kGuideBucketsPerEdge;
+    WalkHop* hops = nullptr;       // hop table of unbiased steps
+    uint32_t* rank = nullptr;      // rank index of the lists (node2vec)
+    int32_t repeats = 0;           // some list holds a neighbor more than once (known with rank)
+    size_t bytes = 0;              // of all of them
+    int64_t users = 0;             // calls that hold them
+
+    ~Tables() {
+        for (void* q : {(void*)wrec_ew, (void*)wrec_deg, (void*)wvtx_ew, (void*)wvtx_deg, (void*)wgd_ew,
+                        (void*)wgd_deg, (void*)hops, (void*)rank})
+            if (q) (void)hipFree(q);
+    }
+};
+
+// Every graph, for give_back (never destroyed: graphs may outlive static objects).
+struct Registry {
+    std::mutex mu;
+    std::vector<csaw_graph> graphs;
+};
+Registry& registry() {
+    static Registry* const r = new Registry();
+    return *r;
+}
+
 }  // namespace
 
 struct csaw_graph_s {
@@ -238,17 +282,10 @@ struct csaw_graph_s {
     uint64_t* wtot_deg = nullptr;
     uint64_t* ctab_ew = nullptr;   // running chunk totals of the long lists
     uint64_t* ctab_deg = nullptr;
-    WalkEdge* wrec_ew = nullptr;   // walk guides: per-edge prefixes and neighbors,
-    WalkEdge* wrec_deg = nullptr;  // per-vertex lists and totals, bucket brackets
-    WalkVertex* wvtx_ew = nullptr;
-    WalkVertex* wvtx_deg = nullptr;
-    WalkBucket* wgd_ew = nullptr;
-    WalkBucket* wgd_deg = nullptr;
-    int32_t gper_ew = kGuideBucketsPerEdge, gper_deg = kGuideBucketsPerEdge;
-    WalkHop* hops = nullptr;       // hop table of unbiased steps
-    uint32_t* rank = nullptr;      // rank index of the lists (node2vec)
-    int32_t repeats = 0;           // some list holds a neighbor more than once (known with rank)
-    mutable std::mutex mu;               // lazy preparation + workspace pool
+    Tables* tables = new Tables();
+    bool lean = false;             // tables were given back: only walk guides are built again
+    std::mutex mu;                 // lazy preparation + workspace pool
+    std::condition_variable idle;  // a call let go of its tables
     std::vector<Workspace*> pool;
     std::atomic<int32_t> bound16{kDefaultBound16}, bound32{kDefaultBound32};  // sub-wave buckets
     std::atomic<int32_t> walk_guides{1};  // weighted walks build and use the walk guides
@@ -256,8 +293,21 @@ struct csaw_graph_s {
     std::atomic<int64_t> hopped{0};                  // unbiased steps asked for (see prepare_hops)
     uint32_t chain_spins = first_spins();
 
-    GraphDev dev() const {
-        std::lock_guard<std::mutex> lk(mu);  // a table may be appearing under another call
+    csaw_graph_s() {
+        std::lock_guard<std::mutex> lk(registry().mu);
+        registry().graphs.push_back(this);
+    }
+    ~csaw_graph_s() {
+        {
+            std::lock_guard<std::mutex> lk(registry().mu);
+            auto& all = registry().graphs;
+            all.erase(std::find(all.begin(), all.end(), this));
+        }
+        delete tables;
+    }
+
+    // The device view, with the tables t (under mu: one may be appearing under another call).
+    GraphDev dev(const Tables& t) const {
         GraphDev g;
         g.n = n;
         g.m = m;
@@ -273,17 +323,17 @@ struct csaw_graph_s {
         g.wtot_deg = wtot_deg;
         g.ctab_ew = ctab_ew;
         g.ctab_deg = ctab_deg;
-        g.wrec_ew = wrec_ew;
-        g.wrec_deg = wrec_deg;
-        g.wvtx_ew = wvtx_ew;
-        g.wvtx_deg = wvtx_deg;
-        g.wgd_ew = wgd_ew;
-        g.wgd_deg = wgd_deg;
-        g.gper_ew = gper_ew;
-        g.gper_deg = gper_deg;
-        g.hops = hops;
-        g.rank = rank;
-        g.repeats = repeats;
+        g.wrec_ew = t.wrec_ew;
+        g.wrec_deg = t.wrec_deg;
+        g.wvtx_ew = t.wvtx_ew;
+        g.wvtx_deg = t.wvtx_deg;
+        g.wgd_ew = t.wgd_ew;
+        g.wgd_deg = t.wgd_deg;
+        g.gper_ew = t.gper_ew;
+        g.gper_deg = t.gper_deg;
+        g.hops = t.hops;
+        g.rank = t.rank;
+        g.repeats = t.repeats;
         if (!walk_guides.load()) {  // walks and long-list draws take the chunk tables
             g.wrec_ew = g.wrec_deg = nullptr;
             g.wvtx_ew = g.wvtx_deg = nullptr;
@@ -294,6 +344,54 @@ struct csaw_graph_s {
 };
 
 namespace {
+
+// A call's view of its graph. The tables stay until it goes: after the call's
+// work, which a call that did not reach its end waits for here. A call allocates
+// what it needs before it takes them, so that give_back's wait ends.
+struct TableUse {
+    csaw_graph g;
+    hipStream_t s;
+    Tables* t;
+    GraphDev dev;
+    bool drained = false;
+    TableUse(csaw_graph graph, hipStream_t stream) : g(graph), s(stream) {
+        std::lock_guard<std::mutex> lk(g->mu);
+        t = g->tables;
+        ++t->users;
+        dev = g->dev(*t);
+    }
+    TableUse(const TableUse&) = delete;
+    ~TableUse() {
+        if (!drained) (void)hipStreamSynchronize(s);
+        std::lock_guard<std::mutex> lk(g->mu);
+        if (--t->users == 0) g->idle.notify_all();
+    }
+};
+
+bool give_back(size_t bytes) {
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return false;
+    std::lock_guard<std::mutex> reg(registry().mu);
+    std::vector<csaw_graph> with;
+    size_t held = 0;
+    for (csaw_graph g : registry().graphs) {
+        std::lock_guard<std::mutex> lk(g->mu);
+        if (g->device != device || g->tables->bytes == 0) continue;
+        with.push_back(g);
+        held += g->tables->bytes;
+    }
+    if (with.empty() || (free_device_bytes && free_device_bytes() + held < bytes)) return false;
+    for (csaw_graph g : with) {
+        std::unique_lock<std::mutex> lk(g->mu);
+        Tables* const old = g->tables;
+        g->tables = new Tables();  // later calls do without
+        g->lean = true;
+        g->idle.wait(lk, [old] { return old->users == 0; });
+        lk.unlock();
+        delete old;
+    }
+    return true;
+}
 
 Workspace* acquire(csaw_graph g) {
     std::lock_guard<std::mutex> lk(g->mu);
@@ -377,7 +475,7 @@ csaw_status ensure_bitmaps(Workspace* w, size_t words, hipStream_t s) {
     return CSAW_OK;
 }
 
-csaw_status prepare_bias(csaw_graph g, int32_t kind, hipStream_t s) {
+csaw_status build_bias(csaw_graph g, int32_t kind, hipStream_t s) {
     // a weight array's positive counts and chunk prefix table; ppos_* is set
     // last, once everything it stands for is on the device
     std::lock_guard<std::mutex> lk(g->mu);
@@ -419,6 +517,13 @@ csaw_status prepare_bias(csaw_graph g, int32_t kind, hipStream_t s) {
     return CSAW_OK;
 }
 
+csaw_status prepare_bias(csaw_graph g, int32_t kind, hipStream_t s) {
+    csaw_status st = build_bias(g, kind, s);
+    if (st != CSAW_ERR_OUT_OF_MEMORY) return st;
+    (void)hipGetLastError();
+    return give_back(0) ? build_bias(g, kind, s) : st;
+}
+
 size_t guide_bytes(csaw_graph g, int per) {
     return (size_t)g->m * sizeof(WalkEdge) + (size_t)g->n * sizeof(WalkVertex) +
            (size_t)(per * g->m + g->n) * sizeof(WalkBucket);
@@ -428,12 +533,14 @@ size_t guide_bytes(csaw_graph g, int per) {
 // prefix and neighbor records, 16 bytes per edge; per-vertex list records,
 // 16 bytes per vertex, when m < 2^32; buckets, 16 bytes each and at most four
 // per edge, or two where four would be more than a third of the free device
-// memory), built once; a graph without them walks through the chunk tables.
+// memory or tables were given back), built once; a graph without them walks
+// through the chunk tables.
 csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     std::lock_guard<std::mutex> lk(g->mu);
     const bool dg = kind == kNeighborDegree;
     if (kind != kEdgeWeight && !dg) return CSAW_OK;
-    if ((dg ? g->wgd_deg : g->wgd_ew) || g->m <= 0) return CSAW_OK;
+    Tables& t = *g->tables;
+    if ((dg ? t.wgd_deg : t.wgd_ew) || g->m <= 0) return CSAW_OK;
     const uint32_t* w = dg ? g->degw : g->ew;
     const uint64_t* tot = dg ? g->wtot_deg : g->wtot_ew;
     if (!w || !tot || !(dg ? g->ppos_deg : g->ppos_ew)) return CSAW_OK;
@@ -441,7 +548,8 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     WalkVertex* vtx = nullptr;
     WalkBucket* gd = nullptr;
     const bool small = g->m < (int64_t(1) << 32);  // vertex records hold 32-bit list offsets
-    const bool scarce = free_device_bytes && guide_bytes(g, kGuideBucketsPerEdge) > free_device_bytes() / 3;
+    const bool scarce =
+        free_device_bytes && (g->lean || guide_bytes(g, kGuideBucketsPerEdge) > free_device_bytes() / 3);
     const int per = scarce ? kGuideBucketsScarce : kGuideBucketsPerEdge;
     if (hipMalloc((void**)&rec, (size_t)g->m * sizeof(WalkEdge)) != hipSuccess ||
         (small && hipMalloc((void**)&vtx, (size_t)std::max<int64_t>(g->n, 1) * sizeof(WalkVertex)) != hipSuccess) ||
@@ -453,17 +561,20 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     }
     if (!scarce) launch_walk_guides(g->rowptr, g->col, w, tot, g->n, rec, vtx, gd, s);
     else launch_walk_guides(g->rowptr, g->col, w, tot, g->n, rec, vtx, gd, per, s);
-    const hipError_t e = hipGetLastError() != hipSuccess ? hipErrorLaunchFailure : hipStreamSynchronize(s);
+    const bool launched = hipGetLastError() == hipSuccess;
+    hipError_t e = hipStreamSynchronize(s);
+    if (e == hipSuccess && !launched) e = hipErrorLaunchFailure;
     if (e != hipSuccess) {
         (void)hipFree(rec);
         if (vtx) (void)hipFree(vtx);
         (void)hipFree(gd);
         return fail(CSAW_ERR_DEVICE, "building the walk guide tables: %s", hipGetErrorString(e));
     }
-    (dg ? g->wrec_deg : g->wrec_ew) = rec;
-    (dg ? g->wvtx_deg : g->wvtx_ew) = vtx;
-    (dg ? g->gper_deg : g->gper_ew) = per;
-    (dg ? g->wgd_deg : g->wgd_ew) = gd;
+    (dg ? t.wrec_deg : t.wrec_ew) = rec;
+    (dg ? t.wvtx_deg : t.wvtx_ew) = vtx;
+    (dg ? t.gper_deg : t.gper_ew) = per;
+    (dg ? t.wgd_deg : t.wgd_ew) = gd;
+    t.bytes += guide_bytes(g, per);
     return CSAW_OK;
 }
 
@@ -477,7 +588,7 @@ void guides_for_sampling(csaw_graph g, int32_t kind, hipStream_t s) {
     if (!g->walk_guides.load() || drawn.load() < g->m || !free_device_bytes) return;
     {
         std::lock_guard<std::mutex> lk(g->mu);
-        if (kind == kNeighborDegree ? g->wgd_deg : g->wgd_ew) return;
+        if (g->lean || (kind == kNeighborDegree ? g->tables->wgd_deg : g->tables->wgd_ew)) return;
     }
     if (guide_bytes(g, kGuideBucketsPerEdge) <= free_device_bytes() / 2 && prepare_walk_guides(g, kind, s) != CSAW_OK) t_err.clear();
 }
@@ -496,17 +607,19 @@ void prepare_hops(csaw_graph g, int64_t steps, int64_t weight, hipStream_t s) {
     std::lock_guard<std::mutex> lk(g->mu);
     const size_t bytes = (size_t)g->m * sizeof(WalkHop);
     WalkHop* hops = nullptr;
-    if (g->hops || bytes > free_device_bytes() / 2) return;
+    if (g->lean || g->tables->hops || bytes > free_device_bytes() / 2) return;
     if (hipMalloc((void**)&hops, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return;
     }
     launch_walk_hops(g->rowptr, g->col, g->m, hops, s);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+    const bool launched = hipGetLastError() == hipSuccess;
+    if (hipStreamSynchronize(s) != hipSuccess || !launched) {
         (void)hipFree(hops);
         return;
     }
-    g->hops = hops;
+    g->tables->hops = hops;
+    g->tables->bytes += bytes;
 }
 
 // The rank index (2 bytes per edge, 4 per vertex), built by a graph's first
@@ -518,7 +631,7 @@ void prepare_ranks(csaw_graph g, hipStream_t s) {
     if (!launch_walk_ranks || !free_device_bytes || g->m <= 0 || !g->col || g->max_deg >= (int64_t(1) << 30)) return;
     std::lock_guard<std::mutex> lk(g->mu);
     const size_t bytes = (size_t)(rank_base(g->m, g->n) + 1) * sizeof(uint32_t);
-    if (g->rank || bytes > free_device_bytes() / 2) return;
+    if (g->lean || g->tables->rank || bytes > free_device_bytes() / 2) return;
     uint32_t* rank = nullptr;
     if (hipMalloc((void**)&rank, bytes) != hipSuccess) {
         (void)hipGetLastError();
@@ -534,8 +647,9 @@ void prepare_ranks(csaw_graph g, hipStream_t s) {
         (void)hipFree(rank);
         return;
     }
-    g->repeats = h;
-    g->rank = rank;
+    g->tables->repeats = h;
+    g->tables->rank = rank;
+    g->tables->bytes += bytes;
 }
 
 int64_t sat_mul(int64_t a, int64_t b) {
@@ -711,7 +825,7 @@ bool layout_sample(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int6
 hipError_t upload_rowptr(int64_t n, int64_t m, const int64_t* host, void** mem, RowPtr* rp, hipStream_t s) {
     const bool narrow = m <= (int64_t)UINT32_MAX;
     const size_t bytes = (size_t)(n + 1) * (narrow ? sizeof(uint32_t) : sizeof(int64_t));
-    hipError_t e = hipMalloc(mem, bytes);
+    hipError_t e = device_malloc(mem, bytes);
     if (e != hipSuccess) return e;
     if (narrow) {
         std::vector<uint32_t> w32((size_t)n + 1);
@@ -784,9 +898,9 @@ csaw_status csaw_graph_create(int64_t n, int64_t m, const int64_t* rowptr, const
     hipError_t e;
     if ((e = upload_rowptr(n, m, rowptr, &g->rowptr_mem, &g->rowptr, s)) != hipSuccess)
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "row offsets: %s", hipGetErrorString(e)));
-    if ((e = hipMalloc((void**)&g->dflag, 256)) != hipSuccess ||
-        (e = hipMalloc((void**)&g->col, std::max<int64_t>(m, 1) * sizeof(int32_t))) != hipSuccess ||
-        (edge_weight && (e = hipMalloc((void**)&g->ew, std::max<int64_t>(m, 1) * sizeof(uint32_t))) != hipSuccess))
+    if ((e = device_malloc((void**)&g->dflag, 256)) != hipSuccess ||
+        (e = device_malloc((void**)&g->col, std::max<int64_t>(m, 1) * sizeof(int32_t))) != hipSuccess ||
+        (edge_weight && (e = device_malloc((void**)&g->ew, std::max<int64_t>(m, 1) * sizeof(uint32_t))) != hipSuccess))
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "graph allocation failed: %s", hipGetErrorString(e)));
     if ((m > 0 && (e = hipMemcpyAsync(g->col, col, m * sizeof(int32_t), hipMemcpyHostToDevice, s)) != hipSuccess) ||
         (edge_weight && m > 0 &&
@@ -817,9 +931,6 @@ csaw_status csaw_graph_destroy(csaw_graph g) {
     if (g->wtot_deg) (void)hipFree(g->wtot_deg);
     if (g->ctab_ew) (void)hipFree(g->ctab_ew);
     if (g->ctab_deg) (void)hipFree(g->ctab_deg);
-    for (void* q : {(void*)g->wrec_ew, (void*)g->wrec_deg, (void*)g->wvtx_ew, (void*)g->wvtx_deg, (void*)g->wgd_ew,
-                    (void*)g->wgd_deg, (void*)g->hops, (void*)g->rank})
-        if (q) (void)hipFree(q);
     delete g;
     return CSAW_OK;
 }
@@ -897,7 +1008,6 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         HIP_OR_FAIL(hipStreamSynchronize(s));
         return CSAW_OK;
     }
-    const GraphDev gd = g->dev();
     const int64_t nwp = bitmap_words_per_instance(g->n);
     const int64_t words = nwp * ni;
     SampleLayout lay;
@@ -910,12 +1020,6 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                  o_bigs = lay.o_bigs;
     const std::vector<size_t>& o_fv = lay.o_fv;
     const std::vector<size_t>& o_fi = lay.o_fi;
-    // weighted draws from lists without a walk guide
-    const bool big_path = (P.uses_deg && !gd.wgd_deg) || (P.uses_ew && !gd.wgd_ew);
-    // every instance draws that way: it depends on the kinds themselves, which are no part of the call's shape
-    const bool wave_only = big_path && b16 <= 0 && b32 <= 0 && !(P.uses_deg && gd.wgd_deg) &&
-                           !(P.uses_ew && gd.wgd_ew) &&
-                           std::none_of(P.bias.begin(), P.bias.end(), [](int32_t k) { return k == kUniform; });
     const size_t o_hctl = align_up(tab_bytes, 64);
     Workspace* ws = nullptr;
     char* A = nullptr;
@@ -946,6 +1050,14 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
         H = ws->pinned;
         ctl_copy = (SampleCtl*)(ws->pinned_dev + o_hctl);
     }
+    TableUse use(g, s);
+    const GraphDev& gd = use.dev;
+    // weighted draws from lists without a walk guide
+    const bool big_path = (P.uses_deg && !gd.wgd_deg) || (P.uses_ew && !gd.wgd_ew);
+    // every instance draws that way: it depends on the kinds themselves, which are no part of the call's shape
+    const bool wave_only = big_path && b16 <= 0 && b32 <= 0 && !(P.uses_deg && gd.wgd_deg) &&
+                           !(P.uses_ew && gd.wgd_ew) &&
+                           std::none_of(P.bias.begin(), P.bias.end(), [](int32_t k) { return k == kUniform; });
 
     SampleCtl* ctl = (SampleCtl*)(A + o_ctl);
     int32_t* d_fan = (int32_t*)(A + o_tab + t_fan);
@@ -1146,6 +1258,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
             key.push_back((int64_t)P.uses_deg);
             key.push_back((int64_t)P.uses_ew);
             key.push_back((int64_t)wave_only);  // chooses the kernels
+            key.push_back(gd.gper_ew);  // (tables built again may lie where others did)
+            key.push_back(gd.gper_deg);
             hipGraphExec_t exec = ws->find_graph(key);
             if (!exec) {
                 HIP_OR_FAIL(hipStreamBeginCapture(ws->capture, hipStreamCaptureModeRelaxed));
@@ -1179,7 +1293,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     // positions, so the bitmaps may not be clean: the workspace is dropped
     // (Lease) instead of going back to the pool
     if (h_ctl->gave_up()) return fail(CSAW_ERR_DEVICE, "frontier build did not complete its block chain");
-    rel.clean = true;
+    rel.clean = use.drained = true;
     out->num_edges = L > 0 ? h_ctl->out_base[L] : 0;
     if (out->num_edges < 0) return fail(CSAW_ERR_DEVICE, "the device reported a negative edge count");
     if (P.uses_deg) g->drawn_deg += out->num_edges;
@@ -1452,12 +1566,12 @@ csaw_status csaw_pgraph_create(int64_t n, int64_t m, const int64_t* rowptr, cons
     hipError_t e;
     if ((e = upload_rowptr(n, m, rowptr, &g->rowptr_mem, &g->rowptr, s)) != hipSuccess)
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "row offsets: %s", hipGetErrorString(e)));
-    if ((e = hipMalloc((void**)&g->ppos_deg, nv * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&g->wtot_deg, nv * sizeof(uint64_t))) != hipSuccess ||
-        (pg->has_ew && (e = hipMalloc((void**)&g->ppos_ew, nv * sizeof(int32_t))) != hipSuccess) ||
-        (pg->has_ew && (e = hipMalloc((void**)&g->wtot_ew, nv * sizeof(uint64_t))) != hipSuccess) ||
-        (e = hipMalloc((void**)&pg->d_vb, (np + 1) * sizeof(int64_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&pg->d_work, 2 * np * sizeof(unsigned long long))) != hipSuccess ||
+    if ((e = device_malloc((void**)&g->ppos_deg, nv * sizeof(int32_t))) != hipSuccess ||
+        (e = device_malloc((void**)&g->wtot_deg, nv * sizeof(uint64_t))) != hipSuccess ||
+        (pg->has_ew && (e = device_malloc((void**)&g->ppos_ew, nv * sizeof(int32_t))) != hipSuccess) ||
+        (pg->has_ew && (e = device_malloc((void**)&g->wtot_ew, nv * sizeof(uint64_t))) != hipSuccess) ||
+        (e = device_malloc((void**)&pg->d_vb, (np + 1) * sizeof(int64_t))) != hipSuccess ||
+        (e = device_malloc((void**)&pg->d_work, 2 * np * sizeof(unsigned long long))) != hipSuccess ||
         (e = hipHostMalloc((void**)&pg->h_work, 2 * np * sizeof(unsigned long long), hipHostMallocDefault)) !=
             hipSuccess)
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "allocation failed: %s", hipGetErrorString(e)));
@@ -1483,7 +1597,7 @@ csaw_status csaw_pgraph_create(int64_t n, int64_t m, const int64_t* rowptr, cons
                      o_gdeg = cv.take<uint64_t>(sr * kChunkGroups);
         const size_t o_ew = pg->has_ew ? cv.take<uint32_t>(se) : 0,
                      o_gew = pg->has_ew ? cv.take<uint64_t>(sr * kChunkGroups) : 0;
-        if ((e = hipMalloc((void**)&x.mem, cv.off)) != hipSuccess)
+        if ((e = device_malloc((void**)&x.mem, cv.off)) != hipSuccess)
             return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "partition slot: %s", hipGetErrorString(e)));
         x.d_col = (int32_t*)(x.mem + o_col);
         x.d_degw = (uint32_t*)(x.mem + o_degw);
@@ -1664,16 +1778,18 @@ static csaw_status walk_prepare(csaw_graph g, const csaw_walk_args* a, hipStream
                 return fail(CSAW_ERR_NOT_READY, "the tables of this bias kind are not built yet");
         } else {
             csaw_status st = prepare_bias(g, a->bias_kind, s);
-            if (st == CSAW_OK && g->walk_guides.load()) st = prepare_walk_guides(g, a->bias_kind, s);
             if (st != CSAW_OK) return st;
+            if (g->walk_guides.load()) st = prepare_walk_guides(g, a->bias_kind, s);
+            if (st == CSAW_ERR_OUT_OF_MEMORY) t_err.clear();  // the same walk through the chunk tables
+            else if (st != CSAW_OK) return st;
         }
     }
     return CSAW_OK;
 }
 
-static WalkParams walk_params(csaw_graph g, const csaw_walk_args* a) {
+static WalkParams walk_params(const GraphDev& g, const csaw_walk_args* a) {
     WalkParams p;
-    p.g = g->dev();
+    p.g = g;
     p.bias = a->bias_kind;
     p.w_return = a->w_return;
     p.w_common = a->w_common;
@@ -1723,7 +1839,8 @@ static csaw_status walk_call(csaw_graph g, const csaw_walk_args* a, int32_t* pat
     unsigned long long* d_steps = (unsigned long long*)dev;
     int32_t* d_bad = (int32_t*)(dev + 256);
     HIP_OR_FAIL(hipMemsetAsync(dev, 0, kWalkScratchBytes, s));
-    WalkParams p = walk_params(g, a);
+    TableUse use(g, s);
+    WalkParams p = walk_params(use.dev, a);
     p.paths = paths;
     p.steps = d_steps;
     p.bad_start = d_bad;
@@ -1734,7 +1851,7 @@ static csaw_status walk_call(csaw_graph g, const csaw_walk_args* a, int32_t* pat
     HIP_OR_FAIL(hipGetLastError());
     HIP_OR_FAIL(hipMemcpyAsync(host, dev, kWalkScratchBytes, hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
-    rel.clean = true;
+    rel.clean = use.drained = true;
     const unsigned long long steps = *(unsigned long long*)host;
     const int32_t bad = *(int32_t*)(host + 256);
     if (bad) return fail(CSAW_ERR_INVALID_ARG, "a start vertex is outside [0, n)");
@@ -1787,8 +1904,9 @@ csaw_status csaw_mdrw(csaw_graph g, const csaw_mdrw_args* a, int32_t* src, int32
     unsigned long long* d_total = (unsigned long long*)ws->arena;
     int32_t* d_bad = (int32_t*)(ws->arena + 256);
     HIP_OR_FAIL(hipMemsetAsync(ws->arena, 0, 512, s));
+    TableUse use(g, s);
     MdrwParams p;
-    p.g = g->dev();
+    p.g = use.dev;
     p.num_instances = ni;
     p.max_pool = (int32_t)max_pool;
     p.max_degree = (uint64_t)g->max_deg;
@@ -1810,7 +1928,7 @@ csaw_status csaw_mdrw(csaw_graph g, const csaw_mdrw_args* a, int32_t* src, int32
     HIP_OR_FAIL(hipGetLastError());
     HIP_OR_FAIL(hipMemcpyAsync(ws->pinned, ws->arena, 512, hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
-    rel.clean = true;
+    rel.clean = use.drained = true;
     const unsigned long long tot = *(unsigned long long*)ws->pinned;
     const int32_t bad = *(int32_t*)(ws->pinned + 256);
     if (total_edges) *total_edges = (int64_t)tot;
@@ -1863,8 +1981,9 @@ csaw_status csaw_layer_sample(csaw_graph g, const csaw_layer_args* a, int32_t* s
     if ((st = ensure_pinned(ws, o_off + ((size_t)ni + 1) * sizeof(int64_t))) != CSAW_OK) return st;
     std::memcpy(ws->pinned + o_off, a->seed_offsets, ((size_t)ni + 1) * sizeof(int64_t));
     HIP_OR_FAIL(hipMemsetAsync(ws->arena, 0, 512, s));
+    TableUse use(g, s);
     LayerParams p{};
-    p.g = g->dev();
+    p.g = use.dev;
     p.num_instances = ni;
     p.seed_off = (const int64_t*)(ws->pinned_dev + o_off);
     p.seeds = a->seeds;
@@ -1888,7 +2007,7 @@ csaw_status csaw_layer_sample(csaw_graph g, const csaw_layer_args* a, int32_t* s
     HIP_OR_FAIL(hipGetLastError());
     HIP_OR_FAIL(hipMemcpyAsync(ws->pinned, ws->arena, 512, hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
-    rel.clean = true;
+    rel.clean = use.drained = true;
     if (*(int32_t*)ws->pinned) return fail(CSAW_ERR_INVALID_ARG, "seeds out of range, unsorted or repeated");
     int64_t draws = 0;
     for (int32_t l = 0; l < L; ++l) draws += 2 * (int64_t)ni * a->fanouts[l];  // a guide saves 0.4 ns each, not 0.2
@@ -1900,6 +2019,14 @@ csaw_status csaw_layer_sample(csaw_graph g, const csaw_layer_args* a, int32_t* s
 }  // extern "C"
 
 namespace csaw {
+
+hipError_t device_malloc(void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();  // reported here, not by the launches that follow
+    if (give_back(bytes) && (e = hipMalloc(p, bytes)) != hipSuccess) (void)hipGetLastError();
+    return e;
+}
 
 csaw_status sample_plan_caps(csaw_graph g, const csaw_sample_args* a, std::vector<int64_t>& fcap,
                              int64_t* max_edges) {
@@ -1981,7 +2108,8 @@ csaw_status walk_batch_in_scratch(csaw_graph g, const csaw_walk_args* common, co
     for (int32_t q = 0; q < nreq; ++q) steps[q] = 0;
     if (nw == 0) return CSAW_OK;
     const WalkBatchLayout y = walk_batch_layout(nreq, nw);
-    WalkParams p = walk_params(g, common);
+    TableUse use(g, s);
+    WalkParams p = walk_params(use.dev, common);
     p.num_walkers = nw;
     p.starts = d_starts;
     p.walker_ids = nullptr;
@@ -2004,6 +2132,7 @@ csaw_status walk_batch_in_scratch(csaw_graph g, const csaw_walk_args* common, co
     HIP_OR_FAIL(hipMemcpyAsync(back.data(), d_tables + y.o_steps, back.size() * sizeof(uint64_t),
                                hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
+    use.drained = true;
     if ((int32_t)back[nreq]) return fail(CSAW_ERR_INVALID_ARG, "a start vertex is outside [0, n)");
     for (int32_t q = 0; q < nreq; ++q) {
         // a device-written count: at most one step per walker and step index

@@ -740,7 +740,7 @@ csaw_status csaw_server_create(csaw_graph g, const csaw_server_config* cfg, csaw
             st = CSAW_ERR_DEVICE;
             break;
         }
-        if (hipMalloc((void**)&x.dev, std::max<size_t>(x.bytes, kAlign)) != hipSuccess ||
+        if (csaw::device_malloc((void**)&x.dev, std::max<size_t>(x.bytes, kAlign)) != hipSuccess ||
             hipHostMalloc((void**)&x.stage[0], kStageBytes, hipHostMallocDefault) != hipSuccess ||
             hipHostMalloc((void**)&x.stage[1], kStageBytes, hipHostMallocDefault) != hipSuccess) {
             st = CSAW_ERR_OUT_OF_MEMORY;

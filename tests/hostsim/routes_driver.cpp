@@ -11,6 +11,8 @@
 //                     calls of four threads, and are left out where memory is
 //                     short; every call gives the same results
 //   driver room       a server on a device with room for one walk guide, or none
+//   driver give_back  calls, graphs and servers that need the memory of such tables
+//                     get it, also while other threads' calls read them
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
@@ -66,6 +68,9 @@ struct Call {
     void check(const Host& h, csaw_graph g, const std::vector<int32_t>& bias, hipStream_t s, bool noalloc = false) {
         csaw_sample_args a = args(bias);
         OK(noalloc ? csaw_sample_noalloc(g, &a, &out, s) : csaw_sample(g, &a, &out, s));
+        check_edges(h, bias);
+    }
+    void check_edges(const Host& h, const std::vector<int32_t>& bias) {
         Edges e;
         e.src.assign(out.src, out.src + out.num_edges);
         e.dst.assign(out.dst, out.dst + out.num_edges);
@@ -290,6 +295,99 @@ void scenario_room() {
     (void)hipStreamDestroy(s);
 }
 
+// An allocator that fails once in the thread that asks for it.
+thread_local int fail_allocs = 0;
+void* picky_alloc(size_t bytes, void*) {
+    if (fail_allocs > 0 && fail_allocs--) return nullptr;
+    void* p = nullptr;
+    return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
+}
+void picky_free(void* p, void*) { (void)hipFree(p); }
+
+void scenario_give_back() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_symmetric(1 << 12, 6 << 12, 38);
+    const size_t slack = size_t(16) << 10;
+    // what needs the memory: a sampling call with a larger workspace, a weight
+    // array's tables, a second graph, a partitioned graph, a server
+    for (int what = 0; what < 5; ++what) {
+        Dev d = upload(h, s);
+        Client c(h, d.g, 60);
+        Call large(h, d.g, 60, 10, {6, 4});
+        Walks degree(h, 50, 8, 64);
+        const int32_t kinds[3] = {CSAW_BIAS_EDGE_WEIGHT, CSAW_BIAS_UNIFORM, CSAW_BIAS_NODE2VEC};
+        for (int rep = 0; rep < 30; ++rep) {
+            c.call.check(h, d.g, std::vector<int32_t>(4, CSAW_BIAS_EDGE_WEIGHT), s);
+            for (int32_t k : kinds) c.walks.check(h, d.g, k, s);
+        }
+        const size_t with = hipsim::device_bytes_in_use();
+        limit_device(with + slack);
+        if (what == 0) large.check(h, d.g, std::vector<int32_t>(60, CSAW_BIAS_EDGE_WEIGHT), s);
+        if (what == 1) degree.check(h, d.g, CSAW_BIAS_NEIGHBOR_DEGREE, s);
+        Dev other;
+        if (what == 2) other = upload(h, s);
+        csaw_pgraph pg = nullptr;
+        if (what == 3)
+            OK(csaw_pgraph_create(h.n, (int64_t)h.col.size(), h.rp.data(), h.col.data(), h.ew.data(), 4, 1, s, &pg));
+        csaw_server srv = nullptr;
+        csaw_server_config cfg{};
+        cfg.memory_budget_bytes = int64_t(1) << 20;
+        cfg.num_streams = 1;
+        if (what == 4) OK(csaw_server_create(d.g, &cfg, &srv));
+        limit_device(0);
+        hipsim_hooks::with_hops = hipsim_hooks::with_rank = 0;
+        c.round();  // without them
+        CHECK(hipsim_hooks::with_hops.load() == 0 && hipsim_hooks::with_rank.load() == 0);
+        if (srv) OK(csaw_server_destroy(srv));
+        if (pg) OK(csaw_pgraph_destroy(pg));
+        if (other.g) OK(csaw_graph_destroy(other.g));
+        OK(csaw_graph_destroy(d.g));
+    }
+    {  // weighted walks without room for a guide
+        Dev d = upload(h, s);
+        Walks w(h, 50, 8, 65);
+        w.check(h, d.g, CSAW_BIAS_UNIFORM, s);  // (its workspace)
+        limit_device(hipsim::device_bytes_in_use() + slack);
+        w.check(h, d.g, CSAW_BIAS_EDGE_WEIGHT, s);
+        limit_device(0);
+        OK(csaw_graph_destroy(d.g));
+    }
+    OK(csaw_set_allocator(picky_alloc, picky_free, nullptr));
+    const Host small = make_graph(1 << 8, 4 << 8, 39);
+    int given = 0;
+    for (int rep = 0; rep < 3; ++rep) {
+        Dev d = upload(h, s);
+        std::atomic<int> running{3};
+        std::vector<std::thread> threads;
+        for (int t = 0; t < 3; ++t)
+            threads.emplace_back([&, t] {
+                Client c(h, d.g, 70 + t);
+                for (int k = 0; k < 4; ++k) c.round();
+                --running;
+            });
+        while (running.load()) {  // a new graph's first workspace
+            Dev mine = upload(small, s);
+            Call c(small, mine.g, 4, 10, {4, 3});
+            const std::vector<int32_t> bias(4, CSAW_BIAS_EDGE_WEIGHT);
+            csaw_sample_args a = c.args(bias);
+            fail_allocs = 1;
+            const csaw_status st = csaw_sample(mine.g, &a, &c.out, s);
+            CHECK(fail_allocs == 0 && (st == CSAW_OK || st == CSAW_ERR_OUT_OF_MEMORY));  // (no tables at that moment)
+            if (st == CSAW_OK) {
+                c.check_edges(small, bias);
+                ++given;
+            }
+            OK(csaw_graph_destroy(mine.g));
+        }
+        for (auto& t : threads) t.join();
+        OK(csaw_graph_destroy(d.g));
+    }
+    CHECK(given > 0);
+    OK(csaw_set_allocator(nullptr, nullptr, nullptr));
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -298,6 +396,7 @@ int main(int argc, char** argv) {
     else if (what == "retry") scenario_retry();
     else if (what == "tables") scenario_tables();
     else if (what == "room") scenario_room();
+    else if (what == "give_back") scenario_give_back();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;
