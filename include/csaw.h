@@ -78,8 +78,9 @@ typedef enum {
  *                    bias, Section II-A); the first step is unbiased.
  *                    Requires sorted adjacency lists. The graph's first such
  *                    csaw_walk builds a rank index of the lists (2 bytes per
- *                    edge, 4 per vertex) where half of the free device memory
- *                    holds it; without it steps merge lists, to the same picks. */
+ *                    edge, 4 per vertex) where there is room for it
+ *                    (csaw_set_walk_guides); without it steps merge lists, to
+ *                    the same picks. */
 typedef enum {
     CSAW_BIAS_UNIFORM = 0,
     CSAW_BIAS_EDGE_WEIGHT = 1,
@@ -327,16 +328,27 @@ csaw_status csaw_walk(csaw_graph g, const csaw_walk_args* args, int32_t* paths,
  * one wavefront per walker, with the same paths. Sampling calls draw
  * through a weight array's guide when it is built and on (a walk or a server
  * builds it, or csaw_sample once its calls have sampled m edges by that
- * array, an edge drawn by csaw_layer_sample counting twice, and the tables fit
- * half of the free device memory), else from the
+ * array, an edge drawn by csaw_layer_sample counting twice), else from the
  * weights and the chunk tables: the same edges either way.
+ * Hop table (UNIFORM and METROPOLIS_HASTINGS walks, csaw_mdrw; m < 2^32): once
+ * m / 2 unbiased steps were asked of a graph (a step of csaw_mdrw counts 16
+ * times) its calls build, once, 16 bytes per edge: the neighbor and its list, so that a
+ * step reads one record.
+ * Memory: what calls build without needing it -- the hop table, the rank index
+ * of NODE2VEC walks, a guide built by sampling -- takes at most half of the
+ * device memory that would be free without it, and is left out where the guides of
+ * the graph's weighted walks would no longer fit. A table that did not fit is tried
+ * again once the calls that would use it have doubled. Calls in caller memory
+ * (csaw_sample_noalloc, served requests) build nothing.
  * Tables that calls built to draw faster -- the guides, and the hop table and
  * rank index of csaw_walk -- are given back when a call, a graph or a server
  * of the library cannot get its device memory otherwise. The graph's calls then
  * do without: of these only walk guides are built again, with two buckets per
  * edge. A weighted walk whose guide does not fit takes the chunk tables.
- * enable: 1 (default) or 0. A walk already running keeps its route. INVALID_ARG
- * otherwise. Turning the guide off does not free built tables. */
+ * enable: 1 (default) or 0, for the guides, the hop table and the rank index: with
+ * 0 the graph's calls neither build nor use one, to the same results. A call already
+ * running keeps its route. INVALID_ARG otherwise. Turning them off does not free
+ * built tables. */
 csaw_status csaw_set_walk_guides(csaw_graph g, int32_t enable);
 /* HOST out: enable. */
 csaw_status csaw_get_walk_guides(csaw_graph g, int32_t* enable);

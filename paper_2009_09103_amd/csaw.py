@@ -352,8 +352,8 @@ class Graph:
         return t.bound16, t.bound32
 
     def set_walk_guides(self, enable: bool):
-        """Weighted walks through the walk guide (True, the default) or the
-        chunk tables (csaw_set_walk_guides)."""
+        """Calls through walk guides, hop table and rank index (True, the
+        default), or without building or using them (csaw_set_walk_guides)."""
         _check(lib.csaw_set_walk_guides(self._h, 1 if enable else 0))
 
     def get_walk_guides(self) -> bool:

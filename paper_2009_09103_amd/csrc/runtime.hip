@@ -241,6 +241,7 @@ struct Tables {
     uint32_t* rank = nullptr;      // rank index of the lists (node2vec)
     int32_t repeats = 0;           // some list holds a neighbor more than once (known with rank)
     size_t bytes = 0;              // of all of them
+    size_t unasked = 0;            // of those that no call needed: all but the guides of weighted walks and servers
     int64_t users = 0;             // calls that hold them
 
     ~Tables() {
@@ -288,9 +289,13 @@ struct csaw_graph_s {
     std::condition_variable idle;  // a call let go of its tables
     std::vector<Workspace*> pool;
     std::atomic<int32_t> bound16{kDefaultBound16}, bound32{kDefaultBound32};  // sub-wave buckets
-    std::atomic<int32_t> walk_guides{1};  // weighted walks build and use the walk guides
+    std::atomic<int32_t> walk_guides{1};  // calls build and use walk guides, hop table and rank index
     std::atomic<int64_t> drawn_ew{0}, drawn_deg{0};  // edges that sampling calls drew, per weight array
     std::atomic<int64_t> hopped{0};                  // unbiased steps asked for (see prepare_hops)
+    int64_t ranked = 0, guided[2] = {0, 0};  // node2vec walks without the rank index, weighted walks without a guide
+    // the same counts at which a table that did not fit is tried again
+    std::atomic<int64_t> due_ew{0}, due_deg{0}, due_hops{0};
+    int64_t due_ranks = 0, due_guided[2] = {0, 0};
     uint32_t chain_spins = first_spins();
 
     csaw_graph_s() {
@@ -334,7 +339,9 @@ struct csaw_graph_s {
         g.hops = t.hops;
         g.rank = t.rank;
         g.repeats = t.repeats;
-        if (!walk_guides.load()) {  // walks and long-list draws take the chunk tables
+        if (!walk_guides.load()) {  // calls take the weights, the chunk tables and the lists themselves
+            g.hops = nullptr;
+            g.rank = nullptr;
             g.wrec_ew = g.wrec_deg = nullptr;
             g.wvtx_ew = g.wvtx_deg = nullptr;
             g.wgd_ew = g.wgd_deg = nullptr;
@@ -535,7 +542,10 @@ size_t guide_bytes(csaw_graph g, int per) {
 // per edge, or two where four would be more than a third of the free device
 // memory or tables were given back), built once; a graph without them walks
 // through the chunk tables.
-csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
+// For a weighted walk a guide that did not fit is tried again by the second, fourth,
+// ... one after it.
+enum class GuideFor { kWalk, kServer, kSampling };
+csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s, GuideFor what) {
     std::lock_guard<std::mutex> lk(g->mu);
     const bool dg = kind == kNeighborDegree;
     if (kind != kEdgeWeight && !dg) return CSAW_OK;
@@ -544,6 +554,8 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     const uint32_t* w = dg ? g->degw : g->ew;
     const uint64_t* tot = dg ? g->wtot_deg : g->wtot_ew;
     if (!w || !tot || !(dg ? g->ppos_deg : g->ppos_ew)) return CSAW_OK;
+    if (what == GuideFor::kWalk && ++g->guided[dg] < g->due_guided[dg])
+        return fail(CSAW_ERR_OUT_OF_MEMORY, "walk guide tables: no room before");
     WalkEdge* rec = nullptr;
     WalkVertex* vtx = nullptr;
     WalkBucket* gd = nullptr;
@@ -557,6 +569,7 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
         (void)hipGetLastError();  // the caller may go on without the tables
         if (rec) (void)hipFree(rec);
         if (vtx) (void)hipFree(vtx);
+        g->due_guided[dg] = 2 * g->guided[dg];
         return fail(CSAW_ERR_OUT_OF_MEMORY, "walk guide tables: allocation failed");
     }
     if (!scarce) launch_walk_guides(g->rowptr, g->col, w, tot, g->n, rec, vtx, gd, s);
@@ -575,41 +588,72 @@ csaw_status prepare_walk_guides(csaw_graph g, int32_t kind, hipStream_t s) {
     (dg ? t.gper_deg : t.gper_ew) = per;
     (dg ? t.wgd_deg : t.wgd_ew) = gd;
     t.bytes += guide_bytes(g, per);
+    if (what == GuideFor::kSampling) t.unasked += guide_bytes(g, per);
     return CSAW_OK;
+}
+
+// Whether a table of so many bytes may be built that no call needs (g->mu held): all
+// of them together take at most half of the memory that would be free without
+// them, and beside it there is room for the guides that the graph's weighted
+// walks may still build, in compact form (but for the weight array `kind`, whose
+// guide this is).
+bool room_for(csaw_graph g, size_t bytes, int32_t kind) {
+    const Tables& t = *g->tables;
+    const size_t free_b = free_device_bytes();
+    size_t walks = 0;
+    if (g->ew && !t.wgd_ew && kind != kEdgeWeight) walks += guide_bytes(g, kGuideBucketsScarce);
+    if (g->ppos_deg && !t.wgd_deg && kind != kNeighborDegree) walks += guide_bytes(g, kGuideBucketsScarce);
+    return t.unasked + bytes <= (free_b + t.unasked) / 2 && bytes + walks <= free_b;
+}
+
+// Memory of such a table that is no walk guide; false without room.
+bool optional_malloc(csaw_graph g, void** p, size_t bytes) {
+    if (!room_for(g, bytes, kUniform)) return false;
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Sampling and layer sampling draw through the walk guide too, but do without it until
 // their weighted draws have paid for it: building it costs about what m sampled
 // edges gain (R-MAT 22, 65M edges: 6 ms and 5 GB of allocations against 0.1 to 0.2 ms
-// per million edges), and it is left out where it would take more than half of the
-// device memory that is free. A failure leaves the chunk tables.
+// per million edges). Where it does not fit the chunk tables remain, and it is tried
+// again once the draws have doubled.
 void guides_for_sampling(csaw_graph g, int32_t kind, hipStream_t s) {
-    const std::atomic<int64_t>& drawn = kind == kNeighborDegree ? g->drawn_deg : g->drawn_ew;
-    if (!g->walk_guides.load() || drawn.load() < g->m || !free_device_bytes) return;
+    const bool dg = kind == kNeighborDegree;
+    const int64_t drawn = (dg ? g->drawn_deg : g->drawn_ew).load();
+    std::atomic<int64_t>& due = dg ? g->due_deg : g->due_ew;
+    if (!g->walk_guides.load() || g->m <= 0 || drawn < std::max(g->m, due.load()) || !free_device_bytes) return;
+    const size_t bytes = guide_bytes(g, kGuideBucketsPerEdge);
+    bool fits;
     {
         std::lock_guard<std::mutex> lk(g->mu);
-        if (g->lean || (kind == kNeighborDegree ? g->tables->wgd_deg : g->tables->wgd_ew)) return;
+        if (g->lean || (dg ? g->tables->wgd_deg : g->tables->wgd_ew)) return;
+        fits = room_for(g, bytes, kind);
     }
-    if (guide_bytes(g, kGuideBucketsPerEdge) <= free_device_bytes() / 2 && prepare_walk_guides(g, kind, s) != CSAW_OK) t_err.clear();
+    if (fits && prepare_walk_guides(g, kind, s, GuideFor::kSampling) == CSAW_OK) return;
+    t_err.clear();
+    due = 2 * drawn;
 }
 
 // The hop table (16 bytes per edge), built for the call about to take `steps`
-// unbiased steps once the steps asked of the graph have paid for it, where it
-// takes at most half of the free device memory; without it steps read the
-// column ids and the row offsets. Building it costs about what m / 2 steps of
+// unbiased steps once the steps asked of the graph have paid for it, where
+// there is room; without it steps read the column ids and the row offsets (and
+// it is tried again once the steps have doubled). Building it costs about what m / 2 steps of
 // walks by the hundred thousand gain (10 ms against 30 ps a step on 500M
 // edges), or m / 32 steps of the pools of a multi-dimensional walk, which wait
 // for every load (weight 16).
 void prepare_hops(csaw_graph g, int64_t steps, int64_t weight, hipStream_t s) {
     if (!launch_walk_hops || !free_device_bytes || g->m <= 0 || g->m > (int64_t)UINT32_MAX || !g->col) return;
-    if (g->hopped.fetch_add(std::min<int64_t>(steps, g->m) * weight) + std::min<int64_t>(steps, g->m) * weight < g->m / 2)
-        return;
+    if (!g->walk_guides.load()) return;
+    const int64_t add = std::min<int64_t>(steps, g->m) * weight, asked = g->hopped.fetch_add(add) + add;
+    if (asked < std::max(g->m / 2, g->due_hops.load())) return;
     std::lock_guard<std::mutex> lk(g->mu);
+    if (g->lean || g->tables->hops) return;
     const size_t bytes = (size_t)g->m * sizeof(WalkHop);
     WalkHop* hops = nullptr;
-    if (g->lean || g->tables->hops || bytes > free_device_bytes() / 2) return;
-    if (hipMalloc((void**)&hops, bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    if (!optional_malloc(g, (void**)&hops, bytes)) {
+        g->due_hops = 2 * asked;
         return;
     }
     launch_walk_hops(g->rowptr, g->col, g->m, hops, s);
@@ -620,21 +664,23 @@ void prepare_hops(csaw_graph g, int64_t steps, int64_t weight, hipStream_t s) {
     }
     g->tables->hops = hops;
     g->tables->bytes += bytes;
+    g->tables->unasked += bytes;
 }
 
 // The rank index (2 bytes per edge, 4 per vertex), built by a graph's first
-// node2vec walk where it takes at most half of the free device memory (one
+// node2vec walk where there is room, or by the second, fourth, ... one (one
 // pass over the column ids, 3.2 ms on 500M edges; that first walk has just
 // looked up the reverse of every edge, 85 ms); without it node2vec steps merge the two
 // lists.
 void prepare_ranks(csaw_graph g, hipStream_t s) {
-    if (!launch_walk_ranks || !free_device_bytes || g->m <= 0 || !g->col || g->max_deg >= (int64_t(1) << 30)) return;
+    if (!g->walk_guides.load() || !launch_walk_ranks || !free_device_bytes) return;
+    if (g->m <= 0 || !g->col || g->max_deg >= (int64_t(1) << 30)) return;
     std::lock_guard<std::mutex> lk(g->mu);
+    if (g->lean || g->tables->rank || ++g->ranked < g->due_ranks) return;
     const size_t bytes = (size_t)(rank_base(g->m, g->n) + 1) * sizeof(uint32_t);
-    if (g->lean || g->tables->rank || bytes > free_device_bytes() / 2) return;
     uint32_t* rank = nullptr;
-    if (hipMalloc((void**)&rank, bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    if (!optional_malloc(g, (void**)&rank, bytes)) {
+        g->due_ranks = 2 * g->ranked;
         return;
     }
     int32_t h = 0;
@@ -650,6 +696,7 @@ void prepare_ranks(csaw_graph g, hipStream_t s) {
     g->tables->repeats = h;
     g->tables->rank = rank;
     g->tables->bytes += bytes;
+    g->tables->unasked += bytes;
 }
 
 int64_t sat_mul(int64_t a, int64_t b) {
@@ -1779,7 +1826,7 @@ static csaw_status walk_prepare(csaw_graph g, const csaw_walk_args* a, hipStream
         } else {
             csaw_status st = prepare_bias(g, a->bias_kind, s);
             if (st != CSAW_OK) return st;
-            if (g->walk_guides.load()) st = prepare_walk_guides(g, a->bias_kind, s);
+            if (g->walk_guides.load()) st = prepare_walk_guides(g, a->bias_kind, s, GuideFor::kWalk);
             if (st == CSAW_ERR_OUT_OF_MEMORY) t_err.clear();  // the same walk through the chunk tables
             else if (st != CSAW_OK) return st;
         }
@@ -2158,7 +2205,7 @@ void prepare_guides(csaw_graph g, int32_t kind, hipStream_t stream) {
         std::lock_guard<std::mutex> lk(g->mu);
         if (!g->walk_guides.load() || !(kind == kNeighborDegree ? g->ppos_deg : g->ppos_ew)) return;
     }
-    if (prepare_walk_guides(g, kind, stream) != CSAW_OK) t_err.clear();
+    if (prepare_walk_guides(g, kind, stream, GuideFor::kServer) != CSAW_OK) t_err.clear();
 }
 
 }  // namespace csaw

@@ -13,6 +13,9 @@
 //   driver room       a server on a device with room for one walk guide, or none
 //   driver give_back  calls, graphs and servers that need the memory of such tables
 //                     get it, also while other threads' calls read them
+//   driver refused    tables that do not fit are asked for ever more seldom, all
+//                     those that calls build by themselves take half of the free
+//                     memory at most, and none is built or used when turned off
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
@@ -388,6 +391,63 @@ void scenario_give_back() {
     (void)hipStreamDestroy(s);
 }
 
+void scenario_refused() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_symmetric(1 << 10, 6 << 10, 41);
+    const size_t n = (size_t)h.n, m = h.col.size();
+    {
+        Dev d = upload(h, s);
+        Client c(h, d.g, 80);
+        c.call.check(h, d.g, std::vector<int32_t>(4, CSAW_BIAS_NEIGHBOR_DEGREE), s);
+        limit_device(hipsim::device_bytes_in_use() + 8 * m);
+        hipsim_hooks::queries = hipsim_hooks::guides = hipsim_hooks::hops = 0;
+        for (int rep = 0; rep < 200; ++rep) c.round();
+        CHECK(hipsim_hooks::guides.load() == 0 && hipsim_hooks::hops.load() == 0);
+        CHECK(hipsim_hooks::queries.load() < 100);
+        limit_device(0);  // there is room again: they come in the end
+        for (int rep = 0; rep < 1000 && (hipsim_hooks::guides.load() < 2 || hipsim_hooks::hops.load() < 1); ++rep) c.round();
+        CHECK(hipsim_hooks::guides.load() == 2 && hipsim_hooks::hops.load() == 1);
+        OK(csaw_graph_destroy(d.g));
+    }
+    {
+        Dev d = upload(h, s);
+        Client c(h, d.g, 81);
+        const size_t guide = 16 * m + 16 * n + 16 * (4 * m + n);
+        c.call.check(h, d.g, std::vector<int32_t>(4, CSAW_BIAS_NEIGHBOR_DEGREE), s);
+        const size_t before = hipsim::device_bytes_in_use(), room = 2 * guide + 2 * 16 * m;
+        limit_device(before + room);  // the guide would fit half of what the hop table and the rank index leave
+        hipsim_hooks::guides = hipsim_hooks::hops = hipsim_hooks::ranks = 0;
+        for (int rep = 0; rep < 60; ++rep) {
+            c.call.check(h, d.g, std::vector<int32_t>(4, CSAW_BIAS_EDGE_WEIGHT), s);
+            c.walks.check(h, d.g, CSAW_BIAS_UNIFORM, s);
+            c.walks.check(h, d.g, CSAW_BIAS_NODE2VEC, s);
+        }
+        CHECK(hipsim_hooks::guides.load() == 0 && hipsim_hooks::hops.load() == 1 && hipsim_hooks::ranks.load() == 1);
+        CHECK(hipsim::device_bytes_in_use() - before <= room / 2);
+        limit_device(0);
+        OK(csaw_graph_destroy(d.g));
+    }
+    {
+        Dev d = upload(h, s);
+        OK(csaw_set_walk_guides(d.g, 0));
+        Client c(h, d.g, 82);
+        hipsim_hooks::guides = hipsim_hooks::hops = hipsim_hooks::ranks = 0;
+        for (int rep = 0; rep < 20; ++rep) c.round();
+        CHECK(hipsim_hooks::guides.load() == 0 && hipsim_hooks::hops.load() == 0 && hipsim_hooks::ranks.load() == 0);
+        OK(csaw_set_walk_guides(d.g, 1));
+        for (int rep = 0; rep < 20; ++rep) c.round();
+        CHECK(hipsim_hooks::guides.load() == 2 && hipsim_hooks::hops.load() == 1 && hipsim_hooks::ranks.load() == 1);
+        OK(csaw_set_walk_guides(d.g, 0));
+        hipsim_hooks::with_guide = hipsim_hooks::with_hops = hipsim_hooks::with_rank = 0;
+        c.round();
+        CHECK(hipsim_hooks::with_guide.load() == 0 && hipsim_hooks::with_hops.load() == 0 &&
+              hipsim_hooks::with_rank.load() == 0);
+        OK(csaw_graph_destroy(d.g));
+    }
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -397,6 +457,7 @@ int main(int argc, char** argv) {
     else if (what == "tables") scenario_tables();
     else if (what == "room") scenario_room();
     else if (what == "give_back") scenario_give_back();
+    else if (what == "refused") scenario_refused();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;
