@@ -260,6 +260,9 @@ csaw_status csaw_get_tuning(csaw_graph g, csaw_tuning* tuning);
 /* Autotuner: runs csaw_sample(g, args, out, stream) under each candidate
  * setting (warm-up call, then `reps` timed calls; reps in [1, 100]), keeps
  * the fastest median on the graph and writes it to *chosen (HOST, nullable).
+ * The candidates are 0, 8, 16 and 32 as the longest list that a lane scans; where the
+ * call scans none (unbiased, or by guides) it runs once and the setting stays.
+ * Its calls build no walk guide and count towards none.
  * Other calls on the same graph while it runs use whichever candidate is
  * current; their results are unchanged.
  * The outputs are those of csaw_sample, identical under every setting. An

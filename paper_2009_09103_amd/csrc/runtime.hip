@@ -1005,7 +1005,9 @@ csaw_status csaw_sample_bound(csaw_graph g, const csaw_sample_args* a, int64_t* 
 // staged through its pinned block, long lists on its side stream, the launch
 // sequence captured and replayed), or, when scratch is set, from that
 // device scratch only: tables copied in, every kernel on the caller's
-// stream, launched directly, no allocation of any kind on the device.
+// stream, launched directly, no allocation of any kind on the device. A trial
+// (the autotuner's) neither builds a guide nor counts towards one: its timings
+// are of one route.
 struct Streamer;
 static csaw_status stream_layer(Streamer& st, const SampleLayer& p, int32_t l, int64_t cap, bool big_path,
                                 bool uses_ew, bool uses_deg, hipStream_t s);
@@ -1020,7 +1022,8 @@ static int select_grid(int64_t cap, int most) {
 }
 
 static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sample_out* out, csaw_stream stream,
-                               char* scratch, size_t scratch_bytes, Streamer* streamer = nullptr) {
+                               char* scratch, size_t scratch_bytes, Streamer* streamer = nullptr,
+                               bool trial = false) {
     if (!out) return fail(CSAW_ERR_INVALID_ARG, "out is NULL");
     SamplePlan P;
     csaw_status st = plan_sample(g, a, P, true);
@@ -1043,8 +1046,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     } else {
         if (P.uses_deg && (st = prepare_bias(g, kNeighborDegree, s)) != CSAW_OK) return st;
         if (P.uses_ew && (st = prepare_bias(g, kEdgeWeight, s)) != CSAW_OK) return st;
-        if (P.uses_deg && !streamer) guides_for_sampling(g, kNeighborDegree, s);
-        if (P.uses_ew && !streamer) guides_for_sampling(g, kEdgeWeight, s);
+        if (P.uses_deg && !streamer && !trial) guides_for_sampling(g, kNeighborDegree, s);
+        if (P.uses_ew && !streamer && !trial) guides_for_sampling(g, kEdgeWeight, s);
     }
 
     const int32_t ni = P.ni, L = P.L;
@@ -1343,8 +1346,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     rel.clean = use.drained = true;
     out->num_edges = L > 0 ? h_ctl->out_base[L] : 0;
     if (out->num_edges < 0) return fail(CSAW_ERR_DEVICE, "the device reported a negative edge count");
-    if (P.uses_deg) g->drawn_deg += out->num_edges;
-    if (P.uses_ew) g->drawn_ew += out->num_edges;
+    if (P.uses_deg && !trial) g->drawn_deg += out->num_edges;
+    if (P.uses_ew && !trial) g->drawn_ew += out->num_edges;
     if (h_ctl->bad_seed) return fail(CSAW_ERR_INVALID_ARG, "a seed is outside [0, n)");
     if (h_ctl->unsupported)
         return fail(CSAW_ERR_UNSUPPORTED, "a drawn fanout exceeds %d", CSAW_MAX_FANOUT);
@@ -1758,9 +1761,23 @@ csaw_status csaw_autotune_sample(csaw_graph g, const csaw_sample_args* a, csaw_s
     t_err.clear();
     if (!g) return fail(CSAW_ERR_INVALID_ARG, "graph is NULL");
     if (reps < 1 || reps > 100) return fail(CSAW_ERR_INVALID_ARG, "reps must be in [1, 100]");
-    static const csaw_tuning kCandidates[] = {{0, 0}, {8, 0}, {16, 0}, {0, 32}, {8, 32}, {16, 32}};
+    // one for each longest list that a lane scans
+    static const csaw_tuning kCandidates[] = {{0, 0}, {8, 0}, {16, 0}, {16, 32}};
     csaw_tuning prev;
     csaw_get_tuning(g, &prev);
+    SamplePlan P;
+    csaw_status st = plan_sample(g, a, P, true);
+    if (st != CSAW_OK) return st;
+    bool scans;  // some draws may be by scan
+    {
+        std::lock_guard<std::mutex> lk(g->mu);
+        const bool on = g->walk_guides.load() != 0;
+        scans = (P.uses_deg && !(on && g->tables->wgd_deg)) || (P.uses_ew && !(on && g->tables->wgd_ew));
+    }
+    if (!scans) {  // every setting is the same
+        if ((st = csaw_sample(g, a, out, stream)) == CSAW_OK && chosen) *chosen = prev;
+        return st;
+    }
     csaw_tuning best = prev;
     double best_t = 0;
     for (const csaw_tuning& c : kCandidates) {
@@ -1768,7 +1785,7 @@ csaw_status csaw_autotune_sample(csaw_graph g, const csaw_sample_args* a, csaw_s
         std::vector<double> ts;
         for (int r = 0; r <= reps; ++r) {  // call 0 warms up (and captures this setting's graph)
             const auto t0 = std::chrono::steady_clock::now();
-            const csaw_status st = csaw_sample(g, a, out, stream);  // returns after its stream drained
+            st = sample_call(g, a, out, stream, nullptr, 0, nullptr, true);  // returns after its stream drained
             const auto t1 = std::chrono::steady_clock::now();
             if (st != CSAW_OK) {
                 csaw_set_tuning(g, &prev);

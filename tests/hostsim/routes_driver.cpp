@@ -16,12 +16,14 @@
 //   driver refused    tables that do not fit are asked for ever more seldom, all
 //                     those that calls build by themselves take half of the free
 //                     memory at most, and none is built or used when turned off
+//   driver autotune   the autotuner's calls: one setting for each list length that
+//                     lanes scan, no guide on their account
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
 
 namespace hipsim_hooks {
-extern std::atomic<int64_t> misrouted, in_order, queries, guides, hops, ranks, with_guide, with_hops, with_rank;
+extern std::atomic<int64_t> misrouted, selects, in_order, queries, guides, hops, ranks, with_guide, with_hops, with_rank;
 extern std::atomic<size_t> device_limit;
 extern std::atomic<int32_t> stuck_layer;
 extern std::atomic<bool> stuck_list;
@@ -448,6 +450,35 @@ void scenario_refused() {
     (void)hipStreamDestroy(s);
 }
 
+void scenario_autotune() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_symmetric(1 << 10, 6 << 10, 43);
+    Dev d = upload(h, s);
+    Call c(h, d.g, 30, 40, {20});
+    const std::vector<int32_t> bias(30, CSAW_BIAS_NEIGHBOR_DEGREE);
+    csaw_sample_args a = c.args(bias);
+    csaw_tuning t{};
+    const int32_t reps = 20;
+    OK(csaw_autotune_sample(d.g, &a, &c.out, reps, s, &t));
+    c.check_edges(h, bias);
+    CHECK(c.out.num_edges * reps > (int64_t)h.col.size());
+    CHECK(hipsim_hooks::selects.load() == 4 * (reps + 1) && hipsim_hooks::guides.load() == 0);
+    c.check(h, d.g, bias, s);  // they paid for nothing
+    CHECK(hipsim_hooks::guides.load() == 0);
+    while (hipsim_hooks::guides.load() == 0) c.check(h, d.g, bias, s);
+    const csaw_tuning mine{5, 7};  // with the guide no list is scanned: one call, the setting stays
+    OK(csaw_set_tuning(d.g, &mine));
+    hipsim_hooks::selects = 0;
+    OK(csaw_autotune_sample(d.g, &a, &c.out, reps, s, &t));
+    c.check_edges(h, bias);
+    CHECK(hipsim_hooks::selects.load() == 1 && t.bound16 == 5 && t.bound32 == 7);
+    OK(csaw_get_tuning(d.g, &t));
+    CHECK(t.bound16 == 5 && t.bound32 == 7);
+    OK(csaw_graph_destroy(d.g));
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -458,6 +489,7 @@ int main(int argc, char** argv) {
     else if (what == "room") scenario_room();
     else if (what == "give_back") scenario_give_back();
     else if (what == "refused") scenario_refused();
+    else if (what == "autotune") scenario_autotune();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;

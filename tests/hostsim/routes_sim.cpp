@@ -20,6 +20,7 @@
 
 namespace hipsim_hooks {
 std::atomic<int64_t> misrouted{0};  // unbiased draws given to the kernel that draws by weight alone
+std::atomic<int64_t> selects{0};    // selection launches that ran
 std::atomic<int32_t> stuck_layer{-1};  // builds of this layer give up their chain by block index ...
 std::atomic<bool> stuck_list{false};   // ... in the compaction
 std::atomic<int64_t> in_order{0};      // builds whose blocks take tickets
@@ -148,6 +149,7 @@ void launch_mdrw(const MdrwParams& p, hipStream_t s, LaunchEvents ev) {
 void launch_select(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev) {
     hipsim::enqueue(s, [p] {
         read_tables(p.g);
+        ++hipsim_hooks::selects;
         for (int64_t e = 0; p.wave_only && e < p.ctl->fcount[p.layer]; ++e) {
             const int32_t P = p.fpos[e] & ~kWideList;
             if (p.bias[p.fi[e]] == kUniform && p.cnt[e] > 0 && p.cnt[e] < P) ++hipsim_hooks::misrouted;
