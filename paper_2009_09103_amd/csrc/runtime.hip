@@ -945,8 +945,9 @@ csaw_status csaw_graph_create(int64_t n, int64_t m, const int64_t* rowptr, const
     hipError_t e;
     if ((e = upload_rowptr(n, m, rowptr, &g->rowptr_mem, &g->rowptr, s)) != hipSuccess)
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "row offsets: %s", hipGetErrorString(e)));
+    // (the column ids as whole 16-byte quads, which node2vec lookups read at 16-byte steps from its start)
     if ((e = device_malloc((void**)&g->dflag, 256)) != hipSuccess ||
-        (e = device_malloc((void**)&g->col, std::max<int64_t>(m, 1) * sizeof(int32_t))) != hipSuccess ||
+        (e = device_malloc((void**)&g->col, align_up(std::max<int64_t>(m, 1), 4) * sizeof(int32_t))) != hipSuccess ||
         (edge_weight && (e = device_malloc((void**)&g->ew, std::max<int64_t>(m, 1) * sizeof(uint32_t))) != hipSuccess))
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "graph allocation failed: %s", hipGetErrorString(e)));
     if ((m > 0 && (e = hipMemcpyAsync(g->col, col, m * sizeof(int32_t), hipMemcpyHostToDevice, s)) != hipSuccess) ||

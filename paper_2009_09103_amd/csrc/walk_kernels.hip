@@ -1161,7 +1161,8 @@ __device__ __forceinline__ void rank_find(const RankStep& st, uint32_t n, const 
                                           uint32_t (&pos)[Q], bool (&hit)[Q], const Ahead& ahead) {
     const uint32_t lane = lane_id();
     if (len <= 256 * Q - 4) {
-        // whole 16-byte quads; what lies outside the stretch becomes -1 and the largest int
+        // whole 16-byte quads of the column ids (whose array is padded to one); what lies
+        // outside the stretch becomes -1 and the largest int
         const uint32_t skew = (st.lg_at + lo) & 3u, top = skew + len;
         const int32_t* from = st.lg + (int64_t)lo - skew;
         const int log = top < 256 ? 8 : 32 - __builtin_clz(top);  // 2^log > top

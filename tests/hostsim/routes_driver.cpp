@@ -415,6 +415,7 @@ void scenario_refused() {
     {
         Dev d = upload(h, s);
         Client c(h, d.g, 81);
+        CHECK(m % 4 == 2);  // (the last quad of column ids is not full)
         const size_t guide = 16 * m + 16 * n + 16 * (4 * m + n);
         c.call.check(h, d.g, std::vector<int32_t>(4, CSAW_BIAS_NEIGHBOR_DEGREE), s);
         const size_t before = hipsim::device_bytes_in_use(), room = 2 * guide + 2 * 16 * m;
