@@ -61,11 +61,21 @@ def small_bucket(c, d, k, take, wflag, long_, bound):
     return (c > 0) & ~long_ & (size <= bound)
 
 
-def slot_bytes(alg):
-    """The same bytes by the kernels that move them: one draws the entries of
-    both sizes, beside the long lists (which it draws too where the weight
-    array has its walk guide)."""
-    return {"select_slots": alg["select_small"] + alg["select_wave"], "select_big": alg["select_big"]}
+SELECT_SCOPES = {"select_slots": "k_select_slots", "select_wave": "k_select_wave<true>",
+                 "select_big": "k_select_wave<false> and k_select_big"}
+
+
+def select_bytes(alg, times):
+    """The same bytes by the profile scopes whose kernels move them, and the
+    main one: with its walk guide built a weight array's every list is drawn
+    by the slot kernel; before that it scans the lists under the bound and leaves
+    the others to the select_big scope, or, where it would have nothing to draw,
+    one wavefront kernel takes its place for all but the long lists."""
+    if times["select_big"][1] == 0:
+        return {"select_slots": sum(alg.values())}, "select_slots"
+    if times["select_wave"][1]:
+        return {"select_wave": alg["select_small"] + alg["select_wave"], "select_big": alg["select_big"]}, "select_wave"
+    return {"select_slots": alg["select_small"], "select_big": alg["select_wave"] + alg["select_big"]}, "select_slots"
 
 
 def path_bytes(rowptr, ppos, seeds, dst, offsets, fanouts, weighted, bound=0):
@@ -197,13 +207,13 @@ def bench_degree_biased(args):
         for k in alg:
             alg[k] += bytes_of[s][k]
     torch.cuda.synchronize()
-    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_big", "frontier_build",
-                                                "visited_clear")}
+    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_wave", "select_big",
+                                                "frontier_build", "visited_clear")}
     csaw.profile_enable(False)
     csaw.profile_reset()
-    alg = slot_bytes(alg)
-    sel_ms, sel_n = times["select_slots"]
-    achieved = alg["select_slots"] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
+    alg, main = select_bytes(alg, times)
+    sel_ms, sel_n = times[main]
+    achieved = alg[main] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
     per_kernel = {k: {"alg_bytes_per_step": alg[k] / args.steps, "ms_per_step": times[k][0] / args.steps,
                       "GB_per_s": alg[k] / (times[k][0] / 1e3) / 1e9 if times[k][0] > 0 else 0.0}
                   for k in alg}
@@ -231,9 +241,9 @@ def bench_degree_biased(args):
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic("traffic_select_degree_biased_rmat22.md"),
-                     "kernel": "select_slots (k_select_slots)", "launches": sel_n,
+                     "kernel": "%s (%s)" % (main, SELECT_SCOPES[main]), "launches": sel_n,
                      "avg_launch_us": sel_ms / max(sel_n, 1) * 1e3,
-                     "alg_bytes_per_launch": alg["select_slots"] / max(sel_n, 1)},
+                     "alg_bytes_per_launch": alg[main] / max(sel_n, 1)},
         "roofline_step": {"alg_bytes": step_bytes, "achieved": step_bytes / (dt / args.steps) / 1e9,
                           "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": step_bytes / (dt / args.steps) / 1e9 / HBM_PEAK_GBS},
@@ -326,13 +336,13 @@ def bench_batched(args):
     csaw.profile_enable(True)
     g.sample(offs, seeds_d, fanouts, bias, rng_seed=1, rounds=args.rounds, out=(src, dst, offsets))
     torch.cuda.synchronize()
-    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_big", "frontier_build",
-                                                "visited_clear")}
+    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_wave", "select_big",
+                                                "frontier_build", "visited_clear")}
     csaw.profile_enable(False)
     csaw.profile_reset()
-    alg = slot_bytes(alg)
-    sel_ms, sel_n = times["select_slots"]
-    achieved = alg["select_slots"] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
+    alg, main = select_bytes(alg, times)
+    sel_ms, sel_n = times[main]
+    achieved = alg[main] / (sel_ms / 1e3) / 1e9 if sel_ms > 0 else 0.0
     step_bytes = sum(alg.values())
     # plain: one call per instance (same ids, same seed)
     per = []
@@ -362,9 +372,10 @@ def bench_batched(args):
         "config": {"workload": rec["name"], "instances": ni, "seeds": int(len(seeds)),
                    "edges_per_step": int(edges), "tuning": tuning, "rounds": args.rounds or 8},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "select_slots (k_select_slots)",
+                     "frac": achieved / HBM_PEAK_GBS, "traffic": None,
+                     "kernel": "%s (%s)" % (main, SELECT_SCOPES[main]),
                      "launches": sel_n, "avg_launch_us": sel_ms / max(sel_n, 1) * 1e3,
-                     "alg_bytes_per_launch": alg["select_slots"] / max(sel_n, 1)},
+                     "alg_bytes_per_launch": alg[main] / max(sel_n, 1)},
         "roofline_step": {"alg_bytes": step_bytes, "achieved": step_bytes / dt / 1e9, "peak": HBM_PEAK_GBS,
                           "unit": "GB/s", "frac": step_bytes / dt / 1e9 / HBM_PEAK_GBS},
         "kernels": {k: {"alg_bytes_per_step": alg[k], "ms_per_step": times[k][0],
@@ -580,7 +591,7 @@ def bench_served(args):
     trace = inputs.request_trace(rp, col, args.requests, best["qps"], rec["trace_rng"], rec["sample_fraction"])
     _, results = run_server(csaw, g, trace, served_kw, profile=True)
     kernels = {}
-    for name in ("walk", "select_slots", "select_big", "frontier_build", "frontier_init",
+    for name in ("walk", "select_slots", "select_wave", "select_big", "frontier_build", "frontier_init",
                  "visited_clear"):
         ms, n = csaw.profile_read(name)
         kernels[name] = {"ms": ms, "launches": n}
@@ -613,7 +624,7 @@ def bench_served(args):
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": walk_traffic,
                      "measured_copy_GBps": copy_gbps, "frac_of_copy": achieved / copy_gbps,
-                     "kernel": "walk (k_walk_lane and k_walk_wave_first, edge-weight walks)", "launches": kernels["walk"]["launches"],
+                     "kernel": "walk (k_walk_lane and k_walk_wave_guide, edge-weight walks)", "launches": kernels["walk"]["launches"],
                      "avg_launch_us": walk_ms * 1e3 / max(kernels["walk"]["launches"], 1),
                      "alg_bytes_per_launch": wbytes / max(kernels["walk"]["launches"], 1),
                      "steps": wsteps,
@@ -729,8 +740,8 @@ def bench_forest_fire(args):
     for _ in range(args.steps):
         g.sample(offs, seeds_d, fan, csaw.UNIFORM, **call)
     torch.cuda.synchronize()
-    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_big", "frontier_build",
-                                                "visited_clear")}
+    times = {k: csaw.profile_read(k) for k in ("frontier_init", "select_slots", "select_wave", "select_big",
+                                                "frontier_build", "visited_clear")}
     csaw.profile_enable(False)
     csaw.profile_reset()
     sel_ms = times["select_slots"][0] / args.steps
@@ -849,7 +860,7 @@ def bench_walks(args):
                      "traffic": per_step * wsteps / max(kn, 1) if per_step else None,
                      "traffic_GBps": per_step * wsteps / (kms / 1e3) / 1e9 if per_step and kms > 0 else None,
                      "measured_copy_GBps": copy_gbps, "kernel": "k_walk_lane<false>" if nw >= 12288 else
-                     "k_walk_wave_first", "launches": kn, "avg_launch_us": kms / max(kn, 1) * 1e3,
+                     "k_walk_wave_guide<false>", "launches": kn, "avg_launch_us": kms / max(kn, 1) * 1e3,
                      "alg_bytes_per_launch": alg / max(kn, 1), "steps_per_s": wsteps / (kms / 1e3)},
     }
     if not args.no_cpu_baseline:

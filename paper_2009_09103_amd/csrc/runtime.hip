@@ -1240,11 +1240,13 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                 HIP_OR_FAIL(hipStreamWaitEvent(aux, ws->fork, 0));
             }
             if (big_path) {
-                ProfScope ps("select_big", aux, true);
+                // (a kernel for the lists of up to kWaveMaxD weights, unless the
+                // main stream's draws them, and one for the longer ones)
+                ProfScope ps("select_big", aux, wave_only);
                 launch_select_big(p, select_grid(cap, 2048), aux, ps.ev());
             }
             {
-                ProfScope ps("select_slots", s, true);
+                ProfScope ps(wave_only ? "select_wave" : "select_slots", s, true);
                 launch_select(p, select_grid(cap, kSelectBlocks), s, ps.ev());
             }
             if (beside) {
