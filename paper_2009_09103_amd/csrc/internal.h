@@ -26,9 +26,10 @@ csaw_status sample_plan_caps(csaw_graph g, const csaw_sample_args* a, std::vecto
 
 // Device scratch of a sampling call of num_instances instances, num_layers
 // layers and per-layer frontier capacities fcap (summed over instances) that
-// runs in caller memory: arena, both instance bitmaps, control block copy.
+// runs in caller memory: arena, both instance bitmaps; where that is more than
+// `room`, of the same call in its compact layout (dense frontier builds).
 size_t sample_scratch_bytes(csaw_graph g, int32_t num_instances, int32_t num_layers,
-                            const std::vector<int64_t>& fcap);
+                            const std::vector<int64_t>& fcap, size_t room);
 
 // csaw_sample / csaw_walk with every device byte in `scratch` (no
 // allocation, no capture, every kernel on `stream`).

@@ -241,6 +241,9 @@ int64_t sparse_build_blocks(int64_t capacity);
 // reads every word; 37 instances on R-MAT 22 (4.8M words) take 48 and 69 us a
 // layer densely, 17 and 25 us through the summary and the dirty words.
 constexpr int64_t kSparseWords = int64_t(1) << 20;
+// ... and above which they are so in memory that is short too: the dirty list
+// takes 8 bytes per frontier entry, which a dense build does without.
+constexpr int64_t kSparseMost = int64_t(1) << 23;
 void launch_frontier_build(const FrontierBuild& fb, hipStream_t s, LaunchEvents ev = {});
 // Every entry that a lane per slot serves (all but the weighted draws below).
 void launch_select(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev = {});

@@ -792,8 +792,7 @@ int64_t summary_words_per_instance(int64_t nwp) { return (int64_t)align_up((size
 
 // Device memory of one sampling call, from its shape alone: the arena (control
 // block, look-back words, tables, per-entry arrays, frontiers), then, for calls
-// in a caller's scratch, the two bitmaps and the copy of the final control
-// block. The small tables have the same layout in host memory.
+// in a caller's scratch, the two bitmaps. The small tables have the same layout in host memory.
 struct SampleLayout {
     bool sparse;                   // frontier builds through a summary bitmap and a dirty-word list
     int64_t nsw;                   // summary words per instance (sparse)
@@ -802,11 +801,14 @@ struct SampleLayout {
     size_t o_ctl, o_status, ctl_words, o_tab, o_cnt, o_off, o_fbeg, o_fdeg, o_fpos, o_bigs, o_dirty;
     std::vector<size_t> o_fv, o_fi;
     size_t arena;                  // bytes of the arena part
-    size_t o_bits, o_copy, scratch;
+    size_t o_bits, scratch;
     int64_t nb_build;
 };
 
-bool layout_sample(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int64_t nwp, SampleLayout& y) {
+// compact: for a caller's scratch that the call does not fit otherwise, dense builds
+// up to kSparseMost words, which need no dirty list (8 bytes per frontier entry).
+bool layout_sample(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int64_t nwp, SampleLayout& y,
+                   bool compact = false) {
     int64_t maxF = 0, sumF = 0;
     for (int l = 0; l <= L; ++l) {
         maxF = std::max(maxF, fcap[l]);
@@ -814,7 +816,7 @@ bool layout_sample(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int6
     }
     if (sumF > (int64_t(1) << 40)) return false;
     const int64_t words = nwp * ni;
-    y.sparse = words > kSparseWords;
+    y.sparse = words > (compact ? kSparseMost : kSparseWords);
     y.nsw = y.sparse ? summary_words_per_instance(nwp) : 0;
     y.bitmap_words = words * 2 + y.nsw * ni;
     if (y.sparse) {  // look-back words for the compaction and for the widest dirty-word build
@@ -848,7 +850,7 @@ bool layout_sample(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int6
     y.o_fdeg = cv.take<int32_t>(F);
     y.o_fpos = cv.take<int32_t>(F);
     y.o_bigs = cv.take<int32_t>(F);
-    y.o_dirty = y.sparse ? cv.take<int64_t>(F) : 0;  // a dirty word holds at least one frontier vertex
+    y.o_dirty = y.sparse ? cv.take<int64_t>(F) : 0;  // a dirty word holds at least one pick
     y.o_fv.assign(L + 1, 0);
     y.o_fi.assign(L + 1, 0);
     for (int l = 0; l <= L; ++l) {
@@ -857,9 +859,14 @@ bool layout_sample(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int6
     }
     y.arena = cv.off;
     y.o_bits = align_up(cv.off, 256);
-    y.o_copy = align_up(y.o_bits + (size_t)y.bitmap_words * sizeof(uint32_t), 256);
-    y.scratch = y.o_copy + sizeof(SampleCtl);
+    y.scratch = align_up(y.o_bits + (size_t)y.bitmap_words * sizeof(uint32_t), 256);
     return true;
+}
+
+// The layout of a call in `room` bytes of scratch: the compact one where only that fits.
+bool layout_in_scratch(int32_t ni, int32_t L, const std::vector<int64_t>& fcap, int64_t nwp, size_t room,
+                       SampleLayout& y) {
+    return layout_sample(ni, L, fcap, nwp, y) && (y.scratch <= room || layout_sample(ni, L, fcap, nwp, y, true));
 }
 
 // Host check of a CSR graph (O(n + m)): bounds, monotone offsets, ids in
@@ -1062,7 +1069,8 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
     const int64_t nwp = bitmap_words_per_instance(g->n);
     const int64_t words = nwp * ni;
     SampleLayout lay;
-    if (!layout_sample(ni, L, P.fcap, nwp, lay)) return fail(CSAW_ERR_OUT_OF_MEMORY, "frontier bound too large");
+    if (!(scratch ? layout_in_scratch(ni, L, P.fcap, nwp, scratch_bytes, lay) : layout_sample(ni, L, P.fcap, nwp, lay)))
+        return fail(CSAW_ERR_OUT_OF_MEMORY, "frontier bound too large");
     const int64_t nb_build = lay.nb_build;
     const size_t t_fan = lay.t_fan, t_bias = lay.t_bias, t_iid = lay.t_iid, t_key = lay.t_key, t_soff = lay.t_soff;
     const size_t tab_bytes = lay.tab_bytes;
@@ -1084,7 +1092,7 @@ static csaw_status sample_call(csaw_graph g, const csaw_sample_args* a, csaw_sam
                         lay.scratch, scratch_bytes);
         A = scratch;
         bitmaps = (uint32_t*)(scratch + lay.o_bits);
-        ctl_copy = (SampleCtl*)(scratch + lay.o_copy);
+        ctl_copy = (SampleCtl*)(scratch + lay.o_ctl);  // (read from there)
         host_tables.resize(o_hctl + sizeof(SampleCtl));
         H = host_tables.data();
     }
@@ -2105,9 +2113,9 @@ csaw_status sample_plan_caps(csaw_graph g, const csaw_sample_args* a, std::vecto
     return CSAW_OK;
 }
 
-size_t sample_scratch_bytes(csaw_graph g, int32_t ni, int32_t L, const std::vector<int64_t>& fcap) {
+size_t sample_scratch_bytes(csaw_graph g, int32_t ni, int32_t L, const std::vector<int64_t>& fcap, size_t room) {
     SampleLayout lay;
-    if (!layout_sample(ni, L, fcap, bitmap_words_per_instance(g->n), lay)) return SIZE_MAX;
+    if (!layout_in_scratch(ni, L, fcap, bitmap_words_per_instance(g->n), room, lay)) return SIZE_MAX;
     return lay.scratch;
 }
 

@@ -339,8 +339,11 @@ __device__ __forceinline__ void block_excl_scan4(int64_t (&x)[4], int64_t (&tot)
     __syncthreads();
 }
 
-// Frontier build of one layer, one pass: each thread takes one bitmap word, of all
-// of them (dense) or of those in the dirty list (sparse); it counts the new bits (entries), their edge counts min(k, P)
+// Frontier build of one layer, one pass: each thread takes kPer consecutive
+// bitmap words, of all of them (dense) or of those in the dirty list (sparse, one
+// word). Dense builds take one up to kSparseWords, and kWidePer above, where a
+// call is short of memory: a sixteenth of the look-back words. The thread counts
+// the new bits (entries), their edge counts min(k, P)
 // (edges) and their long-list route (the words and the list fields are
 // loaded again in the write pass rather than held in registers across the
 // scan, which keeps occupancy up); a block scan plus a decoupled look-back
@@ -349,8 +352,10 @@ __device__ __forceinline__ void block_excl_scan4(int64_t (&x)[4], int64_t (&tot)
 // sets visited |= next, clears next, and the first word of an instance writes
 // that instance's segment offset. The last block writes the layer's totals
 // and the output base of the next layer.
-template <bool kBurn, bool kSparse>
+constexpr int kWidePer = 16;
+template <bool kBurn, bool kSparse, int kPer>
 __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
+    static_assert(!kSparse || kPer == 1, "the dirty list gives one word per thread");
     __shared__ int64_t s_base_e, s_base_g;
     const int tid = threadIdx.x;
     // dense: every word of the bitmaps; sparse: the words of the dirty list
@@ -363,37 +368,47 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
         if (blockIdx.x >= nb) return;
     }
     const int64_t b = chain_place(&fb.ctl->tickets[fb.layer][0], fb.ordered);
-    const int64_t w0 = b * kBlock + tid;  // the thread's word, or dirty word
-    const int64_t iw = kSparse ? (w0 < nwords ? fb.dirty[w0] : 0) : w0;
+    const int64_t w0 = (b * kBlock + tid) * kPer;  // the thread's first word, or its dirty word
+    int64_t iw = kSparse ? (w0 < nwords ? fb.dirty[w0] : 0) : w0;
     const int64_t out_base = fb.ctl->out_base[fb.layer];
-    const uint32_t raw = w0 < nwords ? fb.next[iw] : 0u, vis = w0 < nwords ? fb.visited[iw] : 0u;
-    const uint32_t w = raw & ~vis;  // picks of visited vertices are not new
-    const int64_t inst = iw / fb.nwp;
-    const int32_t vbase = (int32_t)((iw - inst * fb.nwp) * 32);
-    int32_t k = 0, kind = 0;
+    uint32_t raw = 0, vis = 0, w = 0;  // word iw, its visited bits, the new ones
+    int64_t inst = 0;
+    int32_t vbase = 0, k = 0, kind = 0;
     uint64_t key = 0;
     uint32_t iid = 0;
-    if (w) {
-        k = fb.fanout[inst];
-        kind = fb.bias[inst];
-        if (kBurn) {
-            key = fb.inst_key[inst];
-            iid = fb.inst_id[inst];
+    const auto load = [&](int t) {
+        if (!kSparse) iw = w0 + t;
+        raw = w0 + t < nwords ? fb.next[iw] : 0u;
+        vis = w0 + t < nwords && (kPer == 1 || raw) ? fb.visited[iw] : 0u;
+        w = raw & ~vis;  // picks of visited vertices are not new
+        inst = iw / fb.nwp;
+        vbase = (int32_t)((iw - inst * fb.nwp) * 32);
+        if (w) {
+            k = fb.fanout[inst];
+            kind = fb.bias[inst];
+            if (kBurn) {
+                key = fb.inst_key[inst];
+                iid = fb.inst_id[inst];
+            }
         }
-    }
-    int64_t cnt4[4] = {__popc(w), 0, 0, 0};  // entries, edges, long lists, (unused)
-    for (uint32_t bits = w; bits;) {  // four bits at a time so that their loads overlap
-        int32_t bv[4];
+    };
+    int64_t cnt4[4] = {0, 0, 0, 0};  // entries, edges, long lists, (unused)
+    for (int at = 0; at < kPer; ++at) {
+        load(at);
+        cnt4[0] += __popc(w);
+        for (uint32_t bits = w; bits;) {  // four bits at a time so that their loads overlap
+            int32_t bv[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) bv[t] = pop_bit(bits);
+            for (int t = 0; t < 4; ++t) bv[t] = pop_bit(bits);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            int32_t route = kRouteWave, pinfo = 0;
-            int64_t beg = 0, d = 0;
-            if (bv[t] >= 0) {
-                const int32_t kv = neighbor_size<kBurn>(k, fb.burn, key, iid, fb.layer, vbase + bv[t]);
-                cnt4[1] += entry_count(fb.g, kv, kind, vbase + bv[t], route, beg, d, pinfo, fb.ctl);
-                if (route == kRouteBig) ++cnt4[2];
+            for (int t = 0; t < 4; ++t) {
+                int32_t route = kRouteWave, pinfo = 0;
+                int64_t beg = 0, d = 0;
+                if (bv[t] >= 0) {
+                    const int32_t kv = neighbor_size<kBurn>(k, fb.burn, key, iid, fb.layer, vbase + bv[t]);
+                    cnt4[1] += entry_count(fb.g, kv, kind, vbase + bv[t], route, beg, d, pinfo, fb.ctl);
+                    if (route == kRouteBig) ++cnt4[2];
+                }
             }
         }
     }
@@ -419,7 +434,8 @@ __global__ void __launch_bounds__(kBlock) k_frontier_build(FrontierBuild fb) {
     __syncthreads();
     int64_t pos = s_base_e + ex_e;
     int64_t eoff = s_base_g + ex_g;
-    if (w0 < nwords) {
+    for (int at = 0; at < kPer && w0 + at < nwords; ++at) {
+        if (kPer > 1) load(at);
         if (fb.offsets && fb.layer < fb.num_layers) {
             if (!kSparse) {
                 if (vbase == 0) fb.offsets[(int64_t)fb.layer * fb.num_instances + inst] = out_base + eoff;
@@ -1990,7 +2006,7 @@ __global__ void k_call_setup(uint32_t* __restrict__ ctl, int64_t nctl, const uin
 // End of a call: clear the visited bits of every frontier entry, and hand
 // the control block to the host.
 __global__ void k_clear_visited(ClearVisited c) {
-    if (blockIdx.x == 0) {
+    if (blockIdx.x == 0 && c.host_ctl != c.ctl) {
         constexpr int kWords = (int)(sizeof(SampleCtl) / 4);
         const uint32_t* from = (const uint32_t*)c.ctl;
         uint32_t* to = (uint32_t*)c.host_ctl;
@@ -2088,19 +2104,25 @@ void launch_mark_seeds(const int32_t* seeds, int64_t num_seeds, const int64_t* s
                        num_seeds, seed_offsets, ni, n, next, nwp, summ, nsw, ctl);
 }
 
+// Bitmap words per thread of a dense build.
+static int dense_words(int64_t words) { return words > kSparseWords ? kWidePer : 1; }
+
 int64_t frontier_build_blocks(int64_t words) {
-    const int64_t nb = (words + kBlock - 1) / kBlock;
+    const int64_t per = (int64_t)kBlock * dense_words(words);
+    const int64_t nb = (words + per - 1) / per;
     return nb > 0 ? nb : 1;
 }
 
 void launch_frontier_build(const FrontierBuild& fb, hipStream_t s, LaunchEvents ev) {
+    const dim3 grid((unsigned)fb.nb), block(kBlock);
     if (fb.summ) {  // sparse: compact the summary, then one thread per dirty word
-        hipLaunchKernelGGL(k_dirty_compact, dim3((unsigned)fb.nb_dirty), dim3(kBlock), 0, s, fb);
-        launch_kernel(fb.burn ? k_frontier_build<true, true> : k_frontier_build<false, true>, dim3((unsigned)fb.nb),
-                      dim3(kBlock), s, ev, fb);
+        hipLaunchKernelGGL(k_dirty_compact, dim3((unsigned)fb.nb_dirty), block, 0, s, fb);
+        launch_kernel(fb.burn ? k_frontier_build<true, true, 1> : k_frontier_build<false, true, 1>, grid, block, s, ev, fb);
+    } else if (dense_words(fb.nwords) == 1) {
+        launch_kernel(fb.burn ? k_frontier_build<true, false, 1> : k_frontier_build<false, false, 1>, grid, block, s, ev, fb);
     } else {
-        launch_kernel(fb.burn ? k_frontier_build<true, false> : k_frontier_build<false, false>, dim3((unsigned)fb.nb),
-                      dim3(kBlock), s, ev, fb);
+        launch_kernel(fb.burn ? k_frontier_build<true, false, kWidePer> : k_frontier_build<false, false, kWidePer>, grid,
+                      block, s, ev, fb);
     }
 }
 

@@ -222,7 +222,9 @@ struct BatchLayout {
     size_t o_seeds, o_src, o_dst, o_off, o_scratch, scratch, total;
 };
 
-BatchLayout batch_layout(csaw_graph g, const BatchShape& b) {
+// (compact where the block has only `room` bytes: a request alone; batches are
+// formed without)
+BatchLayout batch_layout(csaw_graph g, const BatchShape& b, size_t room = SIZE_MAX) {
     BatchLayout y;
     size_t at = 0;
     y.o_seeds = at;
@@ -235,7 +237,7 @@ BatchLayout batch_layout(csaw_graph g, const BatchShape& b) {
     at = align_up(at + ((size_t)b.L * b.ni + 1) * sizeof(int64_t));
     y.o_scratch = at;
     const std::vector<int64_t> fc(b.fcap.begin(), b.fcap.begin() + b.L + 1);
-    y.scratch = csaw::sample_scratch_bytes(g, b.ni, b.L, fc);
+    y.scratch = csaw::sample_scratch_bytes(g, b.ni, b.L, fc, room > at ? room - at : 0);
     y.total = y.scratch == SIZE_MAX ? SIZE_MAX : at + y.scratch;
     return y;
 }
@@ -450,7 +452,7 @@ void csaw_server_s::run_sample_batch(std::vector<Request*>& batch, Exec& x, Cloc
     BatchShape shape;
     for (Request* r : batch) shape.add(*r);
     const int32_t L = shape.L;
-    const BatchLayout lay = batch_layout(g, shape);
+    const BatchLayout lay = batch_layout(g, shape, x.bytes);
     csaw_status stt = lay.total <= x.bytes ? CSAW_OK : CSAW_ERR_OUT_OF_MEMORY;  // batches are formed to fit
     std::vector<int64_t> offs(ni + 1, 0);
     for (int32_t i = 0; i < ni; ++i) offs[i + 1] = offs[i] + (int64_t)batch[i]->seeds.size();
@@ -803,7 +805,7 @@ csaw_status csaw_server_submit(csaw_server s, const csaw_request* q, uint64_t* t
         }
         BatchShape one;
         one.add(*r);
-        r->need = batch_layout(s->g, one).total;
+        r->need = batch_layout(s->g, one, s->exec_bytes).total;
     } else if (q->kind == CSAW_REQUEST_WALK) {
         if (q->num_walkers < 0 || (q->num_walkers > 0 && !q->starts) || q->length < 0 || q->bias_kind < 0 ||
             q->bias_kind > CSAW_BIAS_METROPOLIS_HASTINGS) {

@@ -18,6 +18,8 @@
 //                     memory at most, and none is built or used when turned off
 //   driver autotune   the autotuner's calls: one setting for each list length that
 //                     lanes scan, no guide on their account
+//   driver scratch    a call that fills the library's own scratch without room for
+//                     a dirty list
 #define main other_scenarios
 #include "driver.cpp"
 #undef main
@@ -480,6 +482,20 @@ void scenario_autotune() {
     (void)hipStreamDestroy(s);
 }
 
+// 9 instances of 5,035 seeds on 2^22 vertices: 1.2M bitmap words; at most 2.9M picks of layer 0 at
+// 40 bytes each in the scratch of 128 MiB, not at 48.
+void scenario_scratch() {
+    hipStream_t s;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    const Host h = make_graph(1 << 22, 500000, 45);
+    Dev d = upload(h, s);
+    Call c(h, d.g, 9, 5035, {64, 1});
+    c.check(h, d.g, std::vector<int32_t>(9, CSAW_BIAS_UNIFORM), s, true);
+    c.check(h, d.g, std::vector<int32_t>(9, CSAW_BIAS_EDGE_WEIGHT), s, true);
+    OK(csaw_graph_destroy(d.g));
+    (void)hipStreamDestroy(s);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -491,6 +507,7 @@ int main(int argc, char** argv) {
     else if (what == "give_back") scenario_give_back();
     else if (what == "refused") scenario_refused();
     else if (what == "autotune") scenario_autotune();
+    else if (what == "scratch") scenario_scratch();
     else return other_scenarios(argc, argv);
     std::printf("ok %s\n", what.c_str());
     return 0;

@@ -21,7 +21,7 @@ def drivers(tmp_path_factory):
         return {k: sim.build(k, out) for k in sim.FLAGS}
 
 
-@pytest.mark.parametrize("scenario", ["replay", "retry", "tables", "room", "give_back", "refused", "autotune"])
+@pytest.mark.parametrize("scenario", ["replay", "retry", "tables", "room", "give_back", "refused", "autotune", "scratch"])
 @pytest.mark.parametrize("kind", ["asan", "tsan"])
 def test_routes_under_sanitizers(drivers, kind, scenario):
     sim.run(drivers[kind], scenario)
