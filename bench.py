@@ -15,8 +15,8 @@ and the CPU oracle timed on a sample of the trace on the host.
 --workload degree_biased: one full csaw_sample call per step (every layer:
 frontier build, select, long-list search) over R-MAT 22 (edge factor 16), one
 instance of 8,192 distinct seeds, fanouts [25, 10, 5], bias = out-degree of
-the neighbor, Philox seeds cycling over {1, 2, 3}; the sub-wave bucket
-setting is autotuned on the timed call first (--tuning).
+the neighbor, Philox seeds cycling over {1, 2, 3}; the longest list that
+lanes scan is autotuned on the timed call first (--tuning).
 
 Other workloads: batched (4,096 instances in one call against 4,096 plain
 calls), node2vec (R-MAT 24 walks), mdrw (multi-dimensional random walks),
@@ -1157,7 +1157,7 @@ def main():
     ap.add_argument("--rounds", type=int, default=0,
                     help="repeated-sampling rounds before the direct draws: 0 (default 8), 1..8, -1 (none)")
     ap.add_argument("--tuning", default="auto",
-                    help='sub-wave buckets of the sampling kernel: "auto", "default" or "bound16,bound32"')
+                    help='lists that lanes of the sampling kernel scan: "auto", "default" or "bound16,bound32"')
     ap.add_argument("--n2v-stride", type=int, default=64)
     ap.add_argument("--partitions", type=int, default=4)
     ap.add_argument("--resident", type=int, default=2)

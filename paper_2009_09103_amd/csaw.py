@@ -342,7 +342,7 @@ class Graph:
         return res, (t.bound16, t.bound32)
 
     def set_tuning(self, bound16: int, bound32: int):
-        """Sub-wave bucket bounds of the sampling kernel (csaw_set_tuning)."""
+        """Longest lists that lanes of the sampling kernel scan (csaw_set_tuning)."""
         t = Tuning(int(bound16), int(bound32))
         _check(lib.csaw_set_tuning(self._h, ctypes.byref(t)))
 

@@ -238,8 +238,12 @@ int64_t dirty_compact_blocks(int64_t summary_words);
 int64_t sparse_build_blocks(int64_t capacity);
 // Bitmap words (all instances) above which frontier builds are sparse: one
 // instance of a 2^25-vertex graph or eight of a 2^22-vertex one. A dense build
-// reads every word; 37 instances on R-MAT 22 (4.8M words) take 48 and 69 us a
-// layer densely, 17 and 25 us through the summary and the dirty words.
+// reads every word, a sparse one the summary and the dirty words, in one launch
+// more; what a sparse one adds in memory (8 bytes per frontier entry) is the reason
+// to stay dense below. Two-layer calls of 64 seeds an instance on R-MAT 22, sparse
+// against dense: 73 and 76 us at 2^17 words, 76 and 100 at 2^19, 80 and 138 at
+// 2^20, 84 and 208 at 2^21, 102 and 624 at 2^23; by time alone the line could
+// lie at 2^17.
 constexpr int64_t kSparseWords = int64_t(1) << 20;
 // ... and above which they are so in memory that is short too: the dirty list
 // takes 8 bytes per frontier entry, which a dense build does without.
@@ -254,7 +258,7 @@ void launch_chunk_table(RowPtr rowptr, const uint32_t* w, int64_t n, uint64_t* t
                         hipStream_t s);
 // Weighted draws from lists without a walk guide that are too long for a lane
 // to scan: the list in a wavefront's registers, or searched through the
-// chunk prefix table. The layer needs it only where needs_list_kernels says so.
+// chunk prefix table. A call needs it where some instance draws by a weight array without its guide.
 void launch_select_big(const SampleLayer& p, int grid, hipStream_t s, LaunchEvents ev = {});
 // Clears the visited bits of every frontier entry of the call's layers.
 struct ClearVisited {

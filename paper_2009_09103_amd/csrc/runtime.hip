@@ -288,7 +288,7 @@ struct csaw_graph_s {
     std::mutex mu;                 // lazy preparation + workspace pool
     std::condition_variable idle;  // a call let go of its tables
     std::vector<Workspace*> pool;
-    std::atomic<int32_t> bound16{kDefaultBound16}, bound32{kDefaultBound32};  // sub-wave buckets
+    std::atomic<int32_t> bound16{kDefaultBound16}, bound32{kDefaultBound32};  // longest lists that lanes scan
     std::atomic<int32_t> walk_guides{1};  // calls build and use walk guides, hop table and rank index
     std::atomic<int64_t> drawn_ew{0}, drawn_deg{0};  // edges that sampling calls drew, per weight array
     std::atomic<int64_t> hopped{0};                  // unbiased steps asked for (see prepare_hops)
@@ -1020,10 +1020,10 @@ struct Streamer;
 static csaw_status stream_layer(Streamer& st, const SampleLayer& p, int32_t l, int64_t cap, bool big_path,
                                 bool uses_ew, bool uses_deg, hipStream_t s);
 
-// Blocks of a selection launch over at most cap entries: a wavefront per entry
-// while they fit the chip's 8,192 resident ones (small launches are bound by one
-// wavefront's chain of loads), then up to twice that many for the dispatcher to
-// balance, each taking a run of consecutive entries.
+// Blocks of a selection launch over at most cap entries: room for a wavefront per
+// entry (small launches are bound by one wavefront's chain of loads) up to 16,384
+// wavefronts, about three times what the chip holds of the slot kernel at once, so
+// that the dispatcher balances them; each takes a run of consecutive entries.
 constexpr int kSelectBlocks = 4096;
 static int select_grid(int64_t cap, int most) {
     return (int)std::min<int64_t>(std::max<int64_t>((cap + 3) / 4, 1), most);

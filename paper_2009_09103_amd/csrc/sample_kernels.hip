@@ -911,8 +911,8 @@ __device__ __forceinline__ void emit_slots(const SampleLayer& p, const EntryInfo
 // Philox block, one search and one column load serve the slots of several
 // entries at once, and small fanouts leave few lanes idle. A slot finds its
 // candidate by itself: an unbiased draw is its position; a weighted draw goes
-// through the list's walk guide (a bucket pair, about 80% of the time nothing
-// else, whatever the list's length); without a guide a list of at most
+// through the list's walk guide (one bucket, which decides nine draws in ten,
+// whatever the list's length); without a guide a list of at most
 // `bound` weights is scanned by each lane (the lanes of an entry read the
 // same few words). Longer lists without a guide are left to k_select_wave and
 // k_select_big.
