@@ -100,7 +100,13 @@ __device__ __forceinline__ void count_steps(int64_t steps, unsigned long long* c
 // when it is evicted, over and over; a run of a line's length reaches its line
 // (or two) at once. 2^20 unbiased walkers x 80: 2.63 ms with runs of 8, 2.53
 // with 16, 2.37 with 32 and 2.25 with 64, although the registers cost
-// occupancy; 262,144 weighted walkers: 1.05 ms with 8 to 32, 1.12 with 64.
+// occupancy; 262,144 weighted walkers: 1.05 ms with 8 to 32, 1.12 with 64. A
+// launch whose lines stay in the L2 until they are full only pays for the run, in
+// registers and in each step's chain, and stores every entry at once (runs of 1):
+// R-MAT 22, length 80, runs of 1 against the long ones: unbiased 74 and 118 us for 1,000
+// walkers, 128 and 158 for 65,536, 241 and 202 for 131,072; weighted, by lanes, 254 and
+// 273 for 12,288, 260 and 278 for 32,768, 304 and 290 for 65,536.
+constexpr int64_t kUniformRunMin = 98304, kLaneRunMin = 57344;
 typedef int32_t PathQuad __attribute__((ext_vector_type(4), aligned(4)));
 template <int kPathRun>
 struct PathRun {
@@ -127,6 +133,13 @@ struct PathRun {
     }
 };
 
+template <>
+struct PathRun<1> {
+    int64_t at = 1;
+    __device__ __forceinline__ void flush(int32_t*) {}
+    __device__ __forceinline__ void push(int32_t* path, int32_t x) { path[at++] = x; }
+};
+
 // v's list.
 __device__ __forceinline__ void list_of(const GraphDev& g, int32_t v, int64_t& beg, int64_t& d) {
     beg = g.rowptr[v];
@@ -138,11 +151,16 @@ __device__ __forceinline__ void list_of(const GraphDev& g, int32_t v, int64_t& b
 // its list), plus its share of a path run; without the table, the neighbor id
 // and then its row offsets. Scattered lines bound it (41e9 a second on this
 // chip): 2^20 walkers x 80 on 500M edges took 4.96 ms with two reads a step and
-// a 4-byte path store each, 2.25 ms with one read and runs.
+// a 4-byte path store each, 2.23 ms with one read and runs.
+// kMoves: the call restarts or jumps. Lanes that move wait for their list with the
+// others (in a step of their own, 1,000 walkers x 80 with restarts took 189 us on
+// R-MAT 22, 144 now); walks without moves do without the test, and its registers
+// (262,144 Metropolis-Hastings walkers x 80: 290 us with it, 239 without).
+// kRun: see PathRun.
 // kMH: Metropolis-Hastings (Section II-A): the uniform pick u is a proposal,
 // accepted iff x * deg(u) < deg(v) * 2^32 for x in [0, 2^32) drawn with
 // counter (walker id, step, v, 4); a rejected proposal is a step that stays.
-template <bool kMH, bool kHops>
+template <bool kMH, bool kHops, bool kMoves, int kRun>
 __global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t w0 = blockIdx.x * (int64_t)blockDim.x; w0 < p.num_walkers; w0 += stride) {
@@ -164,32 +182,30 @@ __global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
                 path[0] = v;
                 const int32_t start = v;
                 const uint32_t c0 = wc.c0;
-                PathRun<64> run;
+                PathRun<kRun> run;
                 int64_t beg, d;
                 list_of(p.g, v, beg, d);
                 for (; s < wc.length; ++s) {
-                    int32_t to;
-                    if (walk_move(p, key, c0, s, v, start, to)) {
-                        v = to;
-                        list_of(p.g, v, beg, d);
-                        run.push(path, v);
-                        continue;
-                    }
-                    if (d == 0) break;
-                    const uint64_t r = draw(key, c0, (uint32_t)s, (uint32_t)v, 0u, (uint64_t)d);
                     int32_t u;
                     int64_t ub, ud;
-                    if (kHops) {
-                        const uint4 h = *(const uint4*)(p.g.hops + beg + (int64_t)r);
-                        u = (int32_t)h.x;
-                        ub = h.y;
-                        ud = h.z;
-                    } else {
-                        u = p.g.col[beg + (int64_t)r];
-                        list_of(p.g, u, ub, ud);
-                    }
                     bool move = true;
-                    if (kMH) {
+                    const bool moved = kMoves && walk_move(p, key, c0, s, v, start, u);
+                    if (moved) {
+                        if (kHops) list_of(p.g, u, ub, ud);
+                    } else {
+                        if (d == 0) break;
+                        const uint64_t r = draw(key, c0, (uint32_t)s, (uint32_t)v, 0u, (uint64_t)d);
+                        if (kHops) {
+                            const uint4 h = *(const uint4*)(p.g.hops + beg + (int64_t)r);
+                            u = (int32_t)h.x;
+                            ub = h.y;
+                            ud = h.z;
+                        } else {
+                            u = p.g.col[beg + (int64_t)r];
+                        }
+                    }
+                    if (!kHops) list_of(p.g, u, ub, ud);  // one wait for the lanes that moved and the others
+                    if (kMH && !moved) {
                         const uint64_t x = draw(key, c0, (uint32_t)s, (uint32_t)v, 4u, uint64_t(1) << 32);
                         move = x * (uint64_t)ud < ((uint64_t)d << 32);
                     }
@@ -960,7 +976,7 @@ constexpr int kLaneProbe = 4;
 // walkers, 261 against 263 at 12,288, 276 against 338 at 16,384).
 constexpr int64_t kLaneWalkMin = 12288;
 
-template <bool kMoves>
+template <bool kMoves, int kRun>
 __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
     const bool dg = p.bias == kNeighborDegree;
     const WalkVertex* __restrict__ vt = dg ? p.g.wvtx_deg : p.g.wvtx_ew;
@@ -987,46 +1003,45 @@ __global__ void __launch_bounds__(kBlock) k_walk_lane(WalkParams p) {
                 path[0] = v;
                 const int32_t start = v;
                 const uint32_t c0 = wc.c0;
-                PathRun<32> run;
+                PathRun<kRun> run;
                 for (; s < wc.length; ++s) {
                     int32_t to;
                     if (kMoves && walk_move(p, key, c0, s, v, start, to)) {
                         v = to;
-                        run.push(path, v);
-                        continue;
-                    }
-                    const WalkVertex x = vt[v];
-                    const int64_t beg = x.beg, d = x.d;
-                    const uint64_t W = x.W;
-                    uint64_t u = philox_u64(key.k0, key.k1, c0, (uint32_t)s, (uint32_t)v, 0u);
-                    // formed while the offsets load, not sunk past the test below
-                    asm volatile("" : "+v"(u));
-                    if (d == 0 || W == 0) break;
-                    const uint64_t r = range_reduce(u, W);
-                    const int sh = guide_shift(W, d, per);
-                    const uint64_t k = r >> sh;
-                    const WalkBucket bk = (gd + guide_base(beg, v, per))[k];
-                    int32_t nx = (uint32_t)(r - (k << sh)) >= (uint32_t)bk.S ? (int32_t)(bk.S >> 32) : bk.col;
-                    if ((uint32_t)(bk.S >> 32) == ~0u) {
-                        for (int64_t lo = bk.pos;; lo += kLaneProbe) {
-                            uint64_t S[kLaneProbe];
-                            int32_t y[kLaneProbe];
+                    } else {
+                        const WalkVertex x = vt[v];
+                        const int64_t beg = x.beg, d = x.d;
+                        const uint64_t W = x.W;
+                        uint64_t u = philox_u64(key.k0, key.k1, c0, (uint32_t)s, (uint32_t)v, 0u);
+                        // formed while the offsets load, not sunk past the test below
+                        asm volatile("" : "+v"(u));
+                        if (d == 0 || W == 0) break;
+                        const uint64_t r = range_reduce(u, W);
+                        const int sh = guide_shift(W, d, per);
+                        const uint64_t k = r >> sh;
+                        const WalkBucket bk = (gd + guide_base(beg, v, per))[k];
+                        int32_t nx = (uint32_t)(r - (k << sh)) >= (uint32_t)bk.S ? (int32_t)(bk.S >> 32) : bk.col;
+                        if ((uint32_t)(bk.S >> 32) == ~0u) {
+                            for (int64_t lo = bk.pos;; lo += kLaneProbe) {
+                                uint64_t S[kLaneProbe];
+                                int32_t y[kLaneProbe];
 #pragma unroll
-                            for (int j = 0; j < kLaneProbe; ++j) {
-                                const uint4 e = *(const uint4*)(er + beg + (lo + j < d ? lo + j : d - 1));
-                                S[j] = (uint64_t)e.x | ((uint64_t)e.y << 32);
-                                y[j] = (int32_t)e.z;
+                                for (int j = 0; j < kLaneProbe; ++j) {
+                                    const uint4 e = *(const uint4*)(er + beg + (lo + j < d ? lo + j : d - 1));
+                                    S[j] = (uint64_t)e.x | ((uint64_t)e.y << 32);
+                                    y[j] = (int32_t)e.z;
+                                }
+                                int c = 0;
+#pragma unroll
+                                for (int j = 0; j < kLaneProbe; ++j) c += S[j] <= r ? 1 : 0;
+                                nx = y[0];
+#pragma unroll
+                                for (int j = 1; j < kLaneProbe; ++j) nx = c == j ? y[j] : nx;
+                                if (c < kLaneProbe) break;
                             }
-                            int c = 0;
-#pragma unroll
-                            for (int j = 0; j < kLaneProbe; ++j) c += S[j] <= r ? 1 : 0;
-                            nx = y[0];
-#pragma unroll
-                            for (int j = 1; j < kLaneProbe; ++j) nx = c == j ? y[j] : nx;
-                            if (c < kLaneProbe) break;
                         }
+                        v = nx;
                     }
-                    v = nx;
                     run.push(path, v);
                 }
                 run.flush(path);
@@ -1743,6 +1758,15 @@ void launch_symmetric_check(RowPtr rowptr, const int32_t* col, int64_t n, int32_
     hipLaunchKernelGGL(k_symmetric_check, dim3((unsigned)g), dim3(kBlock), 0, s, rowptr, col, n, flag);
 }
 
+namespace {
+template <bool kMH, bool kMoves>
+void (*uniform_kernel(const WalkParams& p))(WalkParams) {
+    if (p.num_walkers < kUniformRunMin)
+        return p.g.hops ? k_walk_uniform<kMH, true, kMoves, 1> : k_walk_uniform<kMH, false, kMoves, 1>;
+    return p.g.hops ? k_walk_uniform<kMH, true, kMoves, 64> : k_walk_uniform<kMH, false, kMoves, 64>;
+}
+}  // namespace
+
 void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev) {
     if (p.num_walkers <= 0) return;
     const bool flat_n2v = p.bias == kNode2vec && p.w_return == p.w_common && p.w_common == p.w_outward &&
@@ -1751,8 +1775,9 @@ void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev) 
         int64_t g = (p.num_walkers + kBlock - 1) / kBlock;
         if (g > grid) g = grid;
         const bool mh = p.bias == kMetropolis;
-        launch_kernel(p.g.hops ? (mh ? k_walk_uniform<true, true> : k_walk_uniform<false, true>)
-                               : (mh ? k_walk_uniform<true, false> : k_walk_uniform<false, false>),
+        const bool moves = (p.restart | p.jump) != 0;
+        launch_kernel(mh ? (moves ? uniform_kernel<true, true>(p) : uniform_kernel<true, false>(p))
+                         : (moves ? uniform_kernel<false, true>(p) : uniform_kernel<false, false>(p)),
                       dim3((unsigned)g), dim3(kBlock), s, ev, p);
     } else {
         int64_t g = (p.num_walkers + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -1775,8 +1800,9 @@ void launch_walk(const WalkParams& p, int grid, hipStream_t s, LaunchEvents ev) 
             } else if (guide) {
                 int64_t gl = (p.num_walkers + kBlock - 1) / kBlock;
                 if (gl > grid) gl = grid;
-                if (moves) launch_kernel(k_walk_lane<true>, dim3((unsigned)gl), dim3(kBlock), s, ev, p);
-                else launch_kernel(k_walk_lane<false>, dim3((unsigned)gl), dim3(kBlock), s, ev, p);
+                launch_kernel(p.num_walkers < kLaneRunMin ? (moves ? k_walk_lane<true, 1> : k_walk_lane<false, 1>)
+                                                          : (moves ? k_walk_lane<true, 32> : k_walk_lane<false, 32>),
+                              dim3((unsigned)gl), dim3(kBlock), s, ev, p);
             } else if (moves) {
                 launch_kernel(k_walk_wave_moves, dim3((unsigned)g), dim3(kBlock), s, ev, p);
             } else {
