@@ -118,6 +118,7 @@ struct GraphDev {
     int32_t repeats = 0;            // some list holds a neighbor more than once (set with rank)
 };
 
+constexpr int kWeightPad = 64;   // words allocated past a resident graph's weights (read ahead by list scans)
 constexpr int kWaveMaxD = 512;   // longest weighted list of the wavefront kernels
 constexpr int kTabShift = 9;     // row of a list's first chunk: first edge >> kTabShift
 

@@ -505,7 +505,7 @@ csaw_status build_bias(csaw_graph g, int32_t kind, hipStream_t s) {
     }
     if (kind == kNeighborDegree && !g->ppos_deg) {
         int32_t* pp = nullptr;
-        if (!g->degw) HIP_OR_FAIL(hipMalloc((void**)&g->degw, std::max<int64_t>(g->m, 1) * sizeof(uint32_t)));
+        if (!g->degw) HIP_OR_FAIL(hipMalloc((void**)&g->degw, (g->m + kWeightPad) * sizeof(uint32_t)));
         if (!g->gtab_deg)
             HIP_OR_FAIL(hipMalloc((void**)&g->gtab_deg, (size_t)chunk_table_rows(g->m) * kChunkGroups * sizeof(uint64_t)));
         if (!g->wtot_deg) HIP_OR_FAIL(hipMalloc((void**)&g->wtot_deg, std::max<int64_t>(g->n, 1) * sizeof(uint64_t)));
@@ -955,7 +955,7 @@ csaw_status csaw_graph_create(int64_t n, int64_t m, const int64_t* rowptr, const
     // (the column ids as whole 16-byte quads, which node2vec lookups read at 16-byte steps from its start)
     if ((e = device_malloc((void**)&g->dflag, 256)) != hipSuccess ||
         (e = device_malloc((void**)&g->col, align_up(std::max<int64_t>(m, 1), 4) * sizeof(int32_t))) != hipSuccess ||
-        (edge_weight && (e = device_malloc((void**)&g->ew, std::max<int64_t>(m, 1) * sizeof(uint32_t))) != hipSuccess))
+        (edge_weight && (e = device_malloc((void**)&g->ew, (m + kWeightPad) * sizeof(uint32_t))) != hipSuccess))
         return cleanup(fail(CSAW_ERR_OUT_OF_MEMORY, "graph allocation failed: %s", hipGetErrorString(e)));
     if ((m > 0 && (e = hipMemcpyAsync(g->col, col, m * sizeof(int32_t), hipMemcpyHostToDevice, s)) != hipSuccess) ||
         (edge_weight && m > 0 &&

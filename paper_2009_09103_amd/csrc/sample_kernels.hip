@@ -1708,7 +1708,8 @@ __device__ __forceinline__ int32_t lds_upper(const uint64_t* a, int32_t n, uint6
 
 // m = max{i : S_i <= r} inside one weighted list (weights w, first edge beg,
 // length d, prefix acc before it), with S_m and b_m: a scan of the list for
-// up to kWaveMaxD weights, 64 of them in flight; else through the graph's
+// up to kWaveMaxD weights, kWeightPad of them in flight (past the list's end too, where
+// r, below its total, is never looked for; the arrays are padded); else through the graph's
 // chunk prefix table (the running chunk totals, the chunk's group prefixes, one group).
 struct alignas(4) WeightQuad {
     uint32_t x[4];
@@ -1716,39 +1717,37 @@ struct alignas(4) WeightQuad {
 __device__ __forceinline__ void list_search(const uint32_t* __restrict__ w, const uint64_t* __restrict__ gtab,
                                             const uint64_t* __restrict__ ctab, int64_t beg, int64_t d, uint64_t acc,
                                             uint64_t r, int64_t& m, uint64_t& Sm, uint32_t& bm) {
-    constexpr int kQuads = 16;
-    if (d < 4) {
-        fine_scan_global(w, 0, d, acc, r, m, Sm, bm);
-        return;
-    }
+    constexpr int kQuads = kWeightPad / 4;
     if (d <= kWaveMaxD) {
-        const int32_t n = (int32_t)d;
-        for (int32_t i0 = 0; i0 < n; i0 += 4 * kQuads) {
-            WeightQuad y[kQuads];  // the last one ends with the list: the weights it shares with another count once
+        for (int32_t i0 = 0; i0 < (int32_t)d; i0 += 4 * kQuads) {
+            WeightQuad y[kQuads];
 #pragma unroll
-            for (int q = 0; q < kQuads; ++q) y[q] = *(const WeightQuad*)(w + (i0 + 4 * q < n - 4 ? i0 + 4 * q : n - 4));
-            uint64_t run = acc;
-            bool found = false;
+            for (int q = 0; q < kQuads; ++q) y[q] = *(const WeightQuad*)(w + i0 + 4 * q);
+            uint64_t run = acc;  // the quad that ends above r, then the weight
+            int32_t c = 0;
 #pragma unroll
             for (int q = 0; q < kQuads; ++q) {
-                const int32_t i = i0 + 4 * q, at = i < n - 4 ? i : n - 4;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool in = at + j >= i;
-                    const uint64_t next = run + y[q].x[j];
-                    if (in && !found) {
-                        if (next > r) {
-                            found = true;
-                            m = at + j;
-                            Sm = run;
-                            bm = y[q].x[j];
-                        }
-                        run = next;
-                    }
-                }
+                run += (uint64_t)y[q].x[0] + y[q].x[1] + ((uint64_t)y[q].x[2] + y[q].x[3]);
+                const bool le = run <= r;
+                c += le ? 1 : 0;
+                acc = le ? run : acc;
             }
-            if (found) return;
-            acc = run;
+            if (c == kQuads) continue;
+            uint32_t z0 = y[0].x[0], z1 = y[0].x[1], z2 = y[0].x[2], z3 = y[0].x[3];
+#pragma unroll
+            for (int q = 1; q < kQuads; ++q) {
+                const bool at = q == c;
+                z0 = at ? y[q].x[0] : z0;
+                z1 = at ? y[q].x[1] : z1;
+                z2 = at ? y[q].x[2] : z2;
+                z3 = at ? y[q].x[3] : z3;
+            }
+            const uint64_t s0 = acc + z0, s1 = s0 + z1, s2 = s1 + z2;
+            const int32_t k = (s0 <= r ? 1 : 0) + (s1 <= r ? 1 : 0) + (s2 <= r ? 1 : 0);
+            Sm = k == 0 ? acc : k == 1 ? s0 : k == 2 ? s1 : s2;
+            bm = k == 0 ? z0 : k == 1 ? z1 : k == 2 ? z2 : z3;
+            m = i0 + 4 * c + k;
+            return;
         }
         return;
     }
@@ -1793,9 +1792,11 @@ inline size_t layer_lds_bytes(int32_t mf, int32_t L) {
 // are read with eight loads of a kind in flight, each lane summing a run of the
 // frontier (one scan per layer); a pick is looked for in the earlier frontiers by
 // binary search, and not at all in the last layer.
-// 2,000 instances of 512 seeds, two layers of 64 degree-biased picks on R-MAT 22: 270 us
-// before, 198 now, 90 through a walk guide (110 there with the positive positions of every
-// vertex read and its record in two tables).
+// 2,000 instances of 512 seeds, two layers of 64 degree-biased picks on R-MAT 22: 90 us
+// through a walk guide (110 with the positive positions of every vertex read and its
+// record in two tables). Without one (list_search), calls on new seeds: 324 us with 16
+// weights in flight and linear chunk walks, 253 with 64 compared one by one, 216 with
+// their quads compared first; 500 instances of 16 seeds, one layer of 5: 80, 99 and 68.
 constexpr int kLayerPer = 8;
 __global__ void __launch_bounds__(kWave) k_layer_sample(LayerParams p) {
     extern __shared__ __align__(16) unsigned char layer_lds[];
