@@ -241,7 +241,8 @@ csaw_status csaw_sample_bound(csaw_graph g, const csaw_sample_args* args, int64_
  * wavefront: every unbiased list, every weighted list whose weight array has
  * its walk guide, and the weighted lists without one of at most
  * max(bound16, bound32) candidates, which each lane scans. The other weighted
- * lists take a whole wavefront each. 0 for both leaves the scan out.
+ * lists take a whole wavefront each. 0 for both leaves the scan out, as do calls
+ * with CSAW_DIRECT_ONLY.
  * Results never depend on these bounds (the draws are keyed by their
  * counters and taken in slot order either way); only the speed does.
  * The setting belongs to the graph and applies to later calls. */
@@ -261,7 +262,7 @@ csaw_status csaw_get_tuning(csaw_graph g, csaw_tuning* tuning);
  * setting (warm-up call, then `reps` timed calls; reps in [1, 100]), keeps
  * the fastest median on the graph and writes it to *chosen (HOST, nullable).
  * The candidates are 0, 8, 16 and 32 as the longest list that a lane scans; where the
- * call scans none (unbiased, or by guides) it runs once and the setting stays.
+ * call scans none (unbiased, by guides, or by direct draws) it runs once and the setting stays.
  * Its calls build no walk guide and count towards none.
  * Other calls on the same graph while it runs use whichever candidate is
  * current; their results are unchanged.
