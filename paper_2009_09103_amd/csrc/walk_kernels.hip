@@ -1472,13 +1472,14 @@ __device__ __forceinline__ uint32_t walk_step_rank(const WalkParams& p, const Ra
         }
     }
     uint64_t rem = r - prefix(j0, C0);
-    if (n_t && pos_t >= j0) {
-        const uint64_t gap = (uint64_t)wo * (pos_t - j0), run = (uint64_t)wr * n_t;
+    if (pos_t + n_t > j0) {  // copies of t from j0 on (a chunk may begin among them)
+        const uint32_t from = pos_t > j0 ? pos_t : j0, left = pos_t + n_t - from;
+        const uint64_t gap = (uint64_t)wo * (from - j0), run = (uint64_t)wr * left;
         if (rem >= gap) {
             rem -= gap;
-            if (rem < run) return pos_t + small_quotient(rem, wr, inv[2]);
+            if (rem < run) return from + small_quotient(rem, wr, inv[2]);
             rem -= run;
-            j0 = pos_t + n_t;
+            j0 = from + left;
         }
     }
     return j0 + small_quotient(rem, wo, inv[0]);
