@@ -1127,7 +1127,7 @@ __global__ void __launch_bounds__(kBlock) k_walk_wave_guide(WalkParams p) {
 // 31 with every entry looked up, 28 with the dense stretches staged in LDS,
 // 25.0 with the next chunks' loads issued a block ahead, 24.3 at six waves per
 // SIMD (five or seven: 25.1, 25.3). The vector unit is then busy 45% of the
-// time, the address units 54%, and 87 GB come from beyond the L2s (3.6 TB/s).
+// time, the address units 54%, and 179 GB come from beyond the L2s (7.3 TB/s).
 constexpr int kRankQ = 4;                        // chunks of 64 entries looked up together
 constexpr uint32_t kRankWin = 256 * kRankQ;      // entries of the longer list staged for them
 struct RankStep {
