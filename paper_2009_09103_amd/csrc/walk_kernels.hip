@@ -102,11 +102,14 @@ __device__ __forceinline__ void count_steps(int64_t steps, unsigned long long* c
 // with 16, 2.37 with 32 and 2.25 with 64, although the registers cost
 // occupancy; 262,144 weighted walkers: 1.05 ms with 8 to 32, 1.12 with 64. A
 // launch whose lines stay in the L2 until they are full only pays for the run, in
-// registers and in each step's chain, and stores every entry at once (runs of 1):
-// R-MAT 22, length 80, runs of 1 against the long ones: unbiased 74 and 118 us for 1,000
-// walkers, 128 and 158 for 65,536, 241 and 202 for 131,072; weighted, by lanes, 254 and
-// 273 for 12,288, 260 and 278 for 32,768, 304 and 290 for 65,536.
-constexpr int64_t kUniformRunMin = 98304, kLaneRunMin = 57344;
+// registers and in each step's chain, and stores every entry at once (runs of 1).
+// R-MAT 22, length 80, as it is (most walkers end early) / symmetrised (all walk on),
+// runs of 1 against the long ones: unbiased 92 against 126 us / 116 against 131 for 16,384
+// walkers, 98 against 132 / 126 against 136 for 32,768, 123 against 149 / 184 against 168
+// for 65,536; weighted, by lanes, 252 against 270 / 271 against 290 for 16,384, 256 against
+// 275 / 279 against 294 for 32,768, 302 against 287 / 335 against 309 for 65,536. The lines
+// lie where the symmetrised graph's figures cross.
+constexpr int64_t kUniformRunMin = 49152, kLaneRunMin = 45056;
 typedef int32_t PathQuad __attribute__((ext_vector_type(4), aligned(4)));
 template <int kPathRun>
 struct PathRun {
@@ -155,13 +158,18 @@ __device__ __forceinline__ void list_of(const GraphDev& g, int32_t v, int64_t& b
 // kMoves: the call restarts or jumps. Lanes that move wait for their list with the
 // others (in a step of their own, 1,000 walkers x 80 with restarts took 189 us on
 // R-MAT 22, 144 now); walks without moves do without the test, and its registers
-// (262,144 Metropolis-Hastings walkers x 80: 290 us with it, 239 without).
-// kRun: see PathRun.
+// (262,144 unbiased walkers x 80: 389 us with it, 346 without).
+// kRun: see PathRun. Metropolis-Hastings walkers stay where they are for many steps
+// and find the list's line again in the L2 of their die: with long runs three
+// wavefronts per SIMD hold as many lists as fit it (symmetrised R-MAT 22, 2^20
+// walkers x 80: 1.03 ms with three, 1.20 with four, 1.08 with two; R-MAT 22 as it
+// is 0.91, 0.89, 1.03). Unbiased walkers leave and take four (2.03, 2.06 with three).
 // kMH: Metropolis-Hastings (Section II-A): the uniform pick u is a proposal,
 // accepted iff x * deg(u) < deg(v) * 2^32 for x in [0, 2^32) drawn with
 // counter (walker id, step, v, 4); a rejected proposal is a step that stays.
 template <bool kMH, bool kHops, bool kMoves, int kRun>
-__global__ void __launch_bounds__(kBlock) k_walk_uniform(WalkParams p) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, kMH && kRun > 1 ? 3 : 8)))
+k_walk_uniform(WalkParams p) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t w0 = blockIdx.x * (int64_t)blockDim.x; w0 < p.num_walkers; w0 += stride) {
         const int64_t w = w0 + threadIdx.x;

@@ -29,3 +29,10 @@ def test_runs(bias, line, length, moves):
         got = paths.cpu().numpy()
         np.testing.assert_array_equal(got[ids], ref)
         assert steps == int((got[:, 1:] >= 0).sum())
+
+
+@pytest.mark.parametrize("moves", [(0, 0), (1 << 29, 1 << 28)])
+@pytest.mark.parametrize("bias,line", [(0, 49152), (4, 49152), (1, 45056)])
+@pytest.mark.parametrize("length", [1, 33, 65])
+def test_runs_from_fewer_walkers(bias, line, length, moves):
+    test_runs(bias, line, length, moves)
